@@ -224,6 +224,7 @@ struct LaunchSink {
 // While a sink is installed on this thread, the pipeline launchers append to it and
 // launch nothing.
 void set_launch_sink(LaunchSink* s);
+LaunchSink* launch_sink();  // this thread's, or null
 
 struct Bracket {
   int kid;
@@ -243,6 +244,10 @@ struct Tuning {
 
 hipError_t launch_ntt(const NttArgs& a, int ntransforms, bool inverse, hipStream_t s,
                       const Tuning& t = Tuning());
+// The same with one workgroup per transform (one pass over memory); natural: the
+// transformed side in natural instead of bit-reversed order.  The inverse needs a.scale.
+hipError_t launch_ntt_whole(const NttArgs& a, int ntransforms, bool inverse, bool natural, hipStream_t s);
+bool ntt_whole_wanted(int logN, bool natural, long long ntransforms);
 hipError_t launch_ntt_cols(const NttArgs& a, int ntransforms, bool inverse, hipStream_t s,
                            const Tuning& t = Tuning());
 hipError_t launch_rows_fused(const RowsArgs& a, int mode, hipStream_t s, const Tuning& t = Tuning());

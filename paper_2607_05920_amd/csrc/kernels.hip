@@ -3,102 +3,10 @@
 //   CRT reconstruction (residues -> limbs, on the i8 matrix cores), relinearization
 //   compose, rescale.
 #include <algorithm>
-#include <utility>
 
-#include "fhe_internal.h"
+#include "device_common.h"
 
 namespace fhe {
-
-typedef v4i_t v4i;
-typedef int v16i __attribute__((ext_vector_type(16)));
-
-// Makes a register value opaque to the optimizer.  Uses here: multipliers that must
-// stay 64-bit multiply-adds (not shifts and adds), values that must be computed where
-// written (not re-derived later), and per-iteration offsets of persistent loops (not
-// hoisted out of the loop, where each would hold a register).
-__device__ __forceinline__ void opaque(uint32_t& v) { asm volatile("" : "+v"(v)); }
-
-// A pointer the caller knows to be equal on every lane of the wave, moved to scalar
-// registers: buffer resources need it there, and stores through it take the scalar
-// base + 32-bit lane offset form (no 64-bit address arithmetic per lane).
-template <typename T>
-__device__ __forceinline__ T* wave_uniform(T* p) {
-  const uint64_t v = (uint64_t)p;
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return (T*)(((uint64_t)hi << 32) | lo);
-}
-
-// Raw buffer over `bytes` bytes from the wave-uniform `base`.  Loads at lane offsets at
-// or beyond `bytes` return zero (the buffer range check), which stands in for clamping
-// and masking rows past the end of a polynomial.
-// `bytes` is uniform too: it is moved to a scalar register, so that a value the compiler
-// happened to compute in vector registers does not make the descriptor divergent (which
-// would wrap every access in a loop over lanes).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_buffer(const uint32_t* base, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)__builtin_amdgcn_readfirstlane(bytes),
-                                           0x00020000);
-}
-
-__device__ __forceinline__ uint32_t buffer_word(__amdgpu_buffer_rsrc_t r, uint32_t byte_off) {
-  return __builtin_amdgcn_raw_buffer_load_b32(r, (int)byte_off, 0, 0);
-}
-
-// Global store at a byte offset from a wave-uniform base (the global address space is
-// stated: the pointer's provenance is lost through the scalar move).
-__device__ __forceinline__ void store_at(uint32_t* base, uint32_t byte_off, uint32_t v) {
-  typedef __attribute__((address_space(1))) char gchar;
-  typedef __attribute__((address_space(1))) uint32_t gu32;
-  *(gu32*)((gchar*)base + byte_off) = v;
-}
-
-// a * b + c as one v_mad_i64_i32.  b must be opaque (a register the compiler cannot
-// see the value of), or the product is strength-reduced into shifts and adds; and two
-// terms of one sum must not share a multiplier register, or the compiler merges them
-// into a 64 x 64-bit product.  (Not inline asm: a compiler-visible instruction gets
-// the wait states after the matrix-core op that produced its operand.)
-__device__ __forceinline__ int64_t mad_i64(int32_t a, uint32_t b, int64_t c) { return (int64_t)a * (int32_t)b + c; }
-
-// Exchanges between the wave's lane halves with v_permlane32_swap (a vector op, no LDS
-// round trip).  swap(x, x) returns {r0, r1}: r0 holds, in lanes 32..63, x of the lane 32
-// below (lanes 0..31 keep theirs); r1 holds, in lanes 0..31, x of the lane 32 above.
-__device__ __forceinline__ int64_t from_lane_below(int64_t x) {  // valid in lanes 32..63
-  const uint32_t lo = (uint32_t)x, hi = (uint32_t)((uint64_t)x >> 32);
-  const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-  const auto u = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-  return (int64_t)(((uint64_t)u[0] << 32) | l[0]);
-}
-__device__ __forceinline__ int64_t from_lane_above(int64_t x) {  // valid in lanes 0..31
-  const uint32_t lo = (uint32_t)x, hi = (uint32_t)((uint64_t)x >> 32);
-  const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-  const auto u = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-  return (int64_t)(((uint64_t)u[1] << 32) | l[1]);
-}
-// x plus x of the lane 32 apart, in every lane
-__device__ __forceinline__ uint64_t sum_lane_halves(uint64_t x) {
-  const uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
-  const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-  const auto u = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-  return ((((uint64_t)u[0] << 32) | l[0])) + ((((uint64_t)u[1] << 32) | l[1]));
-}
-
-// o += cin over 4 limbs (unsigned words, least significant first), cin signed 64-bit:
-// one add-with-carry chain over (cin_lo, cin_hi, ext, ext), ext the sign extension.
-// Returns the signed carry out of the top limb, in {-1, 0, 1}.
-__device__ __forceinline__ int32_t add_carry4(uint32_t (&o)[4], int64_t cin) {
-  const uint32_t lo = (uint32_t)cin, hi = (uint32_t)((uint64_t)cin >> 32);
-  const uint32_t ext = (uint32_t)((int32_t)hi >> 31);
-  uint32_t co;
-  asm("v_add_co_u32 %0, vcc, %0, %5\n\t"
-      "v_addc_co_u32 %1, vcc, %1, %6, vcc\n\t"
-      "v_addc_co_u32 %2, vcc, %2, %7, vcc\n\t"
-      "v_addc_co_u32 %3, vcc, %3, %7, vcc\n\t"
-      "v_addc_co_u32 %4, vcc, 0, %7, vcc"
-      : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]), "+v"(o[3]), "=&v"(co)
-      : "v"(lo), "v"(hi), "v"(ext)
-      : "vcc");
-  return (int32_t)co;
-}
 
 static thread_local EventRecorder* g_rec = nullptr;
 static thread_local long long g_launches = 0;
@@ -107,25 +15,7 @@ long long kernel_launch_count() { return g_launches; }
 
 static thread_local LaunchSink* g_sink = nullptr;
 void set_launch_sink(LaunchSink* s) { g_sink = s; }
-
-// Issues a launch of `single` (one struct argument), or records it with its
-// stage-batched entry point `multi` while a sink is installed.
-template <typename A>
-static hipError_t emit(const void* single, const void* multi, dim3 grid, dim3 block, size_t lds, hipStream_t st,
-                       const A& a) {
-  if (g_sink) {
-    LaunchRec r;
-    r.multi = multi;
-    r.grid = grid;
-    r.block = block;
-    r.lds = lds;
-    r.args.assign((const char*)&a, (const char*)&a + sizeof(A));
-    g_sink->recs.push_back(std::move(r));
-    return hipSuccess;
-  }
-  void* args[] = {(void*)&a};
-  return hipLaunchKernel(single, grid, block, args, lds, st);
-}
+LaunchSink* launch_sink() { return g_sink; }
 
 void bracket_begin(int kid, hipStream_t s) {
   ++g_launches;
@@ -150,120 +40,6 @@ void bracket_end(int kid, hipStream_t s, double work) {
 // register phase works on elements {u T + j} ("strided"), the other on
 // {16 j + u} ("contiguous"); one LDS exchange connects them.  Forward passes run
 // strided then contiguous; inverse passes the reverse.
-
-// Workgroup coordinates within one launch's grid.  A kernel body takes them as an
-// argument, so that it runs either as its own launch (own_blk) or as one cell's
-// segment of a stage-batched launch over many cells (cell_of).
-struct Blk {
-  uint32_t x, y, nx;  // block index (x, y) and the grid's width in x
-};
-
-__device__ __forceinline__ Blk own_blk() { return Blk{blockIdx.x, blockIdx.y, gridDim.x}; }
-
-// The cell that workgroup blockIdx.x of a stage-batched launch belongs to: seg[c].off
-// (ascending, multiples of 8, so that a workgroup's XCD, blockIdx.x mod 8, is the one
-// its own launch would give it) is the first workgroup of cell c, whose own grid is
-// gx x gy.  Workgroups past a cell's grid (the rounding to 8) take -1 and exit.
-__device__ __forceinline__ int cell_of(const CellSeg* seg, int ncells, Blk& bk) {
-  const uint32_t w = blockIdx.x;
-  int lo = 0, hi = ncells;  // the last cell with off <= w
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (seg[mid].off <= w) lo = mid;
-    else hi = mid;
-  }
-  const CellSeg sg = seg[lo];
-  const uint32_t l = w - sg.off;
-  if (l >= sg.gx * sg.gy) return -1;
-  bk = Blk{l % sg.gx, l / sg.gx, sg.gx};
-  return lo;
-}
-
-// A pointer read from memory (a stage-batched launch's table of cell arguments) is
-// generic to the compiler, and its loads become flat loads into vector registers even
-// where the address is wave-uniform.  Held as a global-memory pointer, its loads are
-// global ones, or scalar ones where uniform, as in a single launch.
-template <typename T>
-using gptr = const __attribute__((address_space(1))) T*;
-
-// One prime's twiddle table (Shoup pairs) through such a pointer.
-struct TwTab {
-  gptr<uint64_t> p;
-  __device__ __forceinline__ uint2 operator[](int i) const {
-    const uint64_t v = p[i];
-    return make_uint2((uint32_t)v, (uint32_t)(v >> 32));
-  }
-  // entries i and i + 1 in one 16-byte load (i even)
-  __device__ __forceinline__ v4i_t pair(int i) const { return *(gptr<v4i_t>)(p + i); }
-};
-__device__ __forceinline__ TwTab tw_table(const uint2* t, int p) {
-  return TwTab{(gptr<uint64_t>)t + (long long)p * kNMax};
-}
-
-// Low 32 bits of a b + c in one v_mad_u64_u32 (the compiler would otherwise narrow
-// the expression to a 32-bit multiply and an add).
-__device__ __forceinline__ uint32_t mad_lo(uint32_t a, uint32_t b, uint32_t c) {
-  uint64_t r;
-  asm("v_mad_u64_u32 %0, vcc, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"((uint64_t)c) : "vcc");
-  return (uint32_t)r;
-}
-
-__device__ __forceinline__ void ct_bfly(uint32_t& X, uint32_t& Y, uint2 w, uint32_t q,
-                                        uint32_t two_q) {
-  // Lazy Cooley-Tukey butterfly: X, Y in [0, 4q) -> [0, 4q).  With the Shoup product
-  // t = Y w - qh q in [0, 2q), nt = qh q - Y w = -t (mod 2^32); then X + t = X - nt
-  // and X - t + 2q = X + nt + 2q (one three-input add).  The forward table holds
-  // (-w mod 2^32, floor(w 2^32 / q)), so nt = qh q + Y (-w) is one multiply and one
-  // multiply-add: 7 operations per butterfly.
-  const uint32_t x = csub(X, two_q);
-  const uint32_t qh = __umulhi(Y, w.y);
-  const uint32_t nt = mad_lo(qh, q, Y * w.x);
-  X = x - nt;
-  Y = x + nt + two_q;
-}
-
-__device__ __forceinline__ void gs_bfly(uint32_t& X, uint32_t& Y, uint2 w, uint32_t q,
-                                        uint32_t two_q) {
-  // Lazy Gentleman-Sande butterfly: X, Y in [0, 2q) -> [0, 2q); the Shoup product of
-  // d = X - Y + 2q is d w - qh q = d w + qh (-q), one multiply-add.
-  const uint32_t x = X, y = Y;
-  X = csub(x + y, two_q);
-  const uint32_t d = x - y + two_q;
-  const uint32_t qh = __umulhi(d, w.y);
-  Y = mad_lo(qh, 0u - q, d * w.x);
-}
-
-// Inverse twiddles from the forward table.  The bit-reversed index (over the table's
-// 16 bits) of 2H - 1 - i is 2^16 minus that of H + i (H a power of two, i < H), and
-// psi^(2^16) = -1, so psi^-bitrev(H + i) = -v for v = psi^bitrev(2H - 1 - i): for a
-// stage of H groups starting at table index mi H - H (mi the caller's mirrored
-// multiplier), group g's inverse twiddle is minus forward entry mi H - 1 - g.  That
-// entry holds (-v mod 2^32, floor(v 2^32 / q)); mirror_tw makes it the Shoup pair of v
-// (the negation opaque, else the compiler moves it into every butterfly), which
-// gs_bfly_neg takes.
-__device__ __forceinline__ uint2 mirror_tw(uint2 f) {
-  uint32_t v = 0u - f.x;
-  opaque(v);
-  return make_uint2(v, f.y);
-}
-// The same for a wave-uniform twiddle: the negation stays in scalar registers (the
-// compiler rejects the constraint for a value it cannot keep there).
-__device__ __forceinline__ uint2 mirror_tw_s(uint2 f) {
-  uint32_t v = 0u - f.x;
-  asm volatile("" : "+s"(v));
-  return make_uint2(v, f.y);
-}
-
-// gs_bfly with the twiddle given as -v (the Shoup pair of v): (X - Y)(-v) = (Y - X) v,
-// the Shoup product of d = Y - X + 2q.
-__device__ __forceinline__ void gs_bfly_neg(uint32_t& X, uint32_t& Y, uint2 v, uint32_t q,
-                                            uint32_t two_q) {
-  const uint32_t x = X, y = Y;
-  X = csub(x + y, two_q);
-  const uint32_t d = y - x + two_q;
-  const uint32_t qh = __umulhi(d, v.y);
-  Y = mad_lo(qh, 0u - q, d * v.x);
-}
 
 // Threads per workgroup: column passes of 2^8 and 2^7 points take 64 columns of 1024
 // threads and 64 of 512 (256- and 128-byte runs per row); row passes, and column passes
@@ -483,16 +259,6 @@ __global__ __launch_bounds__(BLK) void ntt_pass_kernel_multi(
 }
 
 // ---------------------------------------------------------------------------- fused row pass
-// Every LDS exchange of the row passes stays inside one T-thread slot, and a slot
-// (T <= 16 threads) never straddles two waves: a wave-level ordering point is enough
-// between the writes and the reads (a wave's LDS accesses are performed in order), so
-// the two waves of a workgroup never wait for each other.
-__device__ __forceinline__ void slot_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // The last forward pass, the pointwise products and the first inverse pass touch
 // the same n-point rows: one kernel loads each input row once, finishes its forward
 // transform in registers, multiplies (Eq. ntt_mul), runs the first inverse stages

@@ -1,0 +1,50 @@
+"""GPU: the fused kernels at the sizes where they can go wrong (edges of tiles, remainders,
+the smallest and largest of their ranges), bit for bit against the oracle or against the
+general path."""
+import numpy as np
+import pytest
+
+import paper_2607_05920_amd as fhe
+from oracle import ntt as ontt
+from tests.gpu_helpers import check, dev, host, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need an MI355X"
+    c = fhe.Context(1555, 1555)
+    yield c
+    c.close()
+
+
+# (logN, primes, polynomials, natural order): one transform, counts that leave the last of
+# the eight runs short, and the smallest counts that take one workgroup per transform at
+# 2^15 and 2^16 points
+@pytest.mark.parametrize("logN,nprimes,count,natural", [
+    (10, 1, 1, True), (10, 3, 11, False), (11, 5, 3, True), (12, 3, 5, True), (13, 9, 1, False), (13, 3, 7, True),
+    (14, 1, 1, True), (14, 5, 5, False), (15, 4, 8, True), (15, 7, 32, False), (16, 4, 16, True)])
+def test_ntt_whole(ctx, logN, nprimes, count, natural):
+    say(f"ntt whole logN={logN} primes={nprimes} count={count} natural={natural}")
+    prime0, N = 2, 1 << logN
+    rng = np.random.default_rng(100 * logN + count)
+    q = np.array([ctx.prime_info(prime0 + p)[0] for p in range(nprimes)], dtype=np.uint64)
+    data = (rng.integers(0, 1 << 62, (count, nprimes, N), dtype=np.uint64) % q[:, None]).astype(np.uint32)
+    data[0, 0, :7] = q[0] - 1
+    t = dev(data)
+    ctx.ntt(logN, nprimes, t, count=count, bitrev=not natural, prime0=prime0)
+    fwd = host(t, data.shape).copy()
+    rev = np.array([int(format(i, f"0{logN}b")[::-1], 2) for i in range(N)])
+    for c, p in {(0, 0), (count - 1, nprimes - 1)}:
+        psi = pow(ctx.prime_info(prime0 + p)[1], (1 << 16) // N, int(q[p]))
+        want = ontt.ntt_fast([int(v) for v in data[c, p]], int(q[p]), psi)
+        check([int(v) for v in (fwd[c, p] if natural else fwd[c, p][rev])], want, f"transform {c} prime {p}")
+    if logN >= 15:  # one polynomial at a time takes the two-pass transforms
+        for c in range(count):
+            one = dev(data[c])
+            ctx.ntt(logN, nprimes, one, count=1, bitrev=not natural, prime0=prime0)
+            assert np.array_equal(host(one, data[c].shape), fwd[c]), f"polynomial {c}"
+    ctx.ntt(logN, nprimes, t, count=count, inverse=True, bitrev=not natural, prime0=prime0)
+    assert np.array_equal(host(t, data.shape), data)
