@@ -10,7 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libfhe_mi355x.so")
-SOURCES = ["api.hip", "kernels.hip", "ntt_whole.hip", "ops.hip", "encode.cpp", "boot.cpp"]
+SOURCES = ["api.hip", "kernels.hip", "ntt_whole.hip", "lift_cols.hip", "rows_mid.hip", "crt_cols.hip", "ops.hip", "encode.cpp", "boot.cpp"]
 
 
 def hipcc() -> str:

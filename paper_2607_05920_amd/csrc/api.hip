@@ -243,9 +243,10 @@ struct LiftTab {
 // output limbs Lout).
 struct CrtTab {
   v4i_t* A = nullptr;        // MFMA A fragments [tile][k-block][lane]
-  uint32_t* d = nullptr;     // [k] = [2^e c_k]_(q_k)
   uint32_t* mneg = nullptr;  // limbs of (-M) mod 2^(32 Lout), 8 ntiles words
-  uint32_t* eneg = nullptr;  // limbs of (-2^e) mod 2^(32 Lout), 8 ntiles words
+  uint32_t* eneg = nullptr;  // limbs of the constant row mod 2^(32 Lout), 8 ntiles words:
+                             // 0x80808080 sum_k M/q_k + sum_k d_k M/q_k - 2^e, d_k = [2^e c_k]_(q_k)
+  uint64_t frac0 = 0;        // sum_k d_k floor(2^54 / q_k) + 2^44 (the offset of the quotient)
   int ntiles = 0;
 };
 
@@ -264,7 +265,7 @@ struct fhe_ctx {
   uint2* nscale[kLogNMax + 1] = {};  // N^-1 per prime
   uint32_t* liftT = nullptr;
   int TS = 0, Lmax = 0;
-  uint32_t* rq = nullptr;  // [k] = floor(2^56 / q_k)
+  uint32_t* rq = nullptr;  // [k] = floor(2^54 / q_k)
   std::map<int, std::vector<uint32_t>> crt_c;             // per K: c_k = [(M/q_k)^-1]_(q_k)
   std::map<std::tuple<int, int, int>, CrtTab> crt;        // per (K, e, Lout)
   std::map<std::pair<int, int>, uint2*> cscale;           // per (logN, K): [N^-1 2^32 c_k]_(q_k), Shoup
@@ -330,10 +331,9 @@ struct fhe_evk {
   uint32_t g = 0;  // 0: relinearization key (of s^2); odd g: switching key of kappa_g(s)
   int logN = 0, logQ = 0, logP = 0;
   std::vector<uint32_t> hb, ha;  // host limbs [L_PQ][N]
-  // per logq: [2][K_r][N] in NTT form, each row of the fused pass transposed into its
-  // register order (launch_row_transpose) for rows of 2^(logN/2) points; for odd logN,
-  // ntt_alt holds the same for rows of 2^(logN - logN/2) points
-  std::map<int, uint32_t*> ntt, ntt_alt;
+  // per logq: [2][K_r][N] in NTT form, each row of N / 16 points transposed into the fused
+  // pass's register order (launch_row_transpose)
+  std::map<int, uint32_t*> ntt;
 };
 
 namespace {
@@ -451,12 +451,11 @@ const CrtTab* crt_table(fhe_ctx* c, int K, int e, int Lout, hipError_t* err) {
   const int nkb = (K + 31) / 32, ntiles = (Lout + 7) / 8, Lp = 8 * ntiles;
   CrtTab t;
   t.ntiles = ntiles;
-  std::vector<uint32_t> d(c->Kpad, 0);
-  for (int k = 0; k < K; ++k) d[k] = (uint32_t)mulmod64(powmod(2, e, c->q[k]), ck[k], c->q[k]);
+  t.frac0 = 1ull << 44;
   // V_k = (M / q_k) mod 2^(32 Lout) in balanced limbs D_kl in [-0x80808080, 0x7F7F7F7F];
-  // vsum = sum_k V_k mod 2^(32 Lout)
+  // vsum = sum_k V_k and dsum = sum_k d_k V_k mod 2^(32 Lout)
   std::vector<int64_t> D((size_t)K * Lp, 0);
-  std::vector<uint32_t> vsum(Lout, 0);
+  std::vector<uint32_t> vsum(Lout, 0), dsum(Lout, 0);
   for (int k = 0; k < K; ++k) {
     std::vector<uint32_t> v(Lout, 0);
     v[0] = 1;
@@ -469,6 +468,10 @@ const CrtTab* crt_table(fhe_ctx* c, int K, int e, int Lout, hipError_t* err) {
       carry = u > 0x7F7F7F7FLL ? 1 : 0;
       D[(size_t)k * Lp + l] = u - (carry << 32);
     }
+    const uint32_t d = (uint32_t)mulmod64(powmod(2, e, c->q[k]), ck[k], c->q[k]);
+    t.frac0 += (uint64_t)d * ((1ull << 54) / c->q[k]);
+    mul_small_trunc(v, d);
+    add_trunc(dsum, v);
   }
   // A fragments: lane (r, h) of tile t, k-block kb holds bytes i < 16 of row r
   // (digit plane b = r / 8 of limb 8 t + r % 8) at k = 32 kb + 16 h + i
@@ -495,7 +498,7 @@ const CrtTab* crt_table(fhe_ctx* c, int K, int e, int Lout, hipError_t* err) {
   mneg[0] = 1;
   for (int j = 0; j < K; ++j) mul_small_trunc(mneg, c->q[j]);
   negate_trunc(mneg);
-  // [0x80808080 sum_k V_k - 2^e]: the digits of y_k ^ 0x80808080 stand for y_k - 0x80808080
+  // the digits of x_k ^ 0x80808080 stand for x_k - 0x80808080
   std::vector<uint32_t> eneg(Lout, 0);
   if (e < 32 * Lout) {
     eneg[e >> 5] = 1u << (e & 31);
@@ -503,14 +506,14 @@ const CrtTab* crt_table(fhe_ctx* c, int K, int e, int Lout, hipError_t* err) {
   }
   mul_small_trunc(vsum, 0x80808080u);
   add_trunc(eneg, vsum);
+  add_trunc(eneg, dsum);
   mneg.resize(Lp, 0);
   eneg.resize(Lp, 0);
   *err = upload(&t.A, A);
-  if (*err == hipSuccess) *err = upload(&t.d, d);
   if (*err == hipSuccess) *err = upload(&t.mneg, mneg);
   if (*err == hipSuccess) *err = upload(&t.eneg, eneg);
   if (*err != hipSuccess) {
-    for (void* p : {(void*)t.A, (void*)t.d, (void*)t.mneg, (void*)t.eneg})
+    for (void* p : {(void*)t.A, (void*)t.mneg, (void*)t.eneg})
       if (p) hipFree(p);
     return nullptr;
   }
@@ -655,6 +658,7 @@ LiftArgs lift_args(fhe_ctx* c, const uint32_t* limbs, uint32_t* res, long long i
   }
   a.lds_max = c->lds_max;
   a.cus = c->cus;
+  a.tw = c->tw;
   a.limbs = limbs;
   a.res = res;
   a.in_stride = in_stride;
@@ -672,7 +676,8 @@ LiftArgs lift_args(fhe_ctx* c, const uint32_t* limbs, uint32_t* res, long long i
 // primes -> X mod 2^outbits.  Poly z reads res + (z / per_group) gstride +
 // (z % per_group) pstride and writes out + z ostride.
 hipError_t run_crt(fhe_ctx* c, const uint32_t* res, int per_group, long long gstride, long long pstride,
-                   uint32_t* out, long long ostride, int N, int K, int e, int outbits, int npoly, hipStream_t st) {
+                   uint32_t* out, long long ostride, int N, int K, int e, int outbits, int npoly, const uint2* scale,
+                   hipStream_t st) {
   hipError_t err = hipSuccess;
   const int Lout = (outbits + 31) / 32;
   const CrtTab* t = crt_table(c, K, e, Lout, &err);
@@ -691,13 +696,16 @@ hipError_t run_crt(fhe_ctx* c, const uint32_t* res, int per_group, long long gst
   a.ntiles = t->ntiles;
   a.A = t->A;
   a.pc = c->pc;
-  a.d = t->d;
+  a.itw = c->itw;
+  a.scale = scale;
+  a.scale_w = scale ? scale + c->Kpad : nullptr;  // the tables hold both halves
+  a.frac0 = t->frac0;
   a.rq = c->rq;
   a.mneg = t->mneg;
   a.eneg = t->eneg;
   a.lds_max = c->lds_max;
   a.cus = c->cus;
-  return launch_crt(a, npoly, st);
+  return launch_crt_cols(a, npoly, st);
 }
 
 // Creates the lift and CRT tables one pipeline run at (key, logN, logq) uses, so that a run
@@ -761,24 +769,18 @@ int evk_prepare_locked(fhe_evk* k, int logq, hipStream_t stream) {
     hipFree(out);
     return set_sticky(c, e);
   }
-  // the fused relinearization pass reads each row in its transposed register order; the
-  // row length depends on the column/row split, which differs by tuning for odd logN
+  // the fused relinearization pass reads each row in its transposed register order
   const long long words = 2LL * Kr * N;
-  const int Sa = k->logN / 2, Sb = k->logN - k->logN / 2;
-  uint32_t* perm[2] = {nullptr, nullptr};
-  for (int v = 0; v < (Sa == Sb ? 1 : 2) && e == hipSuccess; ++v) {
-    e = hipMalloc(&perm[v], (size_t)words * 4);
-    if (e == hipSuccess) e = launch_row_transpose(out, perm[v], words, v ? Sb : Sa, stream);
-  }
+  uint32_t* perm = nullptr;
+  e = hipMalloc(&perm, (size_t)words * 4);
+  if (e == hipSuccess) e = launch_row_transpose(out, perm, words, k->logN - 4, stream);
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   hipFree(out);
   if (e != hipSuccess) {
-    for (uint32_t* q : perm)
-      if (q) hipFree(q);
+    if (perm) hipFree(perm);
     return set_sticky(c, e);
   }
-  k->ntt[logq] = perm[0];
-  if (perm[1]) k->ntt_alt[logq] = perm[1];
+  k->ntt[logq] = perm;
   return FHE_OK;
 }
 
@@ -822,17 +824,13 @@ int relin_part(fhe_ctx* c, fhe_evk* k, int logN, int logq, int bits, const PipeI
   if (z.Kt < 0 || z.Kr < 0) return FHE_E_RANGE;
   const int Kr = z.Kr, L = z.L, LK = z.LK;
   const int logP = k->logP;
-  const int rows_log = logN - ntt_split_cols(logN, tu);  // the fused pass's row length
-  const uint32_t* evk_ntt = rows_log == logN / 2 ? k->ntt.at(logq) : k->ntt_alt.at(logq);
+  const uint32_t* evk_ntt = k->ntt.at(logq);
   hipError_t e = hipSuccess;
   const int er = logN + 2 * logq + logP;  // |k_i| < 2^er
   const long long NN = N;
   const long long polyw = (long long)L * NN;
-  // 6. lift d2 onto Kr primes; 7. forward NTT
-  e = launch_lift(lift_args(c, Dl + 2 * polyw, Rr, 3 * polyw, (long long)Kr * NN, N, L, Kr), cnum, st, tu);
-  if (e == hipSuccess)
-    e = launch_ntt_cols(ntt_args(c, Rr, logN, Kr, Kr, (long long)Kr * NN, false, nullptr), cnum * Kr, false, st,
-                        tu);
+  // 6. lift d2 onto Kr primes, 7. first forward stages
+  e = launch_lift_cols(lift_args(c, Dl + 2 * polyw, Rr, 3 * polyw, (long long)Kr * NN, N, L, Kr), cnum, st, tu);
   // 8. forward row pass, products with the resident key into Rk[c][0..1][Kr][N],
   // first inverse row pass
   if (e == hipSuccess) {
@@ -842,15 +840,13 @@ int relin_part(fhe_ctx* c, fhe_evk* k, int logN, int logq, int bits, const PipeI
     ra.key = evk_ntt;
     ra.out = Rk;
     ra.out_stride = 2LL * Kr * NN;
-    e = launch_rows_fused(ra, ROWS_RELIN, st, tu);
+    e = launch_rows_fused(ra, ROWS_RELIN, st);
   }
-  // 9. inverse NTT column pass; 10. CRT -> k0, k1 mod 2^(logP + logq)
-  if (e == hipSuccess)
-    e = launch_ntt_cols(ntt_args(c, Rk, logN, Kr, 2 * Kr, 2LL * Kr * NN, true, nullptr), cnum * 2 * Kr, true, st,
-                        tu);  // the factor is in the prepared key
+  // 9. last inverse stages (the final factor is in the prepared key); 10. CRT -> k0, k1
+  // mod 2^(logP + logq)
   if (e == hipSuccess)
     e = run_crt(c, Rk, 2, 2LL * Kr * NN, (long long)Kr * NN, Kl, (long long)LK * NN, N, Kr, er, logP + logq,
-                cnum * 2, st);
+                cnum * 2, nullptr, st);
   // 11. c_i = [d_i + R(k_i)]_(2^logq), to the outputs or (rescale follows) the staging area
   const uint32_t* pwt = nullptr;
   if (e == hipSuccess && k->scheme == FHE_BGV) pwt = pow_table(c, k->t, &e);
@@ -916,25 +912,19 @@ int pipeline(fhe_ctx* c, fhe_evk* k, int logN, int logq, int bits, const PipeIO&
     la.in4[2] = io.y0;
     la.in4[3] = io.y1;
     la.in_ptrs = io.ins;
-    e = launch_lift(la, 4 * cnum, st, tu);
+    e = launch_lift_cols(la, 4 * cnum, st, tu);  // 2. with the first forward stages
   }
-  // 2. forward NTT column pass of all 4 cnum Kt transforms
-  if (e == hipSuccess)
-    e = launch_ntt_cols(ntt_args(c, Rt, logN, Kt, 4 * Kt, 4LL * Kt * NN, false, nullptr), cnum * 4 * Kt, false, st,
-                        tu);
   // 3. forward row pass, tensor products into slots 0..2, first inverse row pass
   if (e == hipSuccess) {
     RowsArgs ra = rows_args(c, logN, Kt, cnum);
     ra.data = Rt;
     ra.group_stride = 4LL * Kt * NN;
-    e = launch_rows_fused(ra, ROWS_TENSOR, st, tu);
+    e = launch_rows_fused(ra, ROWS_TENSOR, st);
   }
-  // 4. inverse NTT column pass of slots 0..2 (final factor N^-1 2^32 c_k)
+  // 4. last inverse stages of slots 0..2 (final factor N^-1 2^32 c_k); 5. CRT -> d0, d1, d2
+  // mod 2^logq: Dl[c][i][L][N]
   if (e == hipSuccess)
-    e = launch_ntt_cols(ntt_args(c, Rt, logN, Kt, 3 * Kt, 4LL * Kt * NN, true, sct), cnum * 3 * Kt, true, st, tu);
-  // 5. CRT -> d0, d1, d2 mod 2^logq: Dl[c][i][L][N]
-  if (e == hipSuccess)
-    e = run_crt(c, Rt, 3, 4LL * Kt * NN, (long long)Kt * NN, Dl, polyw, N, Kt, et, logq, cnum * 3, st);
+    e = run_crt(c, Rt, 3, 4LL * Kt * NN, (long long)Kt * NN, Dl, polyw, N, Kt, et, logq, cnum * 3, sct, st);
   if (e != hipSuccess) return set_sticky(c, e);
   return relin_part(c, k, logN, logq, bits, io, cnum, st, Dl, Rr, Rk, Kl, tu, false);
 }
@@ -1133,25 +1123,13 @@ int plan_autotune(fhe_plan* pl, PlanCell& cell, hipStream_t st) {
     cell.tune = it->second;
     return FHE_OK;
   }
-  // Candidates: the lift on the matrix cores or the VALU (16 primes per thread); for odd
-  // logN, which pass takes the extra stage; the column passes' workgroup width (64, 32
-  // or 16 columns of 2^8 points, 64 or 32 of 2^7).
+  // Candidates: the lift on the matrix cores or the VALU (16 primes per thread).
   std::vector<Tuning> cands;
-  for (int lp : {0, 16})
-    for (int cf : {1, 0}) {
-      if (cf == 0 && (cell.logN % 2 == 0)) continue;  // same split either way
-      Tuning t;
-      t.lift_primes = lp;
-      t.ntt_cols_first = cf;
-      const int s_cols = ntt_split_cols(cell.logN, t);
-      std::vector<int> widths = {0};  // the default: 64 columns per workgroup
-      if (s_cols == 8) widths = {0, 512, 256};
-      if (s_cols == 7) widths = {0, 256};
-      for (int ct : widths) {
-        t.cols_threads = ct;
-        cands.push_back(t);
-      }
-    }
+  for (int lp : {0, 16}) {
+    Tuning t;
+    t.lift_primes = lp;
+    cands.push_back(t);
+  }
   hipEvent_t e0, e1;
   if (hipEventCreate(&e0) != hipSuccess) return FHE_E_DEVICE;
   if (hipEventCreate(&e1) != hipSuccess) {
@@ -1367,9 +1345,10 @@ int ring_mul_locked(fhe_ctx* c, int logN, int logq, const uint32_t* a, const uin
   if (!R) return set_sticky(c, e);
   uint32_t* Ra = R;
   uint32_t* Rb = R + (long long)cnum * KN;
-  e = launch_lift(lift_args(c, a, Ra, (long long)L * N, KN, N, L, K), cnum, st);
-  if (e == hipSuccess) e = launch_lift(lift_args(c, b, Rb, (long long)L * N, KN, N, L, K), cnum, st);
-  if (e == hipSuccess) e = launch_ntt_cols(ntt_args(c, R, logN, K, K, KN, false, nullptr), 2 * cnum * K, false, st);
+  LiftArgs la = lift_args(c, a, R, (long long)L * N, KN, N, L, K);  // a to Ra, b to Rb
+  la.limbs1 = b;
+  la.first1 = cnum;
+  e = launch_lift_cols(la, 2 * cnum, st);
   if (e == hipSuccess) {
     RowsArgs ra = rows_args(c, logN, K, cnum);
     ra.data = Ra;
@@ -1379,8 +1358,7 @@ int ring_mul_locked(fhe_ctx* c, int logN, int logq, const uint32_t* a, const uin
     ra.data2_groups = cnum;
     e = launch_rows_fused(ra, ROWS_RING, st);
   }
-  if (e == hipSuccess) e = launch_ntt_cols(ntt_args(c, Ra, logN, K, K, KN, true, sc), cnum * K, true, st);
-  if (e == hipSuccess) e = run_crt(c, Ra, 1, KN, 0, out, (long long)L * N, N, K, eb, logq, cnum, st);
+  if (e == hipSuccess) e = run_crt(c, Ra, 1, KN, 0, out, (long long)L * N, N, K, eb, logq, cnum, sc, st);
   return set_sticky(c, e);
 }
 
@@ -1449,11 +1427,12 @@ int plain_mul_locked(fhe_ctx* c, int logN, int logq, const uint32_t* x0, const u
   uint32_t* R = (uint32_t*)stream_scratch(c, st, 0, (size_t)(2LL * cnum + mcount) * KN * 4, &e);
   if (!R) return set_sticky(c, e);
   uint32_t* Rm = R + 2LL * cnum * KN;
-  e = launch_lift(lift_args(c, x0, R, LN, KN, N, L, K), cnum, st);
-  if (e == hipSuccess) e = launch_lift(lift_args(c, x1, R + cnum * KN, LN, KN, N, L, K), cnum, st);
-  if (e == hipSuccess) e = launch_lift(lift_args(c, m, Rm, LN, KN, N, L, K), mcount, st);
-  if (e == hipSuccess)
-    e = launch_ntt_cols(ntt_args(c, R, logN, K, K, KN, false, nullptr), (2 * cnum + mcount) * K, false, st);
+  LiftArgs la = lift_args(c, x0, R, LN, KN, N, L, K);  // x0, x1, m in turn
+  la.limbs1 = x1;
+  la.first1 = cnum;
+  la.limbs2 = m;
+  la.first2 = 2 * cnum;
+  e = launch_lift_cols(la, 2 * cnum + mcount, st);
   if (e == hipSuccess) {
     RowsArgs ra = rows_args(c, logN, K, 2 * cnum);
     ra.data = R;
@@ -1463,9 +1442,8 @@ int plain_mul_locked(fhe_ctx* c, int logN, int logq, const uint32_t* x0, const u
     ra.data2_groups = mcount > 1 ? mcount : 1;
     e = launch_rows_fused(ra, ROWS_RING, st);
   }
-  if (e == hipSuccess) e = launch_ntt_cols(ntt_args(c, R, logN, K, K, KN, true, sc), 2 * cnum * K, true, st);
-  if (e == hipSuccess) e = run_crt(c, R, 1, KN, 0, out0, LN, N, K, eb, logq, cnum, st);
-  if (e == hipSuccess) e = run_crt(c, R + cnum * KN, 1, KN, 0, out1, LN, N, K, eb, logq, cnum, st);
+  if (e == hipSuccess) e = run_crt(c, R, 1, KN, 0, out0, LN, N, K, eb, logq, cnum, sc, st);
+  if (e == hipSuccess) e = run_crt(c, R + cnum * KN, 1, KN, 0, out1, LN, N, K, eb, logq, cnum, sc, st);
   return set_sticky(c, e);
 }
 
@@ -1618,7 +1596,7 @@ int fhe_ctx_create(int device, int logQ_max, int logP_max, fhe_ctx** out) {
     pc[k].two_q = 2 * q;
   }
   std::vector<uint32_t> rq(Kpad, 0);
-  for (int k = 0; k < K; ++k) rq[k] = (uint32_t)((1ull << 56) / c->q[k]);
+  for (int k = 0; k < K; ++k) rq[k] = (uint32_t)((1ull << 54) / c->q[k]);
   // lift constants 2^(28 i) 2^32 mod q_p (Montgomery form)
   c->Lmax = (std::max(logQ_max, logP_max + logQ_max) + 31) / 32;
   c->TS = 8 * ((c->Lmax + 6) / 7);
@@ -1693,7 +1671,7 @@ void fhe_ctx_destroy(fhe_ctx* c) {
     for (void* p : {(void*)kv.second.A, (void*)kv.second.off})
       if (p) hipFree(p);
   for (auto& kv : c->crt)
-    for (void* p : {(void*)kv.second.A, (void*)kv.second.d, (void*)kv.second.mneg, (void*)kv.second.eneg})
+    for (void* p : {(void*)kv.second.A, (void*)kv.second.mneg, (void*)kv.second.eneg})
       if (p) hipFree(p);
   for (auto& kv : c->pw) hipFree(kv.second);
   for (auto& kv : c->ws)
@@ -1931,7 +1909,6 @@ void fhe_evk_destroy(fhe_evk* k) {
     hipDeviceSynchronize();
   }
   for (auto& kv : k->ntt) hipFree(kv.second);
-  for (auto& kv : k->ntt_alt) hipFree(kv.second);
   delete k;
 }
 

@@ -18,6 +18,9 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 // hoisted out of the loop, where each would hold a register).
 __device__ __forceinline__ void opaque(uint32_t& v) { asm volatile("" : "+v"(v)); }
 
+// The same for a value in a scalar register.
+__device__ __forceinline__ void opaque_s(uint32_t& v) { asm volatile("" : "+s"(v)); }
+
 // A pointer the caller knows to be equal on every lane of the wave, moved to scalar
 // registers: buffer resources need it there, and stores through it take the scalar
 // base + 32-bit lane offset form (no 64-bit address arithmetic per lane).
@@ -212,6 +215,62 @@ __device__ __forceinline__ void gs_bfly_neg(uint32_t& X, uint32_t& Y, uint2 v, u
   const uint32_t d = y - x + two_q;
   const uint32_t qh = __umulhi(d, v.y);
   Y = mad_lo(qh, 0u - q, d * v.x);
+}
+
+// The limbs of input polynomial z of a lift.
+__device__ __forceinline__ const uint32_t* lift_source(const LiftArgs& a, uint32_t z) {
+  if (a.interleave4) {
+    const uint32_t i = z & 3u, c = z >> 2;
+    return a.in_ptrs ? a.in_ptrs[i * (uint32_t)(a.npoly >> 2) + c] : a.in4[i] + (long long)c * a.in_stride;
+  }
+  if (a.in_ptrs) return a.in_ptrs[z];
+  if ((int)z >= a.first2) return a.limbs2 + (long long)((int)z - a.first2) * a.in_stride;
+  if ((int)z >= a.first1) return a.limbs1 + (long long)((int)z - a.first1) * a.in_stride;
+  return a.limbs + (long long)z * a.in_stride;
+}
+
+// The four outer stages of a transform on one column {c + (N / 16) u}, u < 16: forward
+// stages of 1, 2, 4 and 8 groups (table entries 1..15), values in [0, 4q) to [0, 4q).
+__device__ __forceinline__ void cols16_forward(uint32_t (&x)[16], TwTab tw, uint32_t q, uint32_t two_q) {
+#pragma unroll
+  for (int m = 1; m <= 8; m *= 2) {
+    const int h = 8 / m;
+#pragma unroll
+    for (int g = 0; g < m; ++g) {
+      const uint2 w = tw[m + g];
+#pragma unroll
+      for (int u = 2 * h * g; u < 2 * h * g + h; ++u) ct_bfly(x[u], x[u + h], w, q, two_q);
+    }
+  }
+}
+
+// The last four inverse stages, values in [0, 2q) to canonical ones; with SCALE the last
+// stage (one group, twiddle w = entry 1) takes the final factor c: (X + Y) c and
+// (X - Y) (w c), pairs sc and sw.
+template <bool SCALE>
+__device__ __forceinline__ void cols16_inverse(uint32_t (&x)[16], TwTab itw, uint2 sc, uint2 sw, uint32_t q,
+                                               uint32_t two_q) {
+#pragma unroll
+  for (int m = 8; m >= (SCALE ? 2 : 1); m /= 2) {
+    const int h = 8 / m;
+#pragma unroll
+    for (int g = 0; g < m; ++g) {
+      const uint2 w = itw[m + g];
+#pragma unroll
+      for (int u = 2 * h * g; u < 2 * h * g + h; ++u) gs_bfly(x[u], x[u + h], w, q, two_q);
+    }
+  }
+  if (SCALE) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const uint32_t xs = x[u], ys = x[u + 8];
+      x[u] = csub(shoup_lazy(xs + ys, sc.x, sc.y, q), q);
+      x[u + 8] = csub(shoup_lazy(xs - ys + two_q, sw.x, sw.y, q), q);
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < 16; ++u) x[u] = csub(x[u], q);
+  }
 }
 
 // Every LDS exchange of the row passes stays inside one T-thread slot, and a slot

@@ -61,6 +61,10 @@ struct LiftArgs {
   // of input i, at in4[i] + c * in_stride, or in_ptrs[i * (npoly / 4) + c]
   const uint32_t* in4[4] = {nullptr, nullptr, nullptr, nullptr};
   bool interleave4 = false;
+  // further inputs: polynomials from first1 on are those of limbs1, from first2 on of limbs2
+  const uint32_t* limbs1 = nullptr;
+  const uint32_t* limbs2 = nullptr;
+  int first1 = 0x7FFFFFFF, first2 = 0x7FFFFFFF;
   uint32_t* res = nullptr;          // poly z at res + z * out_stride, uint32[K][N]
   long long in_stride = 0, out_stride = 0;
   int N = 0, L = 0, K = 0;
@@ -74,10 +78,14 @@ struct LiftArgs {
   const uint64_t* off = nullptr;
   int nkb = 0, ntiles = 0;
   int lds_max = 0, cus = 0;  // device: LDS bytes per workgroup, compute units
+  // with the first four transform stages (launch_lift_cols): forward twiddles, and the
+  // workgroups that share a block of columns (set by the launch)
+  const uint2* tw = nullptr;
+  int nsplit = 1;
 };
 
-// CRT reconstruction of `npoly` polynomials from canonical residues (the inverse
-// NTT's output with the CRT factor c_k folded in).
+// The last four inverse transform stages (with the CRT factor c_k) and the CRT
+// reconstruction of `npoly` polynomials.
 struct CrtArgs {
   const uint32_t* res = nullptr; // poly z: res + (z / per_group) * gstride + (z % per_group) * pstride, [K][N]
   int per_group = 0;
@@ -88,10 +96,13 @@ struct CrtArgs {
   int ntiles = 0;           // tiles of 8 output limbs
   const v4i_t* A = nullptr; // [tile][k-block][lane]: the 16 MFMA A bytes of each lane
   const PrimeC* pc = nullptr;
-  const uint32_t* d = nullptr;    // [k] = [2^e c_k]_(q_k)
-  const uint32_t* rq = nullptr;   // [k] = floor(2^56 / q_k)
+  const uint2* itw = nullptr;     // inverse twiddles, [prime][kNMax]
+  const uint2* scale = nullptr;   // per-prime final factor and (scale_w) the factor times the last
+  const uint2* scale_w = nullptr; // stage's twiddle; null: the inputs already carry it
+  const uint32_t* rq = nullptr;   // [k] = floor(2^54 / q_k)
+  uint64_t frac0 = 0;             // constant of the quotient (CrtTab)
   const uint32_t* mneg = nullptr; // [l < 8 ntiles] limbs of (-M) mod 2^(32 Lout), zero beyond Lout
-  const uint32_t* eneg = nullptr; // [l < 8 ntiles] limbs of (-2^e) mod 2^(32 Lout), zero beyond Lout
+  const uint32_t* eneg = nullptr; // [l < 8 ntiles] the constant row's limbs (CrtTab), zero beyond Lout
   int npoly = 0;                  // set by launch_crt
   int lds_max = 0, cus = 0;       // device: LDS bytes per workgroup, compute units
 };
@@ -234,25 +245,21 @@ struct Bracket {
   ~Bracket() { bracket_end(kid, s, work); }
 };
 
-// Launch parameters chosen by the autotuner (defaults: 16 primes per lift thread,
-// NTT column pass of ceil(logN / 2) stages).
+// Launch parameters chosen by the autotuner.
 struct Tuning {
   int lift_primes = 0;  // 0: matrix-core lift; 8, 16 or 32: VALU lift with that many primes per thread
-  int ntt_cols_first = 1;  // 1: column pass takes ceil(logN/2) stages; 0: floor
-  int cols_threads = 0;    // column-pass workgroup: 0 default (64 columns), or 256 / 512 threads
 };
 
-hipError_t launch_ntt(const NttArgs& a, int ntransforms, bool inverse, hipStream_t s,
-                      const Tuning& t = Tuning());
+hipError_t launch_ntt(const NttArgs& a, int ntransforms, bool inverse, hipStream_t s);
 // The same with one workgroup per transform (one pass over memory); natural: the
 // transformed side in natural instead of bit-reversed order.  The inverse needs a.scale.
 hipError_t launch_ntt_whole(const NttArgs& a, int ntransforms, bool inverse, bool natural, hipStream_t s);
 bool ntt_whole_wanted(int logN, bool natural, long long ntransforms);
-hipError_t launch_ntt_cols(const NttArgs& a, int ntransforms, bool inverse, hipStream_t s,
-                           const Tuning& t = Tuning());
-hipError_t launch_rows_fused(const RowsArgs& a, int mode, hipStream_t s, const Tuning& t = Tuning());
-// log2 of the column pass's length for a transform of 2^logN points
-int ntt_split_cols(int logN, const Tuning& t);
+// Ring products split their transforms as 16 x N / 16: the four outer stages (launch_cols16,
+// or inside the lift and the reconstruction) and the fused pass over rows of N / 16 points.
+hipError_t launch_cols16(const NttArgs& a, int ntransforms, bool inverse, hipStream_t s);
+hipError_t launch_rows_fused(const RowsArgs& a, int mode, hipStream_t s);
+hipError_t launch_rows_mid(const RowsArgs& a, int mode, hipStream_t s);  // rows above 256 points
 // Transposes rows of 2^S words into the register order of the fused relinearization pass.
 hipError_t launch_row_transpose(const uint32_t* src, uint32_t* dst, long long total, int S, hipStream_t s);
 // data[r][j] <- data[r][j] scale[r mod K] mod q_(r mod K) for `rows` rows of N words
@@ -260,7 +267,9 @@ hipError_t launch_row_transpose(const uint32_t* src, uint32_t* dst, long long to
 hipError_t launch_scale_rows(uint32_t* data, long long rows, int K, int N, const uint2* scale, const PrimeC* pc,
                              hipStream_t s);
 hipError_t launch_lift(const LiftArgs& a, int npoly, hipStream_t s, const Tuning& t = Tuning());
-hipError_t launch_crt(CrtArgs a, int npoly, hipStream_t s);
+// the lift and the four outer forward stages (residues in [0, 4q)); out_stride a multiple of K N
+hipError_t launch_lift_cols(const LiftArgs& a, int npoly, hipStream_t s, const Tuning& t = Tuning());
+hipError_t launch_crt_cols(CrtArgs a, int npoly, hipStream_t s);
 hipError_t launch_compose(const ComposeArgs& a, int cnum, hipStream_t s);
 hipError_t launch_rescale(const RescaleArgs& a, int cnum, hipStream_t s);
 hipError_t launch_compose_rescale(const ComposeArgs& a, int cnum, hipStream_t s);

@@ -1,7 +1,6 @@
 // gfx950 kernels for the non-RNS HE-mult pipeline:
 //   lift (limbs -> residues), negacyclic NTT / iNTT, pointwise products,
-//   CRT reconstruction (residues -> limbs, on the i8 matrix cores), relinearization
-//   compose, rescale.
+//   relinearization compose, rescale.
 #include <algorithm>
 
 #include "device_common.h"
@@ -700,7 +699,6 @@ static hipError_t rows_fused_s(int S, const RowsArgs& a, hipStream_t st) {
       rows_span_bytes(a, 4) < 0x70000000LL)
     return rows_fused<8, MODE == 2 ? 0 : MODE, 4>(a, st);
   switch (S) {
-    case 5: return rows_fused<5, MODE, 1>(a, st);
     case 6: return rows_fused<6, MODE, 1>(a, st);
     case 7: return rows_fused<7, MODE, 1>(a, st);
     case 8: return rows_fused<8, MODE, 1>(a, st);
@@ -727,10 +725,8 @@ static hipError_t ntt_pass(const NttArgs& a, int ntr, hipStream_t st) {
   return hipGetLastError();
 }
 
-// cols_threads: 0 for the default workgroup of a column pass, else 256 or 512 threads
-// (16 or 32 columns of 2^8 points, 32 of 2^7) where it is smaller than the default.
 template <bool INV, bool ROWS>
-static hipError_t ntt_pass_s(int S, const NttArgs& a, int ntr, hipStream_t st, int cols_threads = 0) {
+static hipError_t ntt_pass_s(int S, const NttArgs& a, int ntr, hipStream_t st) {
   // row passes of 256 points over blocks of four transforms one group apart (one
   // polynomial per group), where at most one slot in eight idles and the block's span
   // stays below the buffer's out-of-range offset
@@ -738,9 +734,6 @@ static hipError_t ntt_pass_s(int S, const NttArgs& a, int ntr, hipStream_t st, i
   if (ROWS && S == 8 && a.per_group == a.K && npp >= 4 && 8 * (4 * ncg4 - npp) <= 4 * ncg4 &&
       (3 * a.group_stride + (1LL << a.logN)) * 4 < 0x70000000LL)
     return ntt_pass<8, INV, true, 256, 4>(a, ntr, st);
-  if (!ROWS && S == 8 && cols_threads == 256) return ntt_pass<8, INV, false, 256>(a, ntr, st);
-  if (!ROWS && S == 8 && cols_threads == 512) return ntt_pass<8, INV, false, 512>(a, ntr, st);
-  if (!ROWS && S == 7 && cols_threads == 256) return ntt_pass<7, INV, false, 256>(a, ntr, st);
   switch (S) {
     case 5: return ntt_pass<5, INV, ROWS>(a, ntr, st);
     case 6: return ntt_pass<6, INV, ROWS>(a, ntr, st);
@@ -787,21 +780,10 @@ hipError_t launch_scale_rows(uint32_t* data, long long rows, int K, int N, const
   return hipGetLastError();
 }
 
-int ntt_split_cols(int logN, const Tuning& tu) { return tu.ntt_cols_first ? logN - logN / 2 : logN / 2; }
-
-hipError_t launch_ntt_cols(const NttArgs& a0, int ntr, bool inverse, hipStream_t st, const Tuning& tu) {
-  if (ntr <= 0) return hipSuccess;
-  if (ntr % a0.K != 0 || a0.per_group % a0.K != 0) return hipErrorInvalidValue;
-  NttArgs a = a0;
-  a.ntr = ntr;
-  const int s_cols = ntt_split_cols(a.logN, tu);
-  return inverse ? ntt_pass_s<true, false>(s_cols, a, ntr, st, tu.cols_threads)
-                 : ntt_pass_s<false, false>(s_cols, a, ntr, st, tu.cols_threads);
-}
-
-hipError_t launch_rows_fused(const RowsArgs& a, int mode, hipStream_t st, const Tuning& tu) {
+hipError_t launch_rows_fused(const RowsArgs& a, int mode, hipStream_t st) {
   if (a.cnum <= 0) return hipSuccess;
-  const int s_rows = a.logN - ntt_split_cols(a.logN, tu);
+  const int s_rows = a.logN - 4;  // the outer four stages run in the lift and the reconstruction
+  if (s_rows > 8) return launch_rows_mid(a, mode, st);
   switch (mode) {
     case ROWS_TENSOR: return rows_fused_s<0>(s_rows, a, st);
     case ROWS_RELIN: return rows_fused_s<1>(s_rows, a, st);
@@ -810,13 +792,13 @@ hipError_t launch_rows_fused(const RowsArgs& a, int mode, hipStream_t st, const 
   }
 }
 
-hipError_t launch_ntt(const NttArgs& a0, int ntr, bool inverse, hipStream_t st, const Tuning& tu) {
+hipError_t launch_ntt(const NttArgs& a0, int ntr, bool inverse, hipStream_t st) {
   if (ntr <= 0) return hipSuccess;
   if (ntr % a0.K != 0 || a0.per_group % a0.K != 0) return hipErrorInvalidValue;
   NttArgs a = a0;
   a.ntr = ntr;
   // the split groups the same stages differently and does not change the result
-  const int s_cols = ntt_split_cols(a.logN, tu);
+  const int s_cols = a.logN - a.logN / 2;
   const int s_rows = a.logN - s_cols;
   hipError_t e;
   if (!inverse) {
@@ -834,15 +816,6 @@ hipError_t launch_ntt(const NttArgs& a0, int ntr, bool inverse, hipStream_t st, 
 // digits (8 digits per 7 limbs), so every digit-constant product is below 2^58 and
 // 40 of them fit a 64-bit accumulator between folds.  The constants are
 // 2^(28 i) 2^32 mod q, and the final Montgomery reduction removes the 2^32.
-
-// The limbs of input polynomial z of a lift.
-__device__ __forceinline__ const uint32_t* lift_source(const LiftArgs& a, uint32_t z) {
-  if (a.interleave4) {
-    const uint32_t i = z & 3u, c = z >> 2;
-    return a.in_ptrs ? a.in_ptrs[i * (uint32_t)(a.npoly >> 2) + c] : a.in4[i] + (long long)c * a.in_stride;
-  }
-  return a.in_ptrs ? a.in_ptrs[z] : a.limbs + (long long)z * a.in_stride;
-}
 
 template <int PB>
 __device__ __forceinline__ void lift_kernel_body(const LiftArgs& a, const Blk bk) {
@@ -1083,296 +1056,6 @@ hipError_t launch_lift(const LiftArgs& a, int npoly, hipStream_t st, const Tunin
     case 8: lift_launch<8>(b, npoly, st); break;
     case 32: lift_launch<32>(b, npoly, st); break;
     default: lift_launch<16>(b, npoly, st); break;
-  }
-  return hipGetLastError();
-}
-
-// ============================================================================ CRT reconstruction
-// Residues -> limbs (the reconstruction step of Section 5.1 / Eq. garner_mrc, here
-// in its direct CRT form).  With M = q_0 ... q_(K-1), c_k = [(M/q_k)^-1]_(q_k) and
-// the inverse NTT's final factor including c_k, a transform output x_k
-// gives y_k = [x_k + d_k]_(q_k), d_k = [2^e c_k]_(q_k), the CRT coordinates of
-// Y = X + 2^e in [0, 2^(e+1)) (X the signed exact product, |X| < 2^e).  Then
-//   Y = sum_k y_k (M/q_k) - alpha M,   alpha = floor(sum_k y_k / q_k),
-// and the output is X mod 2^outbits = (Y - 2^e) mod 2^outbits.  The prime count
-// leaves Y / M < 2^-16, so alpha is exact from the sum in fixed point
-// sum_k y_k floor(2^56 / q_k) (each term < 2^56, truncation error < K 2^-26 <
-// 2^-18 in units of 2^56): alpha = (sum + 2^38) >> 56.
-//
-// The column sums sum_k y_k V_kl, V_kl = limb l of (M/q_k) mod 2^(32 Lout), are a
-// dense integer contraction [coefficients x K] x [K x Lout] and run on the i8
-// matrix cores: y_k - 0x80808080 and V_kl are split into 4 balanced base-256 digits
-// each (digits in [-128, 127]; the digits of y_k - 0x80808080 are the bytes of
-// y_k ^ 0x80808080, and limbs of V are taken in [-0x80808080, 0x7F7F7F7F]), the 16
-// digit-plane products accumulate exactly in int32 (|sum| <= K 2^14), and the VALU
-// recombines sum_(a,b) 2^(8(a+b)) C_ab per limb (the 7 diagonal sums in int32, then
-// 64-bit multiply-adds), adds alpha [-M] + [0x80808080 sum_k V_k - 2^e] (both
-// constants as limbs mod 2^(32 Lout)), and propagates the carries.
-//
-// One wave per 32 coefficients.  MFMA v_mfma_i32_32x32x32_i8: lane (c, h) = (lane
-// mod 32, lane / 32) supplies B bytes k = 32 kb + 16 h + i (i < 16) of coefficient
-// column c, and A bytes of row c for the same k; its accumulator holds rows
-// 8 j + 4 h + i.  Rows of a tile are (digit plane b of V, limb 8 t + l'), row =
-// 8 b + l', so lane half h ends with all four planes of limbs 8 t + 4 h + i.
-
-
-// 4 x 32-bit words -> their byte plane a (a < 4) as 4 packed bytes, for all planes.
-__device__ __forceinline__ void byte_planes(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, uint32_t& p0,
-                                            uint32_t& p1, uint32_t& p2, uint32_t& p3) {
-  // v_perm_b32: result byte i = byte sel_i of {src0 (bytes 4..7), src1 (bytes 0..3)}
-  const uint32_t lo01 = __builtin_amdgcn_perm(w1, w0, 0x05010400u);  // w0.0 w1.0 w0.1 w1.1
-  const uint32_t hi01 = __builtin_amdgcn_perm(w1, w0, 0x07030602u);  // w0.2 w1.2 w0.3 w1.3
-  const uint32_t lo23 = __builtin_amdgcn_perm(w3, w2, 0x05010400u);
-  const uint32_t hi23 = __builtin_amdgcn_perm(w3, w2, 0x07030602u);
-  p0 = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u);  // w0.0 w1.0 w2.0 w3.0
-  p1 = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u);
-  p2 = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u);
-  p3 = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
-}
-
-// Waves per workgroup: one persistent workgroup per CU holds the LDS table; 12 waves
-// (3 per SIMD) where the registers allow it, else 8.
-template <int NKB>
-constexpr int crt_waves() { return NKB <= 4 ? 12 : 8; }
-
-template <int NKB, bool LDSA>
-__device__ __forceinline__ void crt_kernel_body(const CrtArgs& a, const Blk bk) {
-  constexpr int kCrtWaves = crt_waves<NKB>();
-  extern __shared__ v4i sA[];
-  __shared__ uint32_t s_q[32 * NKB], s_d[32 * NKB], s_r[32 * NKB];
-  __shared__ uint32_t s_mneg[kCrtMaxLimbs], s_eneg[kCrtMaxLimbs];
-  for (int k = threadIdx.x; k < 32 * NKB; k += 64 * kCrtWaves) {
-    const bool in = k < a.K;
-    s_q[k] = in ? a.pc[k].q : 1u;
-    s_d[k] = in ? a.d[k] : 0u;
-    s_r[k] = in ? a.rq[k] : 0u;  // rows past K add nothing to the quotient
-  }
-  for (int l = threadIdx.x; l < 8 * a.ntiles; l += 64 * kCrtWaves) {
-    s_mneg[l] = a.mneg[l];
-    s_eneg[l] = a.eneg[l];
-  }
-  if (LDSA)
-    for (int f = threadIdx.x; f < a.ntiles * NKB * 64; f += 64 * kCrtWaves) sA[f] = a.A[f];
-  __syncthreads();
-  const v4i* At = LDSA ? sA : a.A;
-  const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
-  const int lg = __builtin_ctz((unsigned)a.N) - 5;  // log2 of the 32-coefficient groups per poly
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t total = (uint32_t)a.npoly << lg;
-  // the waves sharing a SIMD start apart, so that one's loads overlap another's products
-  if (wave >= 4) __builtin_amdgcn_s_sleep(63);
-  if (wave >= 8) __builtin_amdgcn_s_sleep(63);
-  for (uint32_t unit = bk.x * kCrtWaves + wave; unit < total; unit += bk.nx * kCrtWaves) {
-  const uint32_t z = unit >> lg, j0 = (unit & ((1u << lg) - 1u)) << 5;
-  const uint32_t row = 4u * (uint32_t)a.N;  // bytes between residue (or limb) rows
-  const uint32_t* xb = wave_uniform(a.res + (long long)(z / a.per_group) * a.gstride +
-                                    (long long)(z % a.per_group) * a.pstride + j0);
-  // residue rows 32 kb + 16 h + i; rows at or beyond K read as zero
-  const __amdgpu_buffer_rsrc_t rs = row_buffer(xb, 4u * ((uint32_t)a.K * (uint32_t)a.N - j0));
-  // recomputed per unit (opaque): hoisted out of the unit loop, the 80-odd row offsets
-  // derived from it would each hold a register for the whole kernel
-  uint32_t in_off = 16u * h * row + 4u * c;
-  opaque(in_off);
-
-  // phase 1: y_k, the partial sum of y_k / q_k, and the four digit planes per k-block.
-  // The digits are the bytes of y_k ^ 0x80808080, i.e. of y_k - 0x80808080 in balanced
-  // base 256; the table's constant adds back 0x80808080 sum_k V_k.  The next block's
-  // loads are in flight while a block is converted.
-  v4i B[NKB][4];
-  uint64_t frac = 0;  // sum_k y_k floor(2^56 / q_k)
-  uint32_t xv[16], xn[16];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) xv[i] = buffer_word(rs, in_off + i * row);
-#pragma unroll
-  for (int kb = 0; kb < NKB; ++kb) {
-    if (kb + 1 < NKB) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) xn[i] = buffer_word(rs, in_off + (32 * (kb + 1) + i) * row);
-    }
-    uint32_t s[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int k = 32 * kb + 16 * h + i;
-      uint32_t y = xv[i] + s_d[k];
-      y = min(y, y - s_q[k]);
-      frac += (uint64_t)y * s_r[k];
-      s[i] = y ^ 0x80808080u;
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      uint32_t p0, p1, p2, p3;
-      byte_planes(s[4 * r], s[4 * r + 1], s[4 * r + 2], s[4 * r + 3], p0, p1, p2, p3);
-      // materialised here: left to the compiler, the planes may be recomputed later
-      opaque(p0);
-      opaque(p1);
-      opaque(p2);
-      opaque(p3);
-      B[kb][0][r] = (int)p0;
-      B[kb][1][r] = (int)p1;
-      B[kb][2][r] = (int)p2;
-      B[kb][3][r] = (int)p3;
-    }
-    if (kb + 1 < NKB) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) xv[i] = xn[i];
-    }
-  }
-  frac = sum_lane_halves(frac);
-  const uint32_t alpha = (uint32_t)((frac + (1ull << 38)) >> 56);
-  // opaque multipliers of mad_i64 (the unit multipliers distinct per term of a sum)
-  uint32_t one0 = 1, one1 = 1, one2 = 1, one3 = 1, m8 = 256, m16 = 65536, m24 = 16777216;
-  opaque(one0);
-  opaque(one1);
-  opaque(one2);
-  opaque(one3);
-  opaque(m8);
-  opaque(m16);
-  opaque(m24);
-
-  // phase 2, per tile of 8 limbs: the digit-plane products, recombination, carries.
-  // Lane half h holds limbs l = 8 t + 4 h + i (i < 4) with C_ab = acc_a[4 b + i] (y plane
-  // a, V plane b) and diagonal sums S_p = sum_(a+b=p) C_ab.  S_4..S_6 weigh 2^0..2^16 in
-  // limb l + 1: inside the lane they join the next limb's sums, from the top limb they
-  // leave with the carry.
-  uint32_t* o = wave_uniform(a.out + (long long)z * a.ostride + j0);
-  uint32_t out_off = 4u * h * row + 4u * c;
-  opaque(out_off);
-  const int topbits = a.outbits - 32 * (a.Lout - 1);
-  int64_t cin = 0;  // carry into the tile (used in lane half 0)
-  v16i acc0, acc1, acc2, acc3;
-  auto products = [&](int t) {
-    const v4i* Ap = At + ((long long)t * NKB) * 64 + lane;
-    v4i Af[NKB];
-#pragma unroll
-    for (int kb = 0; kb < NKB; ++kb) Af[kb] = Ap[kb * 64];
-    acc0 = v16i{};
-    acc1 = v16i{};
-    acc2 = v16i{};
-    acc3 = v16i{};
-#pragma unroll
-    for (int kb = 0; kb < NKB; ++kb) {
-      acc0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(Af[kb], B[kb][0], acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(Af[kb], B[kb][1], acc1, 0, 0, 0);
-      acc2 = __builtin_amdgcn_mfma_i32_32x32x32_i8(Af[kb], B[kb][2], acc2, 0, 0, 0);
-      acc3 = __builtin_amdgcn_mfma_i32_32x32x32_i8(Af[kb], B[kb][3], acc3, 0, 0, 0);
-    }
-  };
-  // tile sums: tt[i][p] = T_p of limb i (S_p plus S_(p+4) of limb i - 1), s4..s6 of limb 3
-  int32_t tt[4][4], s4, s5, s6;
-  auto sums = [&]() {
-    s4 = s5 = s6 = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      tt[i][0] = acc0[i] + s4;
-      tt[i][1] = acc0[4 + i] + acc1[i] + s5;
-      tt[i][2] = acc0[8 + i] + acc1[4 + i] + acc2[i] + s6;
-      tt[i][3] = acc0[12 + i] + acc1[8 + i] + acc2[4 + i] + acc3[i];
-      s4 = acc1[12 + i] + acc2[8 + i] + acc3[4 + i];
-      s5 = acc2[12 + i] + acc3[8 + i];
-      s6 = acc3[12 + i];
-    }
-  };
-  auto finish = [&](int t, bool last) {
-    uint32_t ol[4];
-    int64_t u = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int limb = 8 * t + 4 * h + i;
-      // |T_p| <= 4 K 2^14 < 2^25: the limb value fits 64 bits with the constant and carry
-      int64_t v = (int64_t)((uint64_t)alpha * s_mneg[limb] + s_eneg[limb]);
-      v = mad_i64(tt[i][0], one0, v);
-      v = mad_i64(tt[i][1], m8, v);
-      v = mad_i64(tt[i][2], m16, v);
-      v = mad_i64(tt[i][3], m24, v);
-      if (i > 0) v = mad_i64((int32_t)(u >> 32), one1, v);
-      u = v;
-      ol[i] = (uint32_t)v;
-    }
-    int64_t carry = mad_i64(s4, one0, 0);
-    carry = mad_i64(s5, m8, carry);
-    carry = mad_i64(s6, m16, carry);
-    carry = mad_i64((int32_t)(u >> 32), one1, carry);
-    // carry across the lane halves: half 0 takes the carry into the tile, passes its
-    // carry out to half 1, whose carry out enters the next tile
-    carry = mad_i64(add_carry4(ol, h == 0 ? cin : 0), one2, carry);
-    const int64_t mid = from_lane_below(carry);
-    carry = mad_i64(add_carry4(ol, h == 1 ? mid : 0), one3, carry);
-    cin = from_lane_above(carry);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int limb = 8 * t + 4 * h + i;
-      uint32_t w = ol[i];
-      if (last) {
-        if (limb >= a.Lout) continue;
-        if (limb == a.Lout - 1 && topbits < 32) w &= (1u << topbits) - 1u;
-      }
-      store_at(o, out_off + i * row, w);
-    }
-  };
-  for (int t = 0; t < a.ntiles - 1; ++t) {
-    products(t);
-    sums();
-    finish(t, false);
-    o += 8 * a.N;
-  }
-  products(a.ntiles - 1);
-  sums();
-  finish(a.ntiles - 1, true);
-  }
-}
-
-template <int NKB, bool LDSA>
-__global__ __launch_bounds__(64 * crt_waves<NKB>()) void crt_kernel(CrtArgs a) {
-  crt_kernel_body<NKB, LDSA>(a, own_blk());
-}
-
-// The same over the cells of a stage-batched plan: one launch, each workgroup in its
-// cell's segment (cell_of) with that cell's arguments.
-template <int NKB, bool LDSA>
-__global__ __launch_bounds__(64 * crt_waves<NKB>()) void crt_kernel_multi(
-    const CrtArgs* __restrict__ cells, const CellSeg* __restrict__ seg, int ncells) {
-  Blk bk;
-  const int c = cell_of(seg, ncells, bk);
-  if (c < 0) return;
-  crt_kernel_body<NKB, LDSA>(cells[c], bk);
-}
-
-template <int NKB>
-static void crt_launch(const CrtArgs& a, hipStream_t st) {
-  constexpr int kCrtWaves = crt_waves<NKB>();
-  const long long units = (long long)a.npoly * (a.N >> 5);
-  const size_t lds = (size_t)a.ntiles * NKB * 64 * sizeof(v4i);
-  const unsigned grid = persistent_grid(units, kCrtWaves, 1, a.cus);
-  const size_t lds_static = 32 * NKB * 12 + 2 * kCrtMaxLimbs * 4;
-  if (lds + lds_static <= (size_t)a.lds_max) {
-    static bool attr = false;  // allow the full LDS of the device for this instantiation (once)
-    if (!attr)
-      attr = hipFuncSetAttribute((const void*)crt_kernel<NKB, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 a.lds_max - (int)lds_static) == hipSuccess;
-    (void)emit((const void*)crt_kernel<NKB, true>, (const void*)crt_kernel_multi<NKB, true>, dim3(grid),
-               dim3(64 * kCrtWaves), lds, st, a);
-  } else {
-    (void)emit((const void*)crt_kernel<NKB, false>, (const void*)crt_kernel_multi<NKB, false>, dim3(grid),
-               dim3(64 * kCrtWaves), 0, st, a);
-  }
-}
-
-hipError_t launch_crt(CrtArgs a, int npoly, hipStream_t st) {
-  a.npoly = npoly;
-  if (npoly == 0) return hipSuccess;
-  const int nkb = (a.K + 31) / 32;
-  // algorithmic HBM bytes: K residues read and Lout limbs written per coefficient
-  Bracket br(KID_CRT, st, 4.0 * npoly * a.N * (double)(a.K + a.Lout));
-  switch (nkb) {
-    case 1: crt_launch<1>(a, st); break;
-    case 2: crt_launch<2>(a, st); break;
-    case 3: crt_launch<3>(a, st); break;
-    case 4: crt_launch<4>(a, st); break;
-    case 5: crt_launch<5>(a, st); break;
-    case 6: crt_launch<6>(a, st); break;
-    case 7: crt_launch<7>(a, st); break;
-    case 8: crt_launch<8>(a, st); break;
-    default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
