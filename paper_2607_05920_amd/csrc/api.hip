@@ -102,15 +102,8 @@ bool is_prime32(uint32_t n) {
   return true;
 }
 
-uint32_t bitrev(uint32_t x, int bits) {
-  uint32_t r = 0;
-  for (int i = 0; i < bits; ++i) r |= ((x >> i) & 1u) << (bits - 1 - i);
-  return r;
-}
-
-uint2 shoup_pair(uint32_t w, uint32_t q) {
-  return make_uint2(w, (uint32_t)(((uint64_t)w << 32) / q));
-}
+// w 2^32 mod q, the form in which the kernels take their constants.
+uint32_t to_mont(uint64_t w, uint32_t q) { return (uint32_t)((w << 32) % q); }
 
 // Unsigned big integer as little-endian 32-bit words.
 struct Big {
@@ -260,15 +253,15 @@ struct fhe_ctx {
   std::vector<int> mbits;  // mbits[k] = bit length of M_k = prod_(i<k) q_i, k <= K
   // device tables
   PrimeC* pc = nullptr;
-  uint2* tw = nullptr;
-  uint2* itw = nullptr;
-  uint2* nscale[kLogNMax + 1] = {};  // N^-1 per prime
+  uint32_t* tw = nullptr;
+  uint32_t* itw = nullptr;
+  uint32_t* nscale[kLogNMax + 1] = {};  // N^-1 per prime
   uint32_t* liftT = nullptr;
   int TS = 0, Lmax = 0;
   uint32_t* rq = nullptr;  // [k] = floor(2^54 / q_k)
   std::map<int, std::vector<uint32_t>> crt_c;             // per K: c_k = [(M/q_k)^-1]_(q_k)
   std::map<std::tuple<int, int, int>, CrtTab> crt;        // per (K, e, Lout)
-  std::map<std::pair<int, int>, uint2*> cscale;           // per (logN, K): [N^-1 2^32 c_k]_(q_k), Shoup
+  std::map<std::pair<int, int>, uint32_t*> cscale;  // per (logN, K): [N^-1 2^32 c_k]_(q_k) (crt_scale)
   std::map<std::pair<int, int>, LiftTab> lifts;           // per (L, K)
   std::map<uint32_t, uint32_t*> pw;  // per BGV t: 2^(32 l) mod t
   std::map<std::pair<void*, int>, Workspace> ws;  // (stream, slot)
@@ -379,22 +372,22 @@ uint64_t last_inv_twiddle(const fhe_ctx* c, int k) {
   return powmod(invmod(c->psi[k], c->q[k]), 1ull << (kLogNMax - 1), c->q[k]);
 }
 
-// Final inverse-NTT factors [N^-1 2^32 c_k]_(q_k) (Shoup pairs) for transforms whose
+// Final inverse-NTT factors [N^-1 2^32 c_k]_(q_k) (in Montgomery form) for transforms whose
 // output goes to a K-prime CRT reconstruction: 2^32 undoes the 2^-32 of the
 // Montgomery pointwise products, c_k is the CRT factor.  Entries Kpad + k hold the
 // factor times the last stage's twiddle (NttArgs::scale_w).
-const uint2* crt_scale(fhe_ctx* c, int logN, int K, hipError_t* err) {
+const uint32_t* crt_scale(fhe_ctx* c, int logN, int K, hipError_t* err) {
   auto it = c->cscale.find(std::make_pair(logN, K));
   if (it != c->cscale.end()) return it->second;
   const std::vector<uint32_t>& ck = crt_c(c, K);
-  std::vector<uint2> h(2 * (size_t)c->Kpad, make_uint2(0, 0));
+  std::vector<uint32_t> h(2 * (size_t)c->Kpad, 0);
   for (int k = 0; k < K; ++k) {
     const uint32_t q = c->q[k];
     const uint64_t f = mulmod64(mulmod64(invmod(1ull << logN, q), (1ull << 32) % q, q), ck[k], q);
-    h[k] = shoup_pair((uint32_t)f, q);
-    h[c->Kpad + k] = shoup_pair((uint32_t)mulmod64(f, last_inv_twiddle(c, k), q), q);
+    h[k] = to_mont(f, q);
+    h[c->Kpad + k] = to_mont(mulmod64(f, last_inv_twiddle(c, k), q), q);
   }
-  uint2* d = nullptr;
+  uint32_t* d = nullptr;
   *err = upload(&d, h);
   if (*err != hipSuccess) return nullptr;
   c->cscale[std::make_pair(logN, K)] = d;
@@ -558,7 +551,7 @@ void* stream_scratch(fhe_ctx* c, void* stream, int slot, size_t bytes, hipError_
 int check_logN(int logN) { return (logN >= FHE_LOGN_MIN && logN <= FHE_LOGN_MAX) ? FHE_OK : FHE_E_RANGE; }
 
 NttArgs ntt_args(fhe_ctx* c, uint32_t* data, int logN, int K, int per_group, long long gstride,
-                 bool inverse, const uint2* scale) {
+                 bool inverse, const uint32_t* scale) {
   NttArgs a{};
   a.data = data;
   a.logN = logN;
@@ -676,7 +669,7 @@ LiftArgs lift_args(fhe_ctx* c, const uint32_t* limbs, uint32_t* res, long long i
 // primes -> X mod 2^outbits.  Poly z reads res + (z / per_group) gstride +
 // (z % per_group) pstride and writes out + z ostride.
 hipError_t run_crt(fhe_ctx* c, const uint32_t* res, int per_group, long long gstride, long long pstride,
-                   uint32_t* out, long long ostride, int N, int K, int e, int outbits, int npoly, const uint2* scale,
+                   uint32_t* out, long long ostride, int N, int K, int e, int outbits, int npoly, const uint32_t* scale,
                    hipStream_t st) {
   hipError_t err = hipSuccess;
   const int Lout = (outbits + 31) / 32;
@@ -761,7 +754,7 @@ int evk_prepare_locked(fhe_evk* k, int logq, hipStream_t stream) {
     e = launch_ntt(ntt_args(c, out, k->logN, Kr, 2 * Kr, 0, false, nullptr), 2 * Kr, false, stream);
   // the relinearization's inverse transforms take their final factor (N^-1 2^32 c_k,
   // see crt_scale) from the key: multiplied in here once
-  const uint2* scr = e == hipSuccess ? crt_scale(c, k->logN, Kr, &e) : nullptr;
+  const uint32_t* scr = e == hipSuccess ? crt_scale(c, k->logN, Kr, &e) : nullptr;
   if (e == hipSuccess) e = launch_scale_rows(out, 2LL * Kr, Kr, N, scr, c->pc, stream);
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   hipFree(limbs);
@@ -894,7 +887,7 @@ int pipeline(fhe_ctx* c, fhe_evk* k, int logN, int logq, int bits, const PipeIO&
   const int Kt = z.Kt, Kr = z.Kr, L = z.L;
   hipError_t e = hipSuccess;
   const int et = 2 * logq + logN + 1;  // |d_i| < 2^et
-  const uint2* sct = crt_scale(c, logN, Kt, &e);
+  const uint32_t* sct = crt_scale(c, logN, Kt, &e);
   if (!sct) return set_sticky(c, e);
   const long long NN = N;
   uint32_t* Rt = ws;                                    // [cnum][4][Kt][N]
@@ -1338,7 +1331,7 @@ int ring_mul_locked(fhe_ctx* c, int logN, int logq, const uint32_t* a, const uin
   const int K = primes_for_e(c, eb);
   if (K < 0) return FHE_E_RANGE;
   hipError_t e = hipSuccess;
-  const uint2* sc = crt_scale(c, logN, K, &e);
+  const uint32_t* sc = crt_scale(c, logN, K, &e);
   if (!sc) return set_sticky(c, e);
   const long long KN = (long long)K * N;
   if (!R) R = (uint32_t*)stream_scratch(c, stream, 0, (size_t)2 * cnum * KN * 4, &e);
@@ -1421,7 +1414,7 @@ int plain_mul_locked(fhe_ctx* c, int logN, int logq, const uint32_t* x0, const u
   const int K = primes_for_e(c, eb);
   if (K < 0) return FHE_E_RANGE;
   hipError_t e = hipSuccess;
-  const uint2* sc = crt_scale(c, logN, K, &e);
+  const uint32_t* sc = crt_scale(c, logN, K, &e);
   if (!sc) return set_sticky(c, e);
   const long long KN = (long long)K * N, LN = (long long)L * N;
   uint32_t* R = (uint32_t*)stream_scratch(c, st, 0, (size_t)(2LL * cnum + mcount) * KN * 4, &e);
@@ -1610,37 +1603,34 @@ int fhe_ctx_create(int device, int logQ_max, int logP_max, fhe_ctx** out) {
       v = mulmod64(v, step, q);
     }
   }
-  // twiddles psi^bitrev(k) and psi^-bitrev(k), k < 2^16
-  std::vector<uint2> tw((size_t)K * kNMax), itw((size_t)K * kNMax);
-  {
-    std::vector<uint32_t> pw(kNMax), ipw(kNMax);
-    for (int p = 0; p < K; ++p) {
+  // twiddles psi^bitrev(k) and psi^-bitrev(k), k < 2^16, times 2^32 (Montgomery form).  For
+  // j < m = 2^b, bitrev(m + j) = bitrev(j) + 2^(15 - b): the entries from m on are the first
+  // m times one power, here by Shoup's product (x w - floor(x floor(w 2^32 / q) / 2^32) q).
+  std::vector<uint32_t> tw((size_t)K * kNMax), itw((size_t)K * kNMax);
+  for (int p = 0; p < K; ++p)
+    for (int inv = 0; inv < 2; ++inv) {
       const uint32_t q = c->q[p];
-      const uint64_t ps = c->psi[p], ips = invmod(ps, q);
-      uint64_t a = 1, b = 1;
-      for (int i = 0; i < kNMax; ++i) {
-        pw[i] = (uint32_t)a;
-        ipw[i] = (uint32_t)b;
-        a = mulmod64(a, ps, q);
-        b = mulmod64(b, ips, q);
-      }
-      for (int i = 0; i < kNMax; ++i) {
-        const uint32_t br = bitrev((uint32_t)i, kLogNMax);
-        tw[(size_t)p * kNMax + i] = shoup_pair(pw[br], q);
-        tw[(size_t)p * kNMax + i].x = 0u - tw[(size_t)p * kNMax + i].x;  // forward butterflies take -w
-        itw[(size_t)p * kNMax + i] = shoup_pair(ipw[br], q);
+      const uint64_t ps = inv ? invmod(c->psi[p], q) : c->psi[p];
+      uint32_t* const t = &(inv ? itw : tw)[(size_t)p * kNMax];
+      t[0] = (uint32_t)((1ull << 32) % q);
+      for (int b = 0; b < kLogNMax; ++b) {
+        const uint32_t m = 1u << b, w = (uint32_t)powmod(ps, 1ull << (kLogNMax - 1 - b), q);
+        const uint32_t ws = (uint32_t)(((uint64_t)w << 32) / q);
+        for (uint32_t j = 0; j < m; ++j) {
+          const uint32_t r = t[j] * w - (uint32_t)(((uint64_t)t[j] * ws) >> 32) * q;
+          t[m + j] = std::min(r, r - q);
+        }
       }
     }
-  }
   // final inverse factors N^-1 per logN (standalone transforms), then the same times
   // the last stage's twiddle (NttArgs::scale_w)
-  std::vector<std::vector<uint2>> ns(kLogNMax + 1);
+  std::vector<std::vector<uint32_t>> ns(kLogNMax + 1);
   for (int lg = FHE_LOGN_MIN; lg <= kLogNMax; ++lg) {
-    ns[lg].assign(2 * (size_t)Kpad, make_uint2(0, 0));
+    ns[lg].assign(2 * (size_t)Kpad, 0);
     for (int p = 0; p < K; ++p) {
       const uint64_t f = invmod(1ull << lg, c->q[p]);
-      ns[lg][p] = shoup_pair((uint32_t)f, c->q[p]);
-      ns[lg][Kpad + p] = shoup_pair((uint32_t)mulmod64(f, last_inv_twiddle(c, p), c->q[p]), c->q[p]);
+      ns[lg][p] = to_mont(f, c->q[p]);
+      ns[lg][Kpad + p] = to_mont(mulmod64(f, last_inv_twiddle(c, p), c->q[p]), c->q[p]);
     }
   }
   // upload

@@ -57,11 +57,11 @@ template <int NKB>
 constexpr int crt_bufs() { return NKB <= 5 ? 2 : 1; }
 
 constexpr int kCrtRow = 32 * 16 + 48;  // exchange words per row u: rows and prime halves on different banks
-constexpr int kCrtTw = 36;             // words of a prime's 16 twiddle pairs (four primes on different banks)
+constexpr int kCrtTw = 20;             // words of a prime's twiddles (four primes on different banks)
 
 // Dynamic LDS: the digit table (LDSA), the exchange buffers, twiddles and constants.
 static size_t crt_lds(int nkb, int bufs, int ntiles, bool table) {
-  return ((table ? (size_t)ntiles * nkb * 256 : 0) + (size_t)bufs * 16 * kCrtRow + (size_t)32 * nkb * (kCrtTw + 2) +
+  return ((table ? (size_t)ntiles * nkb * 256 : 0) + (size_t)bufs * 16 * kCrtRow + (size_t)32 * nkb * (kCrtTw + 3) +
           16 * ntiles) * 4;
 }
 
@@ -70,25 +70,22 @@ __device__ __forceinline__ void crt_cols_kernel_body(const CrtArgs& a, const Blk
   constexpr int WAVES = 8, BUFS = crt_bufs<NKB>();
   extern __shared__ v4i sA[];
   uint32_t* const s_x = (uint32_t*)(sA + (LDSA ? a.ntiles * NKB * 64 : 0));
-  uint32_t* const s_tw = s_x + BUFS * 16 * kCrtRow;  // [prime][16 pairs]: final factor or entry 1, then entries 2..15
+  uint32_t* const s_tw = s_x + BUFS * 16 * kCrtRow;  // [prime]: final factor, its second half or entry 1, entries 2..15
   uint32_t* const s_q = s_tw + 32 * NKB * kCrtTw;
-  uint32_t* const s_r = s_q + 32 * NKB;
+  uint32_t* const s_qn = s_q + 32 * NKB;
+  uint32_t* const s_r = s_qn + 32 * NKB;
   uint32_t* const s_mneg = s_r + 32 * NKB;
   uint32_t* const s_eneg = s_mneg + 8 * a.ntiles;
   for (int k = threadIdx.x; k < 32 * NKB; k += 64 * WAVES) {
     const bool in = k < a.K;
     s_q[k] = in ? a.pc[k].q : 1u;
+    s_qn[k] = in ? a.pc[k].qneg : 0u;
     s_r[k] = in ? a.rq[k] : 0u;  // rows past K add nothing to the quotient
   }
   for (int i = threadIdx.x; i < 32 * NKB * 16; i += 64 * WAVES) {
     const int k = i >> 4, e = i & 15;
-    uint2 w = make_uint2(0, 0);
-    if (k < a.K) {
-      if (e == 0) w = a.scale ? a.scale[k] : w;
-      else if (e == 1 && a.scale) w = a.scale_w[k];
-      else w = a.itw[(long long)k * kNMax + e];
-    }
-    *(uint2*)(s_tw + k * kCrtTw + 2 * e) = w;
+    const uint32_t* src = a.scale && e < 2 ? (e ? a.scale_w : a.scale) + k : a.itw + (long long)k * kNMax + e;
+    s_tw[k * kCrtTw + e] = k < a.K ? *src : 0u;
   }
   for (int l = threadIdx.x; l < 8 * a.ntiles; l += 64 * WAVES) {
     s_mneg[l] = a.mneg[l];
@@ -98,9 +95,11 @@ __device__ __forceinline__ void crt_cols_kernel_body(const CrtArgs& a, const Blk
     for (int f = threadIdx.x; f < a.ntiles * NKB * 64; f += 64 * WAVES) sA[f] = a.A[f];
   __syncthreads();
   const v4i* At = LDSA ? sA : a.A;
-  const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t pr = threadIdx.x >> 4, col = threadIdx.x & 15;  // this thread's prime and column of a block of 32 primes
+  // this thread's lane as (c, h), and its prime and column of a block of 32 primes; made
+  // opaque again for each item, or the offsets derived from them would be hoisted out of the
+  // item loop, each holding a register
+  uint32_t lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5, pr = threadIdx.x >> 4, col = lane & 15;
   const uint32_t row = 4u * (uint32_t)a.N;                       // bytes between residue (or limb) rows
   const uint64_t frac0 = a.frac0;
   const bool scaled = a.scale != nullptr;
@@ -125,74 +124,97 @@ __device__ __forceinline__ void crt_cols_kernel_body(const CrtArgs& a, const Blk
 #pragma unroll
     for (int u = 0; u < 16; ++u) x[u] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, (int)(u * (row >> 4)), 0);
   };
+  // the last four inverse stages of this thread's column of block kb
+  auto stages = [&](uint32_t (&x)[16], int kb) {
+    const uint32_t k = 32u * kb + pr;
+    const Mod M(s_q[k], s_qn[k]);
+    const uint32_t* const tp = s_tw + k * kCrtTw;
+    uint32_t w[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) w[e] = tp[e];
+#pragma unroll
+    for (int m = 8; m >= 2; m /= 2) {
+      const int d = 8 / m;
+#pragma unroll
+      for (int g = 0; g < m; ++g)
+#pragma unroll
+        for (int u = 2 * d * g; u < 2 * d * g + d; ++u) gs_bfly(x[u], x[u + d], w[m + g], M);
+    }
+    if (scaled) {  // the last stage with the final factor folded in
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const uint32_t xs = x[u], ys = x[u + 8];
+        x[u] = mont_s(xs + ys + M.neg2q, w[0], M);
+        x[u + 8] = mont_s(xs - ys, w[1], M);
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) gs_bfly(x[u], x[u + 8], w[1], M);
+    }
+  };
+  uint32_t nb = 0;  // blocks of primes done, modulo the buffers
+  auto store = [&](const uint32_t (&x)[16]) {
+    uint32_t* const xw = s_x + (BUFS == 2 ? (nb & 1) * 16 * kCrtRow : 0) + pr * 16 + (pr >> 4) * 32 + col;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) xw[u * kCrtRow] = x[u];
+  };
   uint32_t left;
   const uint32_t* xb = source(item, left);
-  uint32_t xv[16], xn[16];
-  fetch(xv, xb, left, 0);
-  uint32_t nb = 0;  // blocks of primes done, modulo the buffers
+  // Residues of every block: as a block's digit planes take their 16 registers, the
+  // residues they came from leave 16, so all of an item's loads can be in flight at once.
+  uint32_t xv[NKB][16];
+  fetch(xv[0], xb, left, 0);
 
   for (; item < end; item += step) {
     const int z = item / nblk;
     const uint32_t j0 = 16u * (uint32_t)(item % nblk);
+    opaque(lane);
+    opaque(c);
+    opaque(h);
+    opaque(pr);
+    opaque(col);
 
-    // phase 1: the last transform stages, then x_k's part of the quotient and digit planes
+    // phase 1: the last transform stages, then x_k's part of the quotient and digit planes.
+    // Between two barriers a wave reads its unit of one block and runs the stages of the next
+    // while the reads are in flight.
     v4i B[NKB][4];
     uint64_t frac = 0;  // sum_k x_k floor(2^54 / q_k)
 #pragma unroll
+    for (int kb = 1; kb < NKB; ++kb) fetch(xv[kb], xb, left, kb);
+    __builtin_amdgcn_sched_barrier(0);
+    stages(xv[0], 0);
+    store(xv[0]);
+#pragma unroll
     for (int kb = 0; kb < NKB; ++kb) {
-      if (kb + 1 < NKB) fetch(xn, xb, left, kb + 1);
-      {
-        const uint32_t k = 32u * kb + pr;
-        const uint32_t q = s_q[k], two_q = 2 * q;
-        const v4i* tp = (const v4i*)(s_tw + k * kCrtTw);
-#pragma unroll
-        for (int m = 8; m >= 2; m /= 2) {
-          const int d = 8 / m;
-#pragma unroll
-          for (int g = 0; g < m; g += 2) {
-            const v4i w = tp[(m + g) >> 1];
-            const uint2 w0 = make_uint2((uint32_t)w[0], (uint32_t)w[1]), w1 = make_uint2((uint32_t)w[2], (uint32_t)w[3]);
-#pragma unroll
-            for (int u = 2 * d * g; u < 2 * d * g + d; ++u) gs_bfly(xv[u], xv[u + d], w0, q, two_q);
-#pragma unroll
-            for (int u = 2 * d * (g + 1); u < 2 * d * (g + 1) + d; ++u) gs_bfly(xv[u], xv[u + d], w1, q, two_q);
-          }
-        }
-        const v4i w = tp[0];
-        if (scaled) {  // the last stage with the final factor folded in
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const uint32_t xs = xv[u], ys = xv[u + 8];
-            xv[u] = shoup_lazy(xs + ys, (uint32_t)w[0], (uint32_t)w[1], q);
-            xv[u + 8] = shoup_lazy(xs - ys + two_q, (uint32_t)w[2], (uint32_t)w[3], q);
-          }
-        } else {
-#pragma unroll
-          for (int u = 0; u < 8; ++u)
-            gs_bfly(xv[u], xv[u + 8], make_uint2((uint32_t)w[2], (uint32_t)w[3]), q, two_q);
-        }
-      }
-      uint32_t* const buf = s_x + (BUFS == 2 ? (nb & 1) * 16 * kCrtRow : 0);
-      ++nb;
-      {
-        uint32_t* const xw = buf + pr * 16 + (pr >> 4) * 32 + col;
-#pragma unroll
-        for (int u = 0; u < 16; ++u) xw[u * kCrtRow] = xv[u];
-      }
       __syncthreads();
-      const uint32_t* const xr = buf + (2 * wave + (c >> 4)) * kCrtRow + h * (16 * 16 + 32) + (c & 15);
-      const uint32_t* const rp = s_r + 32 * kb + 16 * h;
       uint32_t s[16];
+      uint4 rq[4];
+      {
+        const uint32_t* const xr = s_x + (BUFS == 2 ? (nb & 1) * 16 * kCrtRow : 0) +
+                                   (2 * wave + (c >> 4)) * kCrtRow + h * (16 * 16 + 32) + (c & 15);
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const uint32_t y = xr[16 * i];
-        frac += (uint64_t)y * rp[i];
-        s[i] = y ^ 0x80808080u;
+        for (int i = 0; i < 16; ++i) s[i] = xr[16 * i];
+        const uint4* const rp = (const uint4*)(s_r + 32 * kb + 16 * h);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) rq[i] = rp[i];
       }
+      ++nb;
+      __builtin_amdgcn_sched_barrier(0);
+      if (kb + 1 < NKB) stages(xv[kb + 1], kb + 1);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
+        frac += (uint64_t)s[4 * r] * rq[r].x;
+        frac += (uint64_t)s[4 * r + 1] * rq[r].y;
+        frac += (uint64_t)s[4 * r + 2] * rq[r].z;
+        frac += (uint64_t)s[4 * r + 3] * rq[r].w;
+        asm volatile("" : "+v"(frac));  // here, or all blocks' residues stay live to the end
         uint32_t p0, p1, p2, p3;
         byte_planes(s[4 * r], s[4 * r + 1], s[4 * r + 2], s[4 * r + 3], p0, p1, p2, p3);
+        p0 ^= 0x80808080u;
+        p1 ^= 0x80808080u;
+        p2 ^= 0x80808080u;
+        p3 ^= 0x80808080u;
         // materialised here: left to the compiler, the planes may be recomputed later
         opaque(p0);
         opaque(p1);
@@ -203,27 +225,28 @@ __device__ __forceinline__ void crt_cols_kernel_body(const CrtArgs& a, const Blk
         B[kb][2][r] = (int)p2;
         B[kb][3][r] = (int)p3;
       }
-      if (BUFS == 1) __syncthreads();  // the one buffer has been read
       if (kb + 1 < NKB) {
-#pragma unroll
-        for (int u = 0; u < 16; ++u) xv[u] = xn[u];
+        if (BUFS == 1) __syncthreads();  // the one buffer has been read
+        store(xv[kb + 1]);
       }
     }
+    if (BUFS == 1) __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
     frac = sum_lane_halves(frac) + frac0;
     const uint32_t alpha = (uint32_t)(frac >> 54);
     if (item + step < end) {  // the next block's first residues, in flight during the products
       xb = source(item + step, left);
-      fetch(xv, xb, left, 0);
+      fetch(xv[0], xb, left, 0);
     }
     // opaque multipliers of mad_i64 (the unit multipliers distinct per term of a sum)
     uint32_t one0 = 1, one1 = 1, one2 = 1, one3 = 1, m8 = 256, m16 = 65536, m24 = 16777216;
-    opaque(one0);
-    opaque(one1);
-    opaque(one2);
-    opaque(one3);
-    opaque(m8);
-    opaque(m16);
-    opaque(m24);
+    opaque_s(one0);
+    opaque_s(one1);
+    opaque_s(one2);
+    opaque_s(one3);
+    opaque_s(m8);
+    opaque_s(m16);
+    opaque_s(m24);
 
     // phase 2, per tile of 8 limbs: the digit-plane products, recombination, carries.
     // Lane half h holds limbs l = 8 t + 4 h + i (i < 4) with C_ab = acc_a[4 b + i] (y plane
@@ -236,11 +259,13 @@ __device__ __forceinline__ void crt_cols_kernel_body(const CrtArgs& a, const Blk
     const int topbits = a.outbits - 32 * (a.Lout - 1);
     int64_t cin = 0;  // carry into the tile (used in lane half 0)
     v16i acc0, acc1, acc2, acc3;
-    auto products = [&](int t) {
+    v4i Af[NKB];  // the next tile's fragments
+    auto fragments = [&](int t) {
       const v4i* Ap = At + ((long long)t * NKB) * 64 + lane;
-      v4i Af[NKB];
 #pragma unroll
       for (int kb = 0; kb < NKB; ++kb) Af[kb] = Ap[kb * 64];
+    };
+    auto products = [&]() {
       acc0 = v16i{};
       acc1 = v16i{};
       acc2 = v16i{};
@@ -305,16 +330,18 @@ __device__ __forceinline__ void crt_cols_kernel_body(const CrtArgs& a, const Blk
         store_at(o, out_off + i * row, w);
       }
     };
+    fragments(0);
     for (int t = 0; t < a.ntiles - 1; ++t) {
-      products(t);
+      products();
       sums();
+      fragments(t + 1);  // on their way while this tile is finished
       finish(t, false);
       o += 8 * a.N;
     }
-    products(a.ntiles - 1);
+    products();
     sums();
     finish(a.ntiles - 1, true);
-    }
+  }
 }
 
 template <int NKB, bool LDSA>

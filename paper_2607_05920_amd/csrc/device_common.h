@@ -138,83 +138,78 @@ __device__ __forceinline__ int cell_of(const CellSeg* seg, int ncells, Blk& bk) 
 template <typename T>
 using gptr = const __attribute__((address_space(1))) T*;
 
-// One prime's twiddle table (Shoup pairs) through such a pointer.
+// One prime's twiddle table (32-bit words, Montgomery form) through such a pointer.
 struct TwTab {
-  gptr<uint64_t> p;
-  __device__ __forceinline__ uint2 operator[](int i) const {
-    const uint64_t v = p[i];
-    return make_uint2((uint32_t)v, (uint32_t)(v >> 32));
+  gptr<uint32_t> p;
+  __device__ __forceinline__ uint32_t operator[](int i) const { return p[i]; }
+  // CNT consecutive entries from i (a multiple of CNT, a power of two) in loads of up to 16
+  // bytes
+  template <int CNT>
+  __device__ __forceinline__ void run(int i, uint32_t* w) const {
+    if (CNT == 1) {
+      w[0] = p[i];
+    } else if (CNT == 2) {
+      const uint64_t v = *(gptr<uint64_t>)(p + i);
+      w[0] = (uint32_t)v;
+      w[1] = (uint32_t)(v >> 32);
+    } else {
+#pragma unroll
+      for (int e = 0; e < CNT; e += 4) {
+        const v4i_t v = *(gptr<v4i_t>)(p + i + e);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) w[e + k] = (uint32_t)v[k];
+      }
+    }
   }
-  // entries i and i + 1 in one 16-byte load (i even)
-  __device__ __forceinline__ v4i_t pair(int i) const { return *(gptr<v4i_t>)(p + i); }
 };
-__device__ __forceinline__ TwTab tw_table(const uint2* t, int p) {
-  return TwTab{(gptr<uint64_t>)t + (long long)p * kNMax};
+__device__ __forceinline__ TwTab tw_table(const uint32_t* t, int p) {
+  return TwTab{(gptr<uint32_t>)t + (long long)p * kNMax};
 }
 
-// Low 32 bits of a b + c in one v_mad_u64_u32 (the compiler would otherwise narrow
-// the expression to a 32-bit multiply and an add).
-__device__ __forceinline__ uint32_t mad_lo(uint32_t a, uint32_t b, uint32_t c) {
-  uint64_t r;
-  asm("v_mad_u64_u32 %0, vcc, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"((uint64_t)c) : "vcc");
-  return (uint32_t)r;
+// A prime as the butterflies use it: the same for the whole wave, or (second form) one per
+// lane.  neg2q is -2q, opaque, so that adding it stays one operation of a three-input add.
+struct Mod {
+  uint32_t q, two_q, qneg, neg2q;
+  __device__ __forceinline__ explicit Mod(const PrimeC& c)
+      : q(__builtin_amdgcn_readfirstlane(c.q)), two_q(2 * q), qneg(__builtin_amdgcn_readfirstlane(c.qneg)),
+        neg2q(0u - 2 * q) {
+    asm("" : "+s"(neg2q));
+  }
+  __device__ __forceinline__ Mod(uint32_t q_, uint32_t qneg_) : q(q_), two_q(2 * q_), qneg(qneg_), neg2q(0u - 2 * q_) {
+    asm("" : "+v"(neg2q));
+  }
+};
+
+// Signed Montgomery product: y w 2^-32 mod q in (0, 2q) for |y| < 2q and w in [0, q).
+// T = y w + q 2^32 lies within 2 q^2 of q 2^32, and m q, m the signed word that clears T's
+// low half, within q 2^31 of 0; with 2 q^2 < q 2^31 (q < 2^30) the high word of T + m q is
+// in (0, 2q).  Three operations, a four-byte twiddle, and y may be a plain difference.
+__device__ __forceinline__ uint32_t mont_s(uint32_t y, uint32_t w, const Mod& M) {
+  int64_t T = (int64_t)(int32_t)y * (int32_t)w + (int64_t)((uint64_t)M.q << 32);
+  asm("" : "+v"(T));  // its low half as it is (the compiler would multiply again for it)
+  const uint32_t m = (uint32_t)T * M.qneg;
+  return (uint32_t)((uint64_t)((int64_t)(int32_t)m * (int32_t)M.q + T) >> 32);
 }
 
-__device__ __forceinline__ void ct_bfly(uint32_t& X, uint32_t& Y, uint2 w, uint32_t q,
-                                        uint32_t two_q) {
-  // Lazy Cooley-Tukey butterfly: X, Y in [0, 4q) -> [0, 4q).  With the Shoup product
-  // t = Y w - qh q in [0, 2q), nt = qh q - Y w = -t (mod 2^32); then X + t = X - nt
-  // and X - t + 2q = X + nt + 2q (one three-input add).  The forward table holds
-  // (-w mod 2^32, floor(w 2^32 / q)), so nt = qh q + Y (-w) is one multiply and one
-  // multiply-add: 7 operations per butterfly.
-  const uint32_t x = csub(X, two_q);
-  const uint32_t qh = __umulhi(Y, w.y);
-  const uint32_t nt = mad_lo(qh, q, Y * w.x);
-  X = x - nt;
-  Y = x + nt + two_q;
+// Lazy Cooley-Tukey butterfly.  Forward values are held less 2q: words in [-2q, 2q), two's
+// complement, which the product takes as they are; with t = Y w in (0, 2q) and x = X or
+// X + 2q in [0, 2q) (an unsigned minimum), X + t - 2q and x - t are in [-2q, 2q) again:
+// 7 operations.  FIRST: X is in [0, 2q) already (the transform's first stage).
+template <bool FIRST = false>
+__device__ __forceinline__ void ct_bfly(uint32_t& X, uint32_t& Y, uint32_t w, const Mod& M) {
+  const uint32_t x = FIRST ? X : min(X, X + M.two_q);
+  const uint32_t t = mont_s(Y, w, M);
+  X = x + t + M.neg2q;
+  Y = x - t;
 }
+// A forward value in [-2q, 2q) to [0, 2q).
+__device__ __forceinline__ uint32_t fwd_lift(uint32_t X, const Mod& M) { return min(X, X + M.two_q); }
 
-__device__ __forceinline__ void gs_bfly(uint32_t& X, uint32_t& Y, uint2 w, uint32_t q,
-                                        uint32_t two_q) {
-  // Lazy Gentleman-Sande butterfly: X, Y in [0, 2q) -> [0, 2q); the Shoup product of
-  // d = X - Y + 2q is d w - qh q = d w + qh (-q), one multiply-add.
+// Lazy Gentleman-Sande butterfly: X, Y in [0, 2q) -> [0, 2q); 7 operations.
+__device__ __forceinline__ void gs_bfly(uint32_t& X, uint32_t& Y, uint32_t w, const Mod& M) {
   const uint32_t x = X, y = Y;
-  X = csub(x + y, two_q);
-  const uint32_t d = x - y + two_q;
-  const uint32_t qh = __umulhi(d, w.y);
-  Y = mad_lo(qh, 0u - q, d * w.x);
-}
-
-// Inverse twiddles from the forward table.  The bit-reversed index (over the table's
-// 16 bits) of 2H - 1 - i is 2^16 minus that of H + i (H a power of two, i < H), and
-// psi^(2^16) = -1, so psi^-bitrev(H + i) = -v for v = psi^bitrev(2H - 1 - i): for a
-// stage of H groups starting at table index mi H - H (mi the caller's mirrored
-// multiplier), group g's inverse twiddle is minus forward entry mi H - 1 - g.  That
-// entry holds (-v mod 2^32, floor(v 2^32 / q)); mirror_tw makes it the Shoup pair of v
-// (the negation opaque, else the compiler moves it into every butterfly), which
-// gs_bfly_neg takes.
-__device__ __forceinline__ uint2 mirror_tw(uint2 f) {
-  uint32_t v = 0u - f.x;
-  opaque(v);
-  return make_uint2(v, f.y);
-}
-// The same for a wave-uniform twiddle: the negation stays in scalar registers (the
-// compiler rejects the constraint for a value it cannot keep there).
-__device__ __forceinline__ uint2 mirror_tw_s(uint2 f) {
-  uint32_t v = 0u - f.x;
-  asm volatile("" : "+s"(v));
-  return make_uint2(v, f.y);
-}
-
-// gs_bfly with the twiddle given as -v (the Shoup pair of v): (X - Y)(-v) = (Y - X) v,
-// the Shoup product of d = Y - X + 2q.
-__device__ __forceinline__ void gs_bfly_neg(uint32_t& X, uint32_t& Y, uint2 v, uint32_t q,
-                                            uint32_t two_q) {
-  const uint32_t x = X, y = Y;
-  X = csub(x + y, two_q);
-  const uint32_t d = y - x + two_q;
-  const uint32_t qh = __umulhi(d, v.y);
-  Y = mad_lo(qh, 0u - q, d * v.x);
+  X = csub(x + y, M.two_q);
+  Y = mont_s(x - y, w, M);
 }
 
 // The limbs of input polynomial z of a lift.
@@ -229,47 +224,21 @@ __device__ __forceinline__ const uint32_t* lift_source(const LiftArgs& a, uint32
   return a.limbs + (long long)z * a.in_stride;
 }
 
-// The four outer stages of a transform on one column {c + (N / 16) u}, u < 16: forward
-// stages of 1, 2, 4 and 8 groups (table entries 1..15), values in [0, 4q) to [0, 4q).
-__device__ __forceinline__ void cols16_forward(uint32_t (&x)[16], TwTab tw, uint32_t q, uint32_t two_q) {
+// The first four stages of a transform on one column {c + (N / 16) u}, u < 16: forward
+// stages of 1, 2, 4 and 8 groups (table entries 1..15), values in [0, 2q) to [-2q, 2q).
+__device__ __forceinline__ void cols16_forward(uint32_t (&x)[16], TwTab tw, const Mod& M) {
 #pragma unroll
   for (int m = 1; m <= 8; m *= 2) {
     const int h = 8 / m;
 #pragma unroll
     for (int g = 0; g < m; ++g) {
-      const uint2 w = tw[m + g];
+      const uint32_t w = tw[m + g];
 #pragma unroll
-      for (int u = 2 * h * g; u < 2 * h * g + h; ++u) ct_bfly(x[u], x[u + h], w, q, two_q);
+      for (int u = 2 * h * g; u < 2 * h * g + h; ++u) {
+        if (m == 1) ct_bfly<true>(x[u], x[u + h], w, M);
+        else ct_bfly(x[u], x[u + h], w, M);
+      }
     }
-  }
-}
-
-// The last four inverse stages, values in [0, 2q) to canonical ones; with SCALE the last
-// stage (one group, twiddle w = entry 1) takes the final factor c: (X + Y) c and
-// (X - Y) (w c), pairs sc and sw.
-template <bool SCALE>
-__device__ __forceinline__ void cols16_inverse(uint32_t (&x)[16], TwTab itw, uint2 sc, uint2 sw, uint32_t q,
-                                               uint32_t two_q) {
-#pragma unroll
-  for (int m = 8; m >= (SCALE ? 2 : 1); m /= 2) {
-    const int h = 8 / m;
-#pragma unroll
-    for (int g = 0; g < m; ++g) {
-      const uint2 w = itw[m + g];
-#pragma unroll
-      for (int u = 2 * h * g; u < 2 * h * g + h; ++u) gs_bfly(x[u], x[u + h], w, q, two_q);
-    }
-  }
-  if (SCALE) {
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const uint32_t xs = x[u], ys = x[u + 8];
-      x[u] = csub(shoup_lazy(xs + ys, sc.x, sc.y, q), q);
-      x[u + 8] = csub(shoup_lazy(xs - ys + two_q, sw.x, sw.y, q), q);
-    }
-  } else {
-#pragma unroll
-    for (int u = 0; u < 16; ++u) x[u] = csub(x[u], q);
   }
 }
 

@@ -27,11 +27,11 @@ struct NttArgs {
   int K = 0;
   int per_group = 0;
   long long group_stride = 0;
-  const uint2* tw = nullptr; // [prime][kNMax] (w, floor(w 2^32 / q)), bit-reversed powers
+  const uint32_t* tw = nullptr; // [prime][kNMax] bit-reversed powers w 2^32 mod q
   const PrimeC* pc = nullptr;
-  const uint2* scale = nullptr; // inverse only: per-prime final factor (w, w'); null: the
-                                // inputs already carry it (only the canonical reduction)
-  const uint2* scale_w = nullptr; // with scale: the factor times the last stage's twiddle
+  const uint32_t* scale = nullptr; // inverse only: per-prime final factor times 2^32; null: the
+                                   // inputs already carry it (only the canonical reduction)
+  const uint32_t* scale_w = nullptr; // with scale: the factor times the last stage's twiddle
                                   // (table entry 1), folded into that stage
   int ntr = 0;         // number of transforms (set by launch_ntt; a multiple of K)
 };
@@ -49,8 +49,8 @@ struct RowsArgs {
   uint32_t* out = nullptr;         // relin: group c at out + c out_stride, [2][K][N]
   long long out_stride = 0;
   int logN = 0, K = 0, cnum = 0;
-  const uint2* tw = nullptr;       // forward and inverse twiddles, [prime][kNMax]
-  const uint2* itw = nullptr;
+  const uint32_t* tw = nullptr;    // forward and inverse twiddles, [prime][kNMax]
+  const uint32_t* itw = nullptr;
   const PrimeC* pc = nullptr;
 };
 
@@ -80,7 +80,7 @@ struct LiftArgs {
   int lds_max = 0, cus = 0;  // device: LDS bytes per workgroup, compute units
   // with the first four transform stages (launch_lift_cols): forward twiddles, and the
   // workgroups that share a block of columns (set by the launch)
-  const uint2* tw = nullptr;
+  const uint32_t* tw = nullptr;
   int nsplit = 1;
 };
 
@@ -96,9 +96,9 @@ struct CrtArgs {
   int ntiles = 0;           // tiles of 8 output limbs
   const v4i_t* A = nullptr; // [tile][k-block][lane]: the 16 MFMA A bytes of each lane
   const PrimeC* pc = nullptr;
-  const uint2* itw = nullptr;     // inverse twiddles, [prime][kNMax]
-  const uint2* scale = nullptr;   // per-prime final factor and (scale_w) the factor times the last
-  const uint2* scale_w = nullptr; // stage's twiddle; null: the inputs already carry it
+  const uint32_t* itw = nullptr;  // inverse twiddles, [prime][kNMax]
+  const uint32_t* scale = nullptr;    // per-prime final factor and (scale_w) the factor times the last
+  const uint32_t* scale_w = nullptr;  // stage's twiddle; null: the inputs already carry it
   const uint32_t* rq = nullptr;   // [k] = floor(2^54 / q_k)
   uint64_t frac0 = 0;             // constant of the quotient (CrtTab)
   const uint32_t* mneg = nullptr; // [l < 8 ntiles] limbs of (-M) mod 2^(32 Lout), zero beyond Lout
@@ -255,19 +255,20 @@ hipError_t launch_ntt(const NttArgs& a, int ntransforms, bool inverse, hipStream
 // transformed side in natural instead of bit-reversed order.  The inverse needs a.scale.
 hipError_t launch_ntt_whole(const NttArgs& a, int ntransforms, bool inverse, bool natural, hipStream_t s);
 bool ntt_whole_wanted(int logN, bool natural, long long ntransforms);
-// Ring products split their transforms as 16 x N / 16: the four outer stages (launch_cols16,
-// or inside the lift and the reconstruction) and the fused pass over rows of N / 16 points.
-hipError_t launch_cols16(const NttArgs& a, int ntransforms, bool inverse, hipStream_t s);
+// Ring products split their transforms as 16 x N / 16: the four outer stages in the lift (or,
+// launch_cols16, after it) and the reconstruction, and the fused pass over rows of N / 16
+// points between them.
+hipError_t launch_cols16(const NttArgs& a, int ntransforms, hipStream_t s);
 hipError_t launch_rows_fused(const RowsArgs& a, int mode, hipStream_t s);
 hipError_t launch_rows_mid(const RowsArgs& a, int mode, hipStream_t s);  // rows above 256 points
 // Transposes rows of 2^S words into the register order of the fused relinearization pass.
 hipError_t launch_row_transpose(const uint32_t* src, uint32_t* dst, long long total, int S, hipStream_t s);
 // data[r][j] <- data[r][j] scale[r mod K] mod q_(r mod K) for `rows` rows of N words
 // (canonical in, canonical out).
-hipError_t launch_scale_rows(uint32_t* data, long long rows, int K, int N, const uint2* scale, const PrimeC* pc,
+hipError_t launch_scale_rows(uint32_t* data, long long rows, int K, int N, const uint32_t* scale, const PrimeC* pc,
                              hipStream_t s);
 hipError_t launch_lift(const LiftArgs& a, int npoly, hipStream_t s, const Tuning& t = Tuning());
-// the lift and the four outer forward stages (residues in [0, 4q)); out_stride a multiple of K N
+// the lift and the four outer forward stages (residues less 2q, in [-2q, 2q)); out_stride a multiple of K N
 hipError_t launch_lift_cols(const LiftArgs& a, int npoly, hipStream_t s, const Tuning& t = Tuning());
 hipError_t launch_crt_cols(CrtArgs a, int npoly, hipStream_t s);
 hipError_t launch_compose(const ComposeArgs& a, int cnum, hipStream_t s);

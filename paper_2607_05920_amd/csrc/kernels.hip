@@ -95,9 +95,9 @@ __device__ __forceinline__ void ntt_pass_kernel_body(const NttArgs& a, const Blk
   const int jb = jg * CG;
   const int grp = jb / pk, r = (jb % pk) * a.K + p;
   uint32_t* base = a.data + (long long)grp * a.group_stride + (long long)r * N;
-  const PrimeC pc = a.pc[p];
-  const uint32_t q = pc.q, two_q = pc.two_q;
-  const uint2* tw = a.tw + (long long)p * kNMax;
+  const Mod M(a.pc[p]);
+  const uint32_t q = M.q;
+  const TwTab tw = tw_table(a.tw, p);
 
   // ROWS: element e of block sg at sg * n + e.  COLS: element e of column sg at
   // sg + (N / n) e.  Elements are addressed through a buffer resource over the transform
@@ -130,9 +130,12 @@ __device__ __forceinline__ void ntt_pass_kernel_body(const NttArgs& a, const Blk
       const int m = 1 << st, h = 8 >> st;
 #pragma unroll
       for (int g = 0; g < m; ++g) {
-        const uint2 w = tw[tw_mul * m + g];
+        const uint32_t w = tw[tw_mul * m + g];
 #pragma unroll
-        for (int u = 2 * h * g; u < 2 * h * g + h; ++u) ct_bfly(x[u], x[u + h], w, q, two_q);
+        for (int u = 2 * h * g; u < 2 * h * g + h; ++u) {
+          if (!ROWS && st == 0) ct_bfly<true>(x[u], x[u + h], w, M);
+          else ct_bfly(x[u], x[u + h], w, M);
+        }
       }
     }
 #pragma unroll
@@ -152,14 +155,14 @@ __device__ __forceinline__ void ntt_pass_kernel_body(const NttArgs& a, const Blk
       const int m = n / (2 * t);
 #pragma unroll
       for (int b0 = 0; b0 < 16; b0 += 2 * t) {
-        const uint2 w = tw[tw_mul * m + jt * (8 / t) + b0 / (2 * t)];
+        const uint32_t w = tw[tw_mul * m + jt * (8 / t) + b0 / (2 * t)];
 #pragma unroll
-        for (int u = b0; u < b0 + t; ++u) ct_bfly(x[u], x[u + t], w, q, two_q);
+        for (int u = b0; u < b0 + t; ++u) ct_bfly(x[u], x[u + t], w, M);
       }
     }
     if (ROWS) {  // last forward pass: canonical output
 #pragma unroll
-      for (int u = 0; u < 16; ++u) x[u] = csub(csub(x[u], two_q), q);
+      for (int u = 0; u < 16; ++u) x[u] = csub(fwd_lift(x[u], M), q);
     }
     if (ROWS) {  // a lane's 16 consecutive words: four 16-byte stores
 #pragma unroll
@@ -190,9 +193,9 @@ __device__ __forceinline__ void ntt_pass_kernel_body(const NttArgs& a, const Blk
       const int h = n / (2 * t);
 #pragma unroll
       for (int b0 = 0; b0 < 16; b0 += 2 * t) {
-        const uint2 w = tw[tw_mul * h + jt * (8 / t) + b0 / (2 * t)];
+        const uint32_t w = tw[tw_mul * h + jt * (8 / t) + b0 / (2 * t)];
 #pragma unroll
-        for (int u = b0; u < b0 + t; ++u) gs_bfly(x[u], x[u + t], w, q, two_q);
+        for (int u = b0; u < b0 + t; ++u) gs_bfly(x[u], x[u + t], w, M);
       }
     }
 #pragma unroll
@@ -215,21 +218,21 @@ __device__ __forceinline__ void ntt_pass_kernel_body(const NttArgs& a, const Blk
       if (st == 3 && fold) break;
 #pragma unroll
       for (int g = 0; g < h; ++g) {
-        const uint2 w = tw[tw_mul * h + g];
+        const uint32_t w = tw[tw_mul * h + g];
 #pragma unroll
-        for (int u = 2 * hd * g; u < 2 * hd * g + hd; ++u) gs_bfly(x[u], x[u + hd], w, q, two_q);
+        for (int u = 2 * hd * g; u < 2 * hd * g + hd; ++u) gs_bfly(x[u], x[u + hd], w, M);
       }
     }
     if (!ROWS) {  // last inverse pass: final factor (unless the inputs carry it), canonical output
       if (fold) {
         // the last stage (one group, twiddle w = entry 1) with the factor c folded in:
-        // X + Y times c and (X - Y) times w c (scale_w), both below 4q, then canonical
-        const uint2 sc = a.scale[p], sw = a.scale_w[p];
+        // X + Y - 2q times c and (X - Y) times w c (scale_w), then canonical
+        const uint32_t sc = a.scale[p], sw = a.scale_w[p];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
           const uint32_t xs = x[u], ys = x[u + 8];
-          x[u] = csub(shoup_lazy(xs + ys, sc.x, sc.y, q), q);
-          x[u + 8] = csub(shoup_lazy(xs - ys + two_q, sw.x, sw.y, q), q);
+          x[u] = csub(mont_s(xs + ys + M.neg2q, sc, M), q);
+          x[u + 8] = csub(mont_s(xs - ys, sw, M), q);
         }
       } else {
 #pragma unroll
@@ -244,17 +247,6 @@ __device__ __forceinline__ void ntt_pass_kernel_body(const NttArgs& a, const Blk
 template <int S, bool INV, bool ROWS, int BLK = ntt_pass_threads<S, ROWS>(), int CG = 1>
 __global__ __launch_bounds__(BLK) void ntt_pass_kernel(NttArgs a) {
   ntt_pass_kernel_body<S, INV, ROWS, BLK, CG>(a, own_blk());
-}
-
-// The same over the cells of a stage-batched plan: one launch, each workgroup in its
-// cell's segment (cell_of) with that cell's arguments.
-template <int S, bool INV, bool ROWS, int BLK, int CG = 1>
-__global__ __launch_bounds__(BLK) void ntt_pass_kernel_multi(
-    const NttArgs* __restrict__ cells, const CellSeg* __restrict__ seg, int ncells) {
-  Blk bk;
-  const int c = cell_of(seg, ncells, bk);
-  if (c < 0) return;
-  ntt_pass_kernel_body<S, INV, ROWS, BLK, CG>(cells[c], bk);
 }
 
 // ---------------------------------------------------------------------------- fused row pass
@@ -273,66 +265,37 @@ __global__ __launch_bounds__(BLK) void ntt_pass_kernel_multi(
 // A row's twiddles for one direction, loaded ahead of the stages that use them: the
 // exchange's ordering points keep the compiler from moving loads across them, so the
 // loads are issued before (the strided stages' 15, wave-uniform when a wave holds one
-// sub-row, land in scalar registers; the contiguous stages' up to 15 per thread).
-// MIR: the inverse direction's come from the forward table (mirror_tw, applied where
-// they are used, so that the loads stay in flight until then).
-template <int S>
+// sub-row, land in scalar registers; the contiguous stages' up to 15 per thread).  The
+// stage of m groups per thread has its entries at [m, 2 m).
 struct RowTw {
-  uint2 s[15];  // strided stages: stage st, group g at (1 << st) - 1 + g
-  uint2 c[15];  // contiguous stages, in the order the stages run
+  uint32_t s[16];  // strided stages
+  uint32_t c[16];  // contiguous stages
 };
 
-// MIR (inverse only): tw is the forward table and tw_mul the mirrored multiplier.
-template <int S, bool INV, bool MIR = false>
-__device__ __forceinline__ void load_strided_tw(RowTw<S>& w, TwTab tw, int tw_mul) {
-#pragma unroll
-  for (int st = 0; st < 4; ++st) {
-    const int m = INV ? (8 >> st) : (1 << st);
-#pragma unroll
-    for (int g = 0; g < m; ++g) w.s[m - 1 + g] = tw[MIR ? tw_mul * m - 1 - g : tw_mul * m + g];
-  }
+__device__ __forceinline__ void load_strided_tw(RowTw& w, TwTab tw, int tw_mul) {
+  tw.run<1>(tw_mul, w.s + 1);
+  tw.run<2>(2 * tw_mul, w.s + 2);
+  tw.run<4>(4 * tw_mul, w.s + 4);
+  tw.run<8>(8 * tw_mul, w.s + 8);
 }
 
-// Index in RowTw::c of the contiguous stage with half-distance t, block b0: the forward
-// stages run t = T/2 .. 1 (8/t twiddles each), the inverse ones t = 1 .. T/2.
 template <int S>
-__device__ constexpr int fwd_ci(int t, int b0) { return 8 / t - 256 / (1 << S) + b0 / (2 * t); }
-__device__ constexpr int inv_ci(int t, int b0) { return 16 - 16 / t + b0 / (2 * t); }
-
-template <int S, bool INV, bool MIR = false>
-__device__ __forceinline__ void load_contig_tw(RowTw<S>& w, TwTab tw, int tw_mul, int j) {
-  constexpr int n = 1 << S, T = n / 16;
-#pragma unroll
-  for (int t = 1; t < T; t <<= 1) {
-    const int cnt = 8 / t;  // this thread's twiddles of the stage: groups j cnt + k, k < cnt
-    if (!MIR) {
-#pragma unroll
-      for (int b0 = 0; b0 < 16; b0 += 2 * t)
-        w.c[INV ? inv_ci(t, b0) : fwd_ci<S>(t, b0)] = tw[tw_mul * (n / (2 * t)) + j * cnt + b0 / (2 * t)];
-    } else if (cnt == 1) {
-      w.c[inv_ci(t, 0)] = tw[tw_mul * (n / (2 * t)) - 1 - j];
-    } else {
-      // group j cnt + k is entry tw_mul h - 1 - j cnt - k: element cnt - 1 - k of the
-      // ascending block from tw_mul h - (j + 1) cnt, two entries per 16-byte load (h and
-      // cnt are even, so the block starts on a 16-byte boundary)
-      const int b = tw_mul * (n / (2 * t)) - (j + 1) * cnt;
-#pragma unroll
-      for (int e = 0; e < cnt; e += 2) {
-        const v4i_t v = tw.pair(b + e);
-        w.c[inv_ci(t, 2 * t * (cnt - 1 - e))] = make_uint2((uint32_t)v[0], (uint32_t)v[1]);
-        w.c[inv_ci(t, 2 * t * (cnt - 2 - e))] = make_uint2((uint32_t)v[2], (uint32_t)v[3]);
-      }
-    }
-  }
+__device__ __forceinline__ void load_contig_tw(RowTw& w, TwTab tw, int tw_mul, int j) {
+  // thread j's groups of the stage of m per thread (half-distance 8 / m): j m + g < m T
+  constexpr int T = (1 << S) / 16;
+  const int b = tw_mul * T + j;
+  if (T >= 16) tw.run<1>(b, w.c + 1);
+  if (T >= 8) tw.run<2>(2 * b, w.c + 2);
+  if (T >= 4) tw.run<4>(4 * b, w.c + 4);
+  tw.run<8>(8 * b, w.c + 8);
 }
 
-// The inverse direction's twiddles, issued at once (before the products that precede
-// their first use): from the inverse table, or with MIR from the forward table at the
-// mirrored multiplier.
-template <int S, bool MIR = false>
-__device__ __forceinline__ void load_inv_tw(RowTw<S>& w, TwTab tab, int tw_mul, int j) {
-  load_contig_tw<S, true, MIR>(w, tab, tw_mul, j);
-  load_strided_tw<S, true, MIR>(w, tab, tw_mul);
+// Both, issued at once: before the first stage, or before the products that precede the
+// inverse direction's.
+template <int S>
+__device__ __forceinline__ void load_row_tw(RowTw& w, TwTab tw, int tw_mul, int j) {
+  load_contig_tw<S>(w, tw, tw_mul, j);
+  load_strided_tw(w, tw, tw_mul);
   __builtin_amdgcn_sched_barrier(0);
 }
 
@@ -342,24 +305,20 @@ __device__ __forceinline__ void load_inv_tw(RowTw<S>& w, TwTab tab, int tw_mul, 
 // HOIST: twiddles loaded ahead of their stages (RowTw).
 template <int S, int NP, int NB, bool HOIST = false>
 __device__ __forceinline__ void fwd_rows(uint32_t (&x)[NP][16], uint32_t* const (&l)[NB], int j, TwTab tw,
-                                         int tw_mul, uint32_t q, uint32_t two_q) {
+                                         int tw_mul, const Mod& M) {
   constexpr int n = 1 << S, T = n / 16;
-  RowTw<S> w;
-  if (HOIST) {  // all of this direction's twiddles issued before the first stage
-    load_strided_tw<S, false>(w, tw, tw_mul);
-    load_contig_tw<S, false>(w, tw, tw_mul, j);
-    __builtin_amdgcn_sched_barrier(0);
-  }
+  RowTw w;
+  if (HOIST) load_row_tw<S>(w, tw, tw_mul, j);
 #pragma unroll
   for (int st = 0; st < 4; ++st) {
     const int m = 1 << st, h = 8 >> st;
 #pragma unroll
     for (int g = 0; g < m; ++g) {
-      const uint2 wg = HOIST ? w.s[m - 1 + g] : tw[tw_mul * m + g];
+      const uint32_t wg = HOIST ? w.s[m + g] : tw[tw_mul * m + g];
 #pragma unroll
       for (int r = 0; r < NP; ++r)
 #pragma unroll
-        for (int u = 2 * h * g; u < 2 * h * g + h; ++u) ct_bfly(x[r][u], x[r][u + h], wg, q, two_q);
+        for (int u = 2 * h * g; u < 2 * h * g + h; ++u) ct_bfly(x[r][u], x[r][u + h], wg, M);
     }
   }
   // the transpose through LDS, NB rows at a time (fewer buffers, more workgroups per CU)
@@ -387,28 +346,26 @@ __device__ __forceinline__ void fwd_rows(uint32_t (&x)[NP][16], uint32_t* const 
     const int m = n / (2 * t);
 #pragma unroll
     for (int b0 = 0; b0 < 16; b0 += 2 * t) {
-      const uint2 wg = HOIST ? w.c[fwd_ci<S>(t, b0)] : tw[tw_mul * m + j * (8 / t) + b0 / (2 * t)];
+      const uint32_t wg = HOIST ? w.c[8 / t + b0 / (2 * t)] : tw[tw_mul * m + j * (8 / t) + b0 / (2 * t)];
 #pragma unroll
       for (int r = 0; r < NP; ++r)
 #pragma unroll
-        for (int u = b0; u < b0 + t; ++u) ct_bfly(x[r][u], x[r][u + t], wg, q, two_q);
+        for (int u = b0; u < b0 + t; ++u) ct_bfly(x[r][u], x[r][u + t], wg, M);
     }
   }
-  // [0, 4q) -> [0, 2q): the products below take lazy inputs
+  // to [0, 2q): the products below take lazy inputs
 #pragma unroll
   for (int r = 0; r < NP; ++r)
 #pragma unroll
-    for (int u = 0; u < 16; ++u) x[r][u] = csub(x[r][u], two_q);
+    for (int u = 0; u < 16; ++u) x[r][u] = fwd_lift(x[r][u], M);
 }
 
 // First inverse n-point row stages of NP rows at once, values at e = 16 j + u in
 // [0, 2q); leaves values in [0, 2q) at e = u T + j for the caller to store.  HOIST: the
-// caller has loaded the twiddles into pre (load_inv_tw, before the products).  MIR: tw
-// is the forward table and tw_mul the mirrored multiplier (mirror_tw).  SU: the strided
-// stages' twiddles are wave-uniform (mirror_tw_s).
-template <int S, int NP, int NB, bool HOIST = false, bool MIR = false, bool SU = false>
+// caller has loaded the twiddles into pre (load_row_tw, before the products).
+template <int S, int NP, int NB, bool HOIST = false>
 __device__ __forceinline__ void inv_rows(uint32_t (&x)[NP][16], uint32_t* const (&l)[NB], int j, TwTab tw,
-                                         int tw_mul, uint32_t q, uint32_t two_q, RowTw<S>& pre) {
+                                         int tw_mul, const Mod& M, const RowTw& pre) {
   constexpr int n = 1 << S, T = n / 16;
 #pragma unroll
   for (int t = 1; t < T; t <<= 1) {
@@ -416,15 +373,11 @@ __device__ __forceinline__ void inv_rows(uint32_t (&x)[NP][16], uint32_t* const 
 #pragma unroll
     for (int b0 = 0; b0 < 16; b0 += 2 * t) {
       const int g = j * (8 / t) + b0 / (2 * t);
-      const uint2 wf = HOIST ? pre.c[inv_ci(t, b0)] : tw[MIR ? tw_mul * h - 1 - g : tw_mul * h + g];
-      const uint2 wg = MIR ? mirror_tw(wf) : wf;
+      const uint32_t wg = HOIST ? pre.c[8 / t + b0 / (2 * t)] : tw[tw_mul * h + g];
 #pragma unroll
       for (int r = 0; r < NP; ++r)
 #pragma unroll
-        for (int u = b0; u < b0 + t; ++u) {
-          if (MIR) gs_bfly_neg(x[r][u], x[r][u + t], wg, q, two_q);
-          else gs_bfly(x[r][u], x[r][u + t], wg, q, two_q);
-        }
+        for (int u = b0; u < b0 + t; ++u) gs_bfly(x[r][u], x[r][u + t], wg, M);
     }
   }
 #pragma unroll
@@ -451,15 +404,11 @@ __device__ __forceinline__ void inv_rows(uint32_t (&x)[NP][16], uint32_t* const 
     const int hd = 1 << st, h = 8 >> st;
 #pragma unroll
     for (int g = 0; g < h; ++g) {
-      const uint2 wf = HOIST ? pre.s[h - 1 + g] : tw[MIR ? tw_mul * h - 1 - g : tw_mul * h + g];
-      const uint2 wg = MIR ? (SU ? mirror_tw_s(wf) : mirror_tw(wf)) : wf;
+      const uint32_t wg = HOIST ? pre.s[h + g] : tw[tw_mul * h + g];
 #pragma unroll
       for (int r = 0; r < NP; ++r)
 #pragma unroll
-        for (int u = 2 * hd * g; u < 2 * hd * g + hd; ++u) {
-          if (MIR) gs_bfly_neg(x[r][u], x[r][u + hd], wg, q, two_q);
-          else gs_bfly(x[r][u], x[r][u + hd], wg, q, two_q);
-        }
+        for (int u = 2 * hd * g; u < 2 * hd * g + hd; ++u) gs_bfly(x[r][u], x[r][u + hd], wg, M);
     }
   }
 }
@@ -518,17 +467,11 @@ __device__ __forceinline__ void rows_fused_kernel_body(const RowsArgs& a, const 
   const int c = (rem / nwg) * CG;  // the group's first ciphertext
   const int sg = (rem % nwg) * RPW + sl;
   const bool valid = sg < nsub_total && c + cs < a.cnum;
-  const PrimeC pc = a.pc[p];
-  const uint32_t q = pc.q, two_q = pc.two_q, qneg = pc.qneg;
+  const Mod M(a.pc[p]);
+  const uint32_t q = M.q, two_q = M.two_q, qneg = M.qneg;
   const TwTab tw = tw_table(a.tw, p), itw = tw_table(a.itw, p);
   // one sub-row per wave when CG = 4: the strided stages' twiddle index is then uniform
   const int tw_mul = CG > 1 ? __builtin_amdgcn_readfirstlane(nsub_total + sg) : nsub_total + sg;
-  // The tensor and relinearization forms take their inverse twiddles from the forward
-  // table at the mirrored multiplier (mirror_tw; sg taken inside the transform on lanes
-  // past the last sub-row), so that a prime's inverse table is not read; the ring form
-  // reads the inverse table.
-  const int mi = 2 * nsub_total - min(sg, nsub_total - 1);
-  const int tw_mi = CG > 1 ? __builtin_amdgcn_readfirstlane(mi) : mi;
   const long long KN = (long long)a.K * N;
   // Rows are addressed through buffer resources from the workgroup's first row of
   // prime p (and its first ciphertext): a lane's 32-bit offset selects its sub-row and
@@ -554,9 +497,9 @@ __device__ __forceinline__ void rows_fused_kernel_body(const RowsArgs& a, const 
 #pragma unroll
       for (int u = 0; u < 16; ++u)
         x[r][u] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(lane + 4u * u * T), (int)(4 * r * KN), 0);
-    fwd_rows<S, 4, NB, HOIST>(x, lb, j, tw, tw_mul, q, two_q);
-    RowTw<S> wi;
-    if (HOIST) load_inv_tw<S, true>(wi, tw, tw_mi, j);  // in flight during the products
+    fwd_rows<S, 4, NB, HOIST>(x, lb, j, tw, tw_mul, M);
+    RowTw wi;
+    if (HOIST) load_row_tw<S>(wi, itw, tw_mul, j);  // in flight during the products
     // Montgomery products (Eq. ntt_mul) carry a factor 2^-32, compensated in the inverse
     // transform's final factor.  d1 is formed directly (the Karatsuba identity of
     // Section 5.4 gives the same value; with full-rate multiplies the direct form issues
@@ -572,7 +515,7 @@ __device__ __forceinline__ void rows_fused_kernel_body(const RowsArgs& a, const 
       d[2][u] = redc_lazy(mad64(x[1][u], x[3][u], 0), q, qneg);
     }
     slot_sync();  // every lane has read the forward exchange before it is overwritten
-    inv_rows<S, 3, NB, HOIST, true, (CG > 1)>(d, lb, j, tw, tw_mi, q, two_q, wi);
+    inv_rows<S, 3, NB, HOIST>(d, lb, j, itw, tw_mul, M, wi);
 #pragma unroll
     for (int r = 0; r < 3; ++r)
 #pragma unroll
@@ -592,9 +535,9 @@ __device__ __forceinline__ void rows_fused_kernel_body(const RowsArgs& a, const 
 #pragma unroll
     for (int u = 0; u < 16; ++u) x[0][u] = __builtin_amdgcn_raw_buffer_load_b32(ri, (int)(lane + 4u * u * T), 0, 0);
     uint32_t* const lf[1] = {lb[0]};
-    fwd_rows<S, 1, 1, HOIST>(x, lf, j, tw, tw_mul, q, two_q);
-    RowTw<S> wi;
-    if (HOIST) load_inv_tw<S, true>(wi, tw, tw_mi, j);
+    fwd_rows<S, 1, 1, HOIST>(x, lf, j, tw, tw_mul, M);
+    RowTw wi;
+    if (HOIST) load_row_tw<S>(wi, itw, tw_mul, j);
     // the key rows are stored transposed (launch_row_transpose): thread j's element
     // 16 j + u sits at u T + j, so that these loads are coalesced
     // all 32 key words issued together (left to the scheduler, they may be issued two
@@ -613,7 +556,7 @@ __device__ __forceinline__ void rows_fused_kernel_body(const RowsArgs& a, const 
     }
     slot_sync();  // every lane has read the forward exchange before it is overwritten
     uint32_t* const li[1] = {lb[0]};
-    inv_rows<S, 2, 1, HOIST, true, (CG > 1)>(k, li, j, tw, tw_mi, q, two_q, wi);
+    inv_rows<S, 2, 1, HOIST>(k, li, j, itw, tw_mul, M, wi);
 #pragma unroll
     for (int r = 0; r < 2; ++r)
 #pragma unroll
@@ -631,14 +574,14 @@ __device__ __forceinline__ void rows_fused_kernel_body(const RowsArgs& a, const 
       x[1][u] = __builtin_amdgcn_raw_buffer_load_b32(rb, (int)(lane + 4u * u * T), 0, 0);
     }
     uint32_t* const lf[2] = {lb[0], lb[1]};
-    fwd_rows<S, 2, 2>(x, lf, j, tw, tw_mul, q, two_q);
+    fwd_rows<S, 2, 2>(x, lf, j, tw, tw_mul, M);
     uint32_t y[1][16];
 #pragma unroll
     for (int u = 0; u < 16; ++u) y[0][u] = redc_lazy(mad64(x[0][u], x[1][u], 0), q, qneg);  // [0, 2q)
     slot_sync();  // the forward exchange's buffers are reused
     uint32_t* const li[1] = {lb[0]};
-    RowTw<S> wi;  // unused: this form loads its twiddles in place
-    inv_rows<S, 1, 1>(y, li, j, itw, tw_mul, q, two_q, wi);
+    RowTw wi;  // unused: this form loads its twiddles in place
+    inv_rows<S, 1, 1>(y, li, j, itw, tw_mul, M, wi);
 #pragma unroll
     for (int u = 0; u < 16; ++u) __builtin_amdgcn_raw_buffer_store_b32(y[0][u], ra, (int)(lane + 4u * u * T), 0, 0);
   }
@@ -719,9 +662,7 @@ static hipError_t ntt_pass(const NttArgs& a, int ntr, hipStream_t st) {
   // algorithmic HBM bytes: every element of every transform read and written once
   Bracket br(INV ? (ROWS ? KID_NTT_INV_ROWS : KID_NTT_INV_COLS) : (ROWS ? KID_NTT_FWD_ROWS : KID_NTT_FWD_COLS), st,
              8.0 * ntr * (double)(1 << a.logN));
-  const hipError_t e = emit((const void*)ntt_pass_kernel<S, INV, ROWS, BLK, CG>,
-                             (const void*)ntt_pass_kernel_multi<S, INV, ROWS, BLK, CG>, grid, dim3(BLK), 0, st, a);
-  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((ntt_pass_kernel<S, INV, ROWS, BLK, CG>), grid, dim3(BLK), 0, st, a);
   return hipGetLastError();
 }
 
@@ -762,15 +703,14 @@ hipError_t launch_row_transpose(const uint32_t* src, uint32_t* dst, long long to
 }
 
 __global__ __launch_bounds__(256) void scale_rows_kernel(uint32_t* data, long long total, int K, int logN,
-                                                        const uint2* scale, const PrimeC* pc) {
+                                                        const uint32_t* scale, const PrimeC* pc) {
   const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
   if (i >= total) return;
   const int p = (int)((i >> logN) % K);
-  const uint32_t q = pc[p].q;
-  data[i] = csub(shoup_lazy(data[i], scale[p].x, scale[p].y, q), q);
+  data[i] = csub(mont_s(data[i], scale[p], Mod(pc[p].q, pc[p].qneg)), pc[p].q);
 }
 
-hipError_t launch_scale_rows(uint32_t* data, long long rows, int K, int N, const uint2* scale, const PrimeC* pc,
+hipError_t launch_scale_rows(uint32_t* data, long long rows, int K, int N, const uint32_t* scale, const PrimeC* pc,
                              hipStream_t st) {
   const long long total = rows * N;
   if (total <= 0) return hipSuccess;

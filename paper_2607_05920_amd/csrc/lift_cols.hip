@@ -116,11 +116,10 @@ __device__ __forceinline__ void lift_cols_kernel_body(const LiftArgs& a, const B
   auto stages = [&](int s) {
     const int p = 16 * s + (int)wave;
     if (p >= a.K) return;
-    const PrimeC pc = a.pc[p];
     uint32_t x[16];
 #pragma unroll
     for (int u = 0; u < 16; ++u) x[u] = sx[s & 1][wave * XS + u * 64 + lane];
-    cols16_forward(x, tw_table(a.tw, p), pc.q, pc.two_q);
+    cols16_forward(x, tw_table(a.tw, p), Mod(a.pc[p]));
     const __amdgpu_buffer_rsrc_t ro = row_buffer(wave_uniform(out + (long long)p * a.N), row);
 #pragma unroll
     for (int u = 0; u < 16; ++u)
@@ -184,7 +183,7 @@ hipError_t launch_lift_cols(const LiftArgs& a, int npoly, hipStream_t st, const 
     n.group_stride = a.out_stride;
     n.tw = a.tw;
     n.pc = a.pc;
-    return e != hipSuccess ? e : launch_cols16(n, npoly * a.K, false, st);
+    return e != hipSuccess ? e : launch_cols16(n, npoly * a.K, st);
   }
   LiftArgs b = a;
   b.npoly = npoly;

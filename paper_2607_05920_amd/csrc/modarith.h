@@ -38,13 +38,6 @@ __device__ __forceinline__ uint64_t mad64(uint32_t a, uint32_t b, uint64_t c) {
   return (uint64_t)a * (uint64_t)b + c;
 }
 
-// Shoup multiplication by a constant w < q with wp = floor(w 2^32 / q):
-// for any a < 2^32 returns a w mod q in [0, 2q).
-__device__ __forceinline__ uint32_t shoup_lazy(uint32_t a, uint32_t w, uint32_t wp, uint32_t q) {
-  uint32_t qh = __umulhi(a, wp);
-  return a * w - qh * q;
-}
-
 // Montgomery reduction: for T < q 2^32 returns T 2^-32 mod q in [0, 2q).
 __device__ __forceinline__ uint32_t redc_lazy(uint64_t T, uint32_t q, uint32_t qneg) {
   uint32_t m = (uint32_t)T * qneg;

@@ -95,7 +95,7 @@ struct Whole {
   }
 
   template <int I>
-  static __device__ __forceinline__ void forward(uint32_t (&x)[R], TwTab tw, int t, uint32_t q, uint32_t two_q) {
+  static __device__ __forceinline__ void forward(uint32_t (&x)[R], TwTab tw, int t, const Mod& M) {
     constexpr int g_ = G(I);
 #pragma unroll
     for (int k = 0; k < R / g_; ++k) {
@@ -106,9 +106,12 @@ struct Whole {
         if (V == 6) __builtin_amdgcn_sched_barrier(0);  // later stages' twiddles loaded this early would spill
 #pragma unroll
         for (int g = 0; g < (1 << j); ++g) {
-          const uint2 w = tw[(b << j) + g];
+          const uint32_t w = tw[(b << j) + g];
 #pragma unroll
-          for (int u = 2 * h * g; u < 2 * h * g + h; ++u) ct_bfly(x[k * g_ + u], x[k * g_ + u + h], w, q, two_q);
+          for (int u = 2 * h * g; u < 2 * h * g + h; ++u) {
+            if (I == 0 && j == 0) ct_bfly<true>(x[k * g_ + u], x[k * g_ + u + h], w, M);
+            else ct_bfly(x[k * g_ + u], x[k * g_ + u + h], w, M);
+          }
         }
       }
     }
@@ -116,7 +119,7 @@ struct Whole {
 
   // FOLD: leave the last stage (one group over the whole transform) to the caller
   template <int I, bool FOLD>
-  static __device__ __forceinline__ void inverse(uint32_t (&x)[R], TwTab tw, int t, uint32_t q, uint32_t two_q) {
+  static __device__ __forceinline__ void inverse(uint32_t (&x)[R], TwTab tw, int t, const Mod& M) {
     constexpr int g_ = G(I);
 #pragma unroll
     for (int k = 0; k < R / g_; ++k) {
@@ -127,9 +130,9 @@ struct Whole {
         if (V == 6) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int g = 0; g < (1 << j); ++g) {
-          const uint2 w = tw[(b << j) + g];
+          const uint32_t w = tw[(b << j) + g];
 #pragma unroll
-          for (int u = 2 * h * g; u < 2 * h * g + h; ++u) gs_bfly(x[k * g_ + u], x[k * g_ + u + h], w, q, two_q);
+          for (int u = 2 * h * g; u < 2 * h * g + h; ++u) gs_bfly(x[k * g_ + u], x[k * g_ + u + h], w, M);
         }
       }
     }
@@ -203,21 +206,19 @@ struct Whole {
   }
 
   template <int I>
-  static __device__ __forceinline__ void forward_from(uint32_t (&x)[R], uint32_t* lds, TwTab tw, int t, uint32_t q,
-                                                      uint32_t two_q) {
-    forward<I>(x, tw, t, q, two_q);
+  static __device__ __forceinline__ void forward_from(uint32_t (&x)[R], uint32_t* lds, TwTab tw, int t, const Mod& M) {
+    forward<I>(x, tw, t, M);
     if constexpr (I + 1 < NPH) {
       exchange<I, I + 1>(x, lds, t);
-      forward_from<I + 1>(x, lds, tw, t, q, two_q);
+      forward_from<I + 1>(x, lds, tw, t, M);
     }
   }
   template <int I>
-  static __device__ __forceinline__ void inverse_from(uint32_t (&x)[R], uint32_t* lds, TwTab tw, int t, uint32_t q,
-                                                      uint32_t two_q) {
-    inverse<I, I == 0>(x, tw, t, q, two_q);
+  static __device__ __forceinline__ void inverse_from(uint32_t (&x)[R], uint32_t* lds, TwTab tw, int t, const Mod& M) {
+    inverse<I, I == 0>(x, tw, t, M);
     if constexpr (I > 0) {
       exchange<I, I - 1>(x, lds, t);
-      inverse_from<I - 1>(x, lds, tw, t, q, two_q);
+      inverse_from<I - 1>(x, lds, tw, t, M);
     }
   }
 };
@@ -240,29 +241,29 @@ __global__ __launch_bounds__((Whole<LG, V>::T)) void ntt_whole_kernel(NttArgs a)
   const int pk = a.per_group / a.K;  // polynomials per group
   const long long row = (long long)(jg / pk) * a.group_stride + ((long long)(jg % pk) * a.K + p) * (1 << LG);
   const __amdgpu_buffer_rsrc_t rb = row_buffer(wave_uniform(a.data + row), 4u << LG);
-  const PrimeC pc = a.pc[p];
-  const uint32_t q = pc.q, two_q = pc.two_q;
+  const Mod M(a.pc[p]);
+  const uint32_t q = M.q;
   const TwTab tw = tw_table(a.tw, p);
   uint32_t x[W::R];
   if (!INV) {
 #pragma unroll
     for (int r = 0; r < W::R; ++r) x[r] = __builtin_amdgcn_raw_buffer_load_b32(rb, 4 * t, 4 * r * W::T, 0);
-    W::template forward_from<0>(x, lds, tw, t, q, two_q);
+    W::template forward_from<0>(x, lds, tw, t, M);
 #pragma unroll
-    for (int r = 0; r < W::R; ++r) x[r] = csub(csub(x[r], two_q), q);
+    for (int r = 0; r < W::R; ++r) x[r] = csub(fwd_lift(x[r], M), q);
     if (NAT) W::template natural<true>(x, lds, rb, t);
     else W::template runs<true>(x, rb, t);
   } else {
     if (NAT) W::template natural<false>(x, lds, rb, t);
     else W::template runs<false>(x, rb, t);
-    W::template inverse_from<W::NPH - 1>(x, lds, tw, t, q, two_q);
+    W::template inverse_from<W::NPH - 1>(x, lds, tw, t, M);
     // the last stage with the final factor folded in, as in the two-pass form
-    const uint2 sc = a.scale[p], sw = a.scale_w[p];
+    const uint32_t sc = a.scale[p], sw = a.scale_w[p];
 #pragma unroll
     for (int u = 0; u < W::R / 2; ++u) {
       const uint32_t xs = x[u], ys = x[u + W::R / 2];
-      x[u] = csub(shoup_lazy(xs + ys, sc.x, sc.y, q), q);
-      x[u + W::R / 2] = csub(shoup_lazy(xs - ys + two_q, sw.x, sw.y, q), q);
+      x[u] = csub(mont_s(xs + ys + M.neg2q, sc, M), q);
+      x[u + W::R / 2] = csub(mont_s(xs - ys, sw, M), q);
     }
 #pragma unroll
     for (int r = 0; r < W::R; ++r) __builtin_amdgcn_raw_buffer_store_b32(x[r], rb, 4 * t, 4 * r * W::T, 0);

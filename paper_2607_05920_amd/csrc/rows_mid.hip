@@ -29,40 +29,27 @@ struct MidRow {
   }
 };
 
-// A phase's twiddles of one thread: the stage of c groups per thread has its c pairs at
-// [c - 1, 2 c - 1).
-struct Tw15 {
-  uint2 w[15];
+// A phase's twiddles of one thread: the stage of c groups per thread has its c entries at
+// [c, 2 c).
+struct Tw16 {
+  uint32_t w[16];
 };
 
 // Phase I's twiddles: the stage with c groups per thread starts at table index
 // mult c G + (thread's block) c, G the groups of the phase's first stage over the row.
-// MIR: minus the inverse ones, from the forward table read backwards (mirror_tw) at the
-// mirrored multiplier.
-template <int S, int I, bool MIR>
-__device__ __forceinline__ void load_phase_tw(Tw15& w, TwTab tw, int mult, int t) {
+template <int S, int I>
+__device__ __forceinline__ void load_phase_tw(Tw16& w, TwTab tw, int mult, int t) {
   typedef MidRow<S> M;
   constexpr int G = I == 0 ? 1 : (I == 1 ? 16 : M::T);
-  const int blk = I == 0 ? 0 : (I == 1 ? t / M::C : t);
-#pragma unroll
-  for (int c = I == 2 ? M::C2 : 1; c <= 8; c *= 2) {
-    const int b = MIR ? mult * c * G - (blk + 1) * c : mult * c * G + blk * c;
-    if (I == 0 || c == 1) {  // wave-uniform (scalar loads), or a single entry
-#pragma unroll
-      for (int g = 0; g < c; ++g) w.w[c - 1 + (MIR ? c - 1 - g : g)] = tw[b + g];
-    } else {
-#pragma unroll
-      for (int g = 0; g < c; g += 2) {
-        const v4i_t v = tw.pair(b + g);
-        w.w[c - 1 + (MIR ? c - 1 - g : g)] = make_uint2((uint32_t)v[0], (uint32_t)v[1]);
-        w.w[c - 1 + (MIR ? c - 2 - g : g + 1)] = make_uint2((uint32_t)v[2], (uint32_t)v[3]);
-      }
-    }
-  }
+  const int b = mult * G + (I == 0 ? 0 : (I == 1 ? t / M::C : t));
+  if (I < 2 || M::C2 <= 1) tw.run<1>(b, w.w + 1);
+  if (I < 2 || M::C2 <= 2) tw.run<2>(2 * b, w.w + 2);
+  if (I < 2 || M::C2 <= 4) tw.run<4>(4 * b, w.w + 4);
+  tw.run<8>(8 * b, w.w + 8);
 }
 
 template <int S, int I, int NP>
-__device__ __forceinline__ void fwd_phase(uint32_t (&x)[NP][16], const Tw15& w, uint32_t q, uint32_t two_q) {
+__device__ __forceinline__ void fwd_phase(uint32_t (&x)[NP][16], const Tw16& w, const Mod& M) {
 #pragma unroll
   for (int c = I == 2 ? MidRow<S>::C2 : 1; c <= 8; c *= 2) {
     const int h = 8 / c;
@@ -71,26 +58,21 @@ __device__ __forceinline__ void fwd_phase(uint32_t (&x)[NP][16], const Tw15& w, 
 #pragma unroll
       for (int r = 0; r < NP; ++r)
 #pragma unroll
-        for (int u = 2 * h * g; u < 2 * h * g + h; ++u) ct_bfly(x[r][u], x[r][u + h], w.w[c - 1 + g], q, two_q);
+        for (int u = 2 * h * g; u < 2 * h * g + h; ++u) ct_bfly(x[r][u], x[r][u + h], w.w[c + g], M);
   }
 }
 
 template <int S, int I, int NP>
-__device__ __forceinline__ void inv_phase(uint32_t (&x)[NP][16], const Tw15& w, uint32_t q, uint32_t two_q) {
+__device__ __forceinline__ void inv_phase(uint32_t (&x)[NP][16], const Tw16& w, const Mod& M) {
 #pragma unroll
   for (int c = 8; c >= (I == 2 ? MidRow<S>::C2 : 1); c /= 2) {
     const int h = 8 / c;
 #pragma unroll
-    for (int g = 0; g < c; ++g) {
-      const uint2 f = w.w[c - 1 + g];
-      const uint2 v = I == 0 && MidRow<S>::T >= 64
-                          ? mirror_tw_s(make_uint2(__builtin_amdgcn_readfirstlane(f.x), __builtin_amdgcn_readfirstlane(f.y)))
-                          : mirror_tw(f);
+    for (int g = 0; g < c; ++g)
 #pragma unroll
       for (int r = 0; r < NP; ++r)
 #pragma unroll
-        for (int u = 2 * h * g; u < 2 * h * g + h; ++u) gs_bfly_neg(x[r][u], x[r][u + h], v, q, two_q);
-    }
+        for (int u = 2 * h * g; u < 2 * h * g + h; ++u) gs_bfly(x[r][u], x[r][u + h], w.w[c + g], M);
   }
 }
 
@@ -120,53 +102,49 @@ __device__ __forceinline__ void mid_exchange(uint32_t (&x)[NP][16], uint32_t* co
   }
 }
 
-// All row stages of NP forward transforms: values in [0, 4q) at elements u T + t, left in
+// All row stages of NP forward transforms: values in [-2q, 2q) at elements u T + t, left in
 // [0, 2q) at 16 t + u.  A phase's twiddles are issued before the exchange that precedes it.
 template <int S, int NP, int NB>
 __device__ __forceinline__ void mid_forward(uint32_t (&x)[NP][16], uint32_t* const (&l)[NB], int t, TwTab tw, int mult,
-                                            uint32_t q, uint32_t two_q) {
-  Tw15 w0, w1, w2;
-  load_phase_tw<S, 0, false>(w0, tw, mult, t);
-  load_phase_tw<S, 1, false>(w1, tw, mult, t);
+                                            const Mod& M) {
+  Tw16 w0, w1, w2;
+  load_phase_tw<S, 0>(w0, tw, mult, t);
+  load_phase_tw<S, 1>(w1, tw, mult, t);
   __builtin_amdgcn_sched_barrier(0);
-  fwd_phase<S, 0, NP>(x, w0, q, two_q);
+  fwd_phase<S, 0, NP>(x, w0, M);
   mid_exchange<S, 0, 1, NP, NB>(x, l, t);
-  fwd_phase<S, 1, NP>(x, w1, q, two_q);
-  __builtin_amdgcn_sched_barrier(0);  // the registers do not hold two phases' twiddles
-  load_phase_tw<S, 2, false>(w2, tw, mult, t);
+  load_phase_tw<S, 2>(w2, tw, mult, t);
   __builtin_amdgcn_sched_barrier(0);
+  fwd_phase<S, 1, NP>(x, w1, M);
   mid_exchange<S, 1, 2, NP, NB>(x, l, t);
-  fwd_phase<S, 2, NP>(x, w2, q, two_q);
+  fwd_phase<S, 2, NP>(x, w2, M);
 #pragma unroll
   for (int r = 0; r < NP; ++r)
 #pragma unroll
-    for (int u = 0; u < 16; ++u) x[r][u] = csub(x[r][u], two_q);
+    for (int u = 0; u < 16; ++u) x[r][u] = fwd_lift(x[r][u], M);
 }
 
 // The row stages of NP inverse transforms, values in [0, 2q) from 16 t + u to u T + t; w2
 // holds phase 2's twiddles (loaded before the products).
 template <int S, int NP, int NB>
-__device__ __forceinline__ void mid_inverse(uint32_t (&x)[NP][16], uint32_t* const (&l)[NB], int t, TwTab tw,
-                                            int mirror, uint32_t q, uint32_t two_q, const Tw15& w2) {
-  Tw15 w0, w1;
-  inv_phase<S, 2, NP>(x, w2, q, two_q);
+__device__ __forceinline__ void mid_inverse(uint32_t (&x)[NP][16], uint32_t* const (&l)[NB], int t, TwTab itw, int mult,
+                                            const Mod& M, const Tw16& w2) {
+  Tw16 w0, w1;
+  inv_phase<S, 2, NP>(x, w2, M);
   __builtin_amdgcn_sched_barrier(0);
-  load_phase_tw<S, 1, true>(w1, tw, mirror, t);
+  load_phase_tw<S, 1>(w1, itw, mult, t);
   __builtin_amdgcn_sched_barrier(0);
   mid_exchange<S, 2, 1, NP, NB>(x, l, t);
-  load_phase_tw<S, 0, true>(w0, tw, mirror, t);
-  inv_phase<S, 1, NP>(x, w1, q, two_q);
+  load_phase_tw<S, 0>(w0, itw, mult, t);
+  inv_phase<S, 1, NP>(x, w1, M);
   mid_exchange<S, 1, 0, NP, NB>(x, l, t);
-  inv_phase<S, 0, NP>(x, w0, q, two_q);
+  inv_phase<S, 0, NP>(x, w0, M);
 }
 
-// CG ciphertexts per row of the relinearization form: they share the row's twiddles and
-// key words.
-template <int S, int MODE, int CG>
+template <int S, int MODE>
 __device__ __forceinline__ void rows_mid_kernel_body(const RowsArgs& a, const Blk bk) {
   typedef MidRow<S> M;
-  constexpr int n = M::n, T = M::T, RPW = M::RPW, NB = MODE == ROWS_RELIN && CG == 1 ? 1 : 2;
-  static_assert(CG == 1 || MODE == ROWS_RELIN, "only the relinearization form groups ciphertexts");
+  constexpr int n = M::n, T = M::T, RPW = M::RPW, NB = MODE == ROWS_RELIN ? 1 : 2;
   __shared__ uint32_t lds[NB][RPW * M::LDS_ROW];
   const int s = threadIdx.x / T, t = threadIdx.x % T;
   const int N = 1 << a.logN;
@@ -174,18 +152,17 @@ __device__ __forceinline__ void rows_mid_kernel_body(const RowsArgs& a, const Bl
   // Workgroup w runs on XCD w % 8.  The rows, ordered by prime, are cut into eight runs of
   // equal length, one per XCD: a prime's table and key rows are read into one L2, and the
   // XCDs finish together whatever K is.
-  const int ncg = (a.cnum + CG - 1) / CG;
-  const int per_prime = ncg * (ROWS / RPW), total = a.K * per_prime, chunk = (total + 7) / 8;
+  const int per_prime = a.cnum * (ROWS / RPW), total = a.K * per_prime, chunk = (total + 7) / 8;
   const int li = bk.x >> 3, item = (bk.x & 7) * chunk + li;
   if (li >= chunk || item >= total) return;  // whole workgroup exits
   const int p = item / per_prime, rem = item % per_prime;
-  // consecutive items: the groups of ciphertexts of one row, which share its twiddles
-  const int c = (rem % ncg) * CG, row0 = (rem / ncg) * RPW;
-  const PrimeC pc = a.pc[p];
-  const uint32_t q = pc.q, two_q = pc.two_q, qneg = pc.qneg;
-  const TwTab tw = tw_table(a.tw, p);
+  // consecutive items: the ciphertexts of one row, which share its twiddles
+  const int c = rem % a.cnum, row0 = (rem / a.cnum) * RPW;
+  const Mod Q(a.pc[p]);
+  const uint32_t q = Q.q, two_q = Q.two_q, qneg = Q.qneg;
+  const TwTab tw = tw_table(a.tw, p), itw = tw_table(a.itw, p);
   const int sg = T >= 64 ? __builtin_amdgcn_readfirstlane(row0 + s) : row0 + s;
-  const int mult = ROWS + sg, mirror = 2 * ROWS - sg;
+  const int mult = ROWS + sg;
   const long long KN = (long long)a.K * N;
   const long long base = (long long)p * N + (long long)row0 * n;
   const uint32_t lane = 4u * (uint32_t)(s * n + t);
@@ -202,10 +179,10 @@ __device__ __forceinline__ void rows_mid_kernel_body(const RowsArgs& a, const Bl
     for (int r = 0; r < 4; ++r)
 #pragma unroll
       for (int u = 0; u < 16; ++u)
-        x[r][u] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(lane + 4u * u * T), (int)(4 * r * KN), 0);
-    mid_forward<S, 4, NB>(x, lb, t, tw, mult, q, two_q);
-    Tw15 w2;
-    load_phase_tw<S, 2, true>(w2, tw, mirror, t);  // in flight during the products
+        x[r][u] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)lane, (int)(4 * (r * KN + u * T)), 0);
+    mid_forward<S, 4, NB>(x, lb, t, tw, mult, Q);
+    Tw16 w2;
+    load_phase_tw<S, 2>(w2, itw, mult, t);  // in flight during the products
     __builtin_amdgcn_sched_barrier(0);
     // products as in rows_fused_kernel: inputs and outputs in [0, 2q)
     uint32_t d[3][16];
@@ -215,57 +192,44 @@ __device__ __forceinline__ void rows_mid_kernel_body(const RowsArgs& a, const Bl
       d[1][u] = csub(redc_lazy(mad64(x[0][u], x[3][u], mad64(x[1][u], x[2][u], 0)), q, qneg), two_q);
       d[2][u] = redc_lazy(mad64(x[1][u], x[3][u], 0), q, qneg);
     }
-    mid_inverse<S, 3, NB>(d, lb, t, tw, mirror, q, two_q, w2);
+    mid_inverse<S, 3, NB>(d, lb, t, itw, mult, Q, w2);
 #pragma unroll
     for (int r = 0; r < 3; ++r)
 #pragma unroll
       for (int u = 0; u < 16; ++u)
-        __builtin_amdgcn_raw_buffer_store_b32(d[r][u], rs, (int)(lane + 4u * u * T), (int)(4 * r * KN), 0);
+        __builtin_amdgcn_raw_buffer_store_b32(d[r][u], rs, (int)lane, (int)(4 * (r * KN + u * T)), 0);
   } else if constexpr (MODE == ROWS_RELIN) {  // d2 rows times the key's two rows, to out
     const uint32_t bytes = (uint32_t)(KN * 4) + row_bytes;
     const __amdgpu_buffer_rsrc_t rk = row_buffer(wave_uniform(a.key + base), bytes);
-    uint32_t x[CG][16], k[2 * CG][16];
+    const __amdgpu_buffer_rsrc_t ri =
+        row_buffer(wave_uniform(a.data + (long long)c * a.group_stride + base), row_bytes);
+    uint32_t x[1][16], k[2][16];
 #pragma unroll
-    for (int g = 0; g < CG; ++g) {
-      // a ciphertext past the last reads zeros and stores nothing (an empty buffer)
-      const bool in = c + g < a.cnum;
-      const __amdgpu_buffer_rsrc_t ri = row_buffer(
-          wave_uniform(a.data + (in ? (long long)(c + g) * a.group_stride + base : 0)), in ? row_bytes : 0);
-#pragma unroll
-      for (int u = 0; u < 16; ++u) x[g][u] = __builtin_amdgcn_raw_buffer_load_b32(ri, (int)(lane + 4u * u * T), 0, 0);
-    }
-    mid_forward<S, CG, NB>(x, lb, t, tw, mult, q, two_q);
+    for (int u = 0; u < 16; ++u) x[0][u] = __builtin_amdgcn_raw_buffer_load_b32(ri, (int)lane, 4 * u * T, 0);
+    mid_forward<S, 1, NB>(x, lb, t, tw, mult, Q);
     // the key's rows are stored so that thread t's element 16 t + u sits at u T + t; all 32
     // words are issued together
-    uint32_t kw[2][16];
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
-      kw[0][u] = __builtin_amdgcn_raw_buffer_load_b32(rk, (int)(lane + 4u * u * T), 0, 0);
-      kw[1][u] = __builtin_amdgcn_raw_buffer_load_b32(rk, (int)(lane + 4u * u * T), (int)(4 * KN), 0);
+      k[0][u] = __builtin_amdgcn_raw_buffer_load_b32(rk, (int)lane, 4 * u * T, 0);
+      k[1][u] = __builtin_amdgcn_raw_buffer_load_b32(rk, (int)lane, (int)(4 * (KN + u * T)), 0);
     }
+    Tw16 w2;
+    load_phase_tw<S, 2>(w2, itw, mult, t);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < 16; ++u)
-#pragma unroll
-      for (int g = CG - 1; g >= 0; --g) {
-        // x in [0, 2q), key canonical: results in [0, 2q)
-        k[2 * g][u] = redc_lazy(mad64(x[g][u], kw[0][u], 0), q, qneg);
-        k[2 * g + 1][u] = redc_lazy(mad64(x[g][u], kw[1][u], 0), q, qneg);
-      }
-    Tw15 w2;
-    load_phase_tw<S, 2, true>(w2, tw, mirror, t);
-    mid_inverse<S, 2 * CG, NB>(k, lb, t, tw, mirror, q, two_q, w2);
-#pragma unroll
-    for (int g = 0; g < CG; ++g) {
-      const bool in = c + g < a.cnum;
-      const __amdgpu_buffer_rsrc_t ro =
-          row_buffer(wave_uniform(a.out + (in ? (long long)(c + g) * a.out_stride + base : 0)), in ? bytes : 0);
-#pragma unroll
-      for (int r = 0; r < 2; ++r)
-#pragma unroll
-        for (int u = 0; u < 16; ++u)
-          __builtin_amdgcn_raw_buffer_store_b32(k[2 * g + r][u], ro, (int)(lane + 4u * u * T), (int)(4 * r * KN), 0);
+    for (int u = 0; u < 16; ++u) {
+      // x in [0, 2q), key canonical: results in [0, 2q)
+      k[0][u] = redc_lazy(mad64(x[0][u], k[0][u], 0), q, qneg);
+      k[1][u] = redc_lazy(mad64(x[0][u], k[1][u], 0), q, qneg);
     }
+    mid_inverse<S, 2, NB>(k, lb, t, itw, mult, Q, w2);
+    const __amdgpu_buffer_rsrc_t ro = row_buffer(wave_uniform(a.out + (long long)c * a.out_stride + base), bytes);
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+        __builtin_amdgcn_raw_buffer_store_b32(k[r][u], ro, (int)lane, (int)(4 * (r * KN + u * T)), 0);
   } else {  // ring: a times b, in place of a
     const __amdgpu_buffer_rsrc_t ra =
         row_buffer(wave_uniform(a.data + (long long)c * a.group_stride + base), row_bytes);
@@ -274,48 +238,56 @@ __device__ __forceinline__ void rows_mid_kernel_body(const RowsArgs& a, const Bl
     uint32_t x[2][16];
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
-      x[0][u] = __builtin_amdgcn_raw_buffer_load_b32(ra, (int)(lane + 4u * u * T), 0, 0);
-      x[1][u] = __builtin_amdgcn_raw_buffer_load_b32(rb, (int)(lane + 4u * u * T), 0, 0);
+      x[0][u] = __builtin_amdgcn_raw_buffer_load_b32(ra, (int)lane, 4 * u * T, 0);
+      x[1][u] = __builtin_amdgcn_raw_buffer_load_b32(rb, (int)lane, 4 * u * T, 0);
     }
-    mid_forward<S, 2, NB>(x, lb, t, tw, mult, q, two_q);
-    Tw15 w2;
-    load_phase_tw<S, 2, true>(w2, tw, mirror, t);
+    mid_forward<S, 2, NB>(x, lb, t, tw, mult, Q);
+    Tw16 w2;
+    load_phase_tw<S, 2>(w2, itw, mult, t);
     __builtin_amdgcn_sched_barrier(0);
     uint32_t y[1][16];
 #pragma unroll
     for (int u = 0; u < 16; ++u) y[0][u] = redc_lazy(mad64(x[0][u], x[1][u], 0), q, qneg);  // [0, 2q)
-    mid_inverse<S, 1, NB>(y, lb, t, tw, mirror, q, two_q, w2);
+    mid_inverse<S, 1, NB>(y, lb, t, itw, mult, Q, w2);
 #pragma unroll
-    for (int u = 0; u < 16; ++u) __builtin_amdgcn_raw_buffer_store_b32(y[0][u], ra, (int)(lane + 4u * u * T), 0, 0);
+    for (int u = 0; u < 16; ++u) __builtin_amdgcn_raw_buffer_store_b32(y[0][u], ra, (int)lane, 4 * u * T, 0);
   }
 }
 
-template <int S, int MODE, int CG>
-__global__ __launch_bounds__(MidRow<S>::THREADS) __attribute__((amdgpu_waves_per_eu(3))) void rows_mid_kernel(
+// What bounds it: VALU issue.  2^16 points, 106 primes, 4 ciphertexts (tensor): 5 000 VALU
+// instructions per wave, 40% of them 32-bit products at 4 clocks, adds at 2.4: 237 us of
+// issue of the 323 us that a launch takes.  The tensor and ring forms are held to 128
+// registers (4 waves per SIMD; 3 took 8% longer), the relinearization form to 96 (5).  Two
+// ciphertexts per workgroup, sharing the row's key words and twiddles, needed 168 registers
+// in that form and took 5% longer.
+constexpr int mid_waves(int mode) { return mode == ROWS_RELIN ? 5 : 4; }
+
+template <int S, int MODE>
+__global__ __launch_bounds__(MidRow<S>::THREADS) __attribute__((amdgpu_waves_per_eu(mid_waves(MODE)))) void rows_mid_kernel(
     RowsArgs a) {
-  rows_mid_kernel_body<S, MODE, CG>(a, own_blk());
+  rows_mid_kernel_body<S, MODE>(a, own_blk());
 }
 
 // The same over the cells of a stage-batched plan: one launch, each workgroup in its
 // cell's segment (cell_of) with that cell's arguments.
-template <int S, int MODE, int CG>
-__global__ __launch_bounds__(MidRow<S>::THREADS) __attribute__((amdgpu_waves_per_eu(3))) void rows_mid_kernel_multi(
+template <int S, int MODE>
+__global__ __launch_bounds__(MidRow<S>::THREADS) __attribute__((amdgpu_waves_per_eu(mid_waves(MODE)))) void rows_mid_kernel_multi(
     const RowsArgs* __restrict__ cells, const CellSeg* __restrict__ seg, int ncells) {
   Blk bk;
   const int c = cell_of(seg, ncells, bk);
   if (c < 0) return;
-  rows_mid_kernel_body<S, MODE, CG>(cells[c], bk);
+  rows_mid_kernel_body<S, MODE>(cells[c], bk);
 }
 
-template <int S, int MODE, int CG>
+template <int S, int MODE>
 static hipError_t rows_mid(const RowsArgs& a, hipStream_t st) {
-  const int total = a.K * ((a.cnum + CG - 1) / CG) * (16 / MidRow<S>::RPW);
+  const int total = a.K * a.cnum * (16 / MidRow<S>::RPW);
   // algorithmic HBM bytes per prime, as in the fused pass of kernels.hip
   const int b_rows = a.data2_stride ? std::min(a.data2_groups, a.cnum) : 1;
   const double rows = MODE == ROWS_TENSOR ? 7.0 * a.cnum
                                           : (MODE == ROWS_RELIN ? 3.0 * a.cnum + 2.0 : 2.0 * a.cnum + b_rows);
   Bracket br(KID_ROWS_FUSED, st, 4.0 * rows * a.K * (double)(1 << a.logN));
-  const hipError_t e = emit((const void*)rows_mid_kernel<S, MODE, CG>, (const void*)rows_mid_kernel_multi<S, MODE, CG>,
+  const hipError_t e = emit((const void*)rows_mid_kernel<S, MODE>, (const void*)rows_mid_kernel_multi<S, MODE>,
                             dim3(8 * ((total + 7) / 8)), dim3(MidRow<S>::THREADS), 0, st, a);
   return e != hipSuccess ? e : hipGetLastError();
 }
@@ -323,9 +295,9 @@ static hipError_t rows_mid(const RowsArgs& a, hipStream_t st) {
 template <int S>
 static hipError_t rows_mid_mode(const RowsArgs& a, int mode, hipStream_t st) {
   switch (mode) {
-    case ROWS_TENSOR: return rows_mid<S, ROWS_TENSOR, 1>(a, st);
-    case ROWS_RELIN: return a.cnum > 1 ? rows_mid<S, ROWS_RELIN, 2>(a, st) : rows_mid<S, ROWS_RELIN, 1>(a, st);
-    case ROWS_RING: return rows_mid<S, ROWS_RING, 1>(a, st);
+    case ROWS_TENSOR: return rows_mid<S, ROWS_TENSOR>(a, st);
+    case ROWS_RELIN: return rows_mid<S, ROWS_RELIN>(a, st);
+    case ROWS_RING: return rows_mid<S, ROWS_RING>(a, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -343,10 +315,8 @@ hipError_t launch_rows_mid(const RowsArgs& a, int mode, hipStream_t st) {
   }
 }
 
-// The four outer stages on their own, where the lift or the reconstruction cannot take
-// them: a thread holds one column {c + (N / 16) u} of a transform; forward values in
-// [0, 4q) out, inverse ones canonical, times the final factor if there is one.
-template <bool INV>
+// The first four stages on their own, after a lift that cannot take them: a thread holds one
+// column {c + (N / 16) u} of a transform; residues in [0, 2q) in, [-2q, 2q) out.
 __device__ __forceinline__ void cols16_kernel_body(const NttArgs& a, const Blk bk) {
   const int cols = 1 << (a.logN - 4);  // at least 64: a wave's columns are one transform's
   const long long w = (long long)bk.x * 256 + threadIdx.x;
@@ -356,45 +326,34 @@ __device__ __forceinline__ void cols16_kernel_body(const NttArgs& a, const Blk b
   const uint32_t c4 = 4u * (uint32_t)(w & (cols - 1));
   const __amdgpu_buffer_rsrc_t rb = row_buffer(
       wave_uniform(a.data + (long long)g * a.group_stride + ((long long)r << a.logN)), 4u << a.logN);
-  const PrimeC pc = a.pc[p];
-  const uint32_t q = pc.q, two_q = pc.two_q;
-  const TwTab tw = tw_table(a.tw, p);
   uint32_t x[16];
 #pragma unroll
   for (int u = 0; u < 16; ++u) x[u] = __builtin_amdgcn_raw_buffer_load_b32(rb, (int)c4, 4 * u * cols, 0);
-  if (!INV) cols16_forward(x, tw, q, two_q);
-  else if (a.scale) cols16_inverse<true>(x, tw, a.scale[p], a.scale_w[p], q, two_q);
-  else cols16_inverse<false>(x, tw, make_uint2(0, 0), make_uint2(0, 0), q, two_q);
+  cols16_forward(x, tw_table(a.tw, p), Mod(a.pc[p]));
 #pragma unroll
   for (int u = 0; u < 16; ++u) __builtin_amdgcn_raw_buffer_store_b32(x[u], rb, (int)c4, 4 * u * cols, 0);
 }
 
-template <bool INV>
-__global__ __launch_bounds__(256) void cols16_kernel(NttArgs a) {
-  cols16_kernel_body<INV>(a, own_blk());
-}
-template <bool INV>
+__global__ __launch_bounds__(256) void cols16_kernel(NttArgs a) { cols16_kernel_body(a, own_blk()); }
+
 __global__ __launch_bounds__(256) void cols16_kernel_multi(const NttArgs* __restrict__ cells,
                                                            const CellSeg* __restrict__ seg, int ncells) {
   Blk bk;
   const int c = cell_of(seg, ncells, bk);
   if (c < 0) return;
-  cols16_kernel_body<INV>(cells[c], bk);
+  cols16_kernel_body(cells[c], bk);
 }
 
-hipError_t launch_cols16(const NttArgs& a0, int ntr, bool inverse, hipStream_t st) {
+hipError_t launch_cols16(const NttArgs& a0, int ntr, hipStream_t st) {
   if (ntr <= 0) return hipSuccess;
   if (ntr % a0.K != 0 || a0.per_group % a0.K != 0 || a0.logN < 10) return hipErrorInvalidValue;
   NttArgs a = a0;
   a.ntr = ntr;
   const long long threads = (long long)ntr << (a.logN - 4);
   // algorithmic HBM bytes: every element of every transform read and written once
-  Bracket br(inverse ? KID_NTT_INV_COLS : KID_NTT_FWD_COLS, st, 8.0 * ntr * (double)(1 << a.logN));
-  const hipError_t e =
-      inverse ? emit((const void*)cols16_kernel<true>, (const void*)cols16_kernel_multi<true>,
-                     dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, a)
-              : emit((const void*)cols16_kernel<false>, (const void*)cols16_kernel_multi<false>,
-                     dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, a);
+  Bracket br(KID_NTT_FWD_COLS, st, 8.0 * ntr * (double)(1 << a.logN));
+  const hipError_t e = emit((const void*)cols16_kernel, (const void*)cols16_kernel_multi,
+                            dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, a);
   return e != hipSuccess ? e : hipGetLastError();
 }
 

@@ -5,8 +5,10 @@ import numpy as np
 import pytest
 
 import paper_2607_05920_amd as fhe
+import synth
 from oracle import ntt as ontt
-from tests.gpu_helpers import check, dev, host, say
+from oracle import ring
+from tests.gpu_helpers import check, dev, host, ints, limbs_of, say
 
 pytestmark = pytest.mark.gpu
 
@@ -48,3 +50,25 @@ def test_ntt_whole(ctx, logN, nprimes, count, natural):
             assert np.array_equal(host(one, data[c].shape), fwd[c]), f"polynomial {c}"
     ctx.ntt(logN, nprimes, t, count=count, inverse=True, bitrev=not natural, prime0=prime0)
     assert np.array_equal(host(t, data.shape), data)
+
+
+# (logN, logq, cnum): one limb (one k-block of the lift, primes far below a step of 16 and a
+# block of 32); prime counts on both sides of a block (31 and 33 primes at logN 10); the
+# lift's largest fused limb count and the first that takes the separate stages; every row
+# length of the middle pass, with uneven ciphertext counts
+@pytest.mark.parametrize("logN,logq,cnum", [
+    (10, 20, 1), (10, 430, 3), (10, 470, 1), (10, 1792, 1), (10, 1793, 2), (11, 256, 2), (12, 257, 1), (13, 100, 3),
+    (14, 64, 2), (15, 33, 1), (16, 40, 1)])
+def test_ring_mul_fused(ctx, logN, logq, cnum):
+    say(f"ring_mul fused logN={logN} logq={logq} cnum={cnum}")
+    N, L = 1 << logN, synth.nlimbs(logq)
+    rng = np.random.default_rng(7 * logN + logq)
+    a, b = (synth.uniform_limbs(rng, logq, N, count=cnum) for _ in range(2))
+    top = limbs_of([(1 << logq) - 1], logq)[:, 0]
+    a[0, :, :] = top[:, None]  # every coefficient at its largest: the products' largest value
+    b[0, :, :] = top[:, None]
+    out = dev(np.zeros((cnum, L, N), dtype=np.uint32))
+    ctx.ring_mul(logN, logq, dev(a), dev(b), out, cnum=cnum)
+    got = host(out, (cnum, L, N))
+    for c in range(cnum):
+        check(ints(got[c]), ring.ring_mul(ints(a[c]), ints(b[c]), 1 << logq), f"ring_mul {c}")
