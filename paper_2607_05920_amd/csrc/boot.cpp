@@ -267,7 +267,8 @@ class Boot {
     {
       const size_t inw = (size_t)((P_.logq_in + 31) / 32) << P_.logN;
       hipStream_t s = (hipStream_t)st_;
-      hipError_t e = hipMemsetAsync(x.buf, 0, 2 * half_ * 4, s);
+      hipError_t e = hipMemsetAsync(x.ct.c0, 0, half_ * 4, s);
+      if (e == hipSuccess) e = hipMemsetAsync(x.ct.c1, 0, half_ * 4, s);
       if (e == hipSuccess) e = hipMemcpyAsync(x.ct.c0, in->c0, inw * 4, hipMemcpyDeviceToDevice, s);
       if (e == hipSuccess) e = hipMemcpyAsync(x.ct.c1, in->c1, inw * 4, hipMemcpyDeviceToDevice, s);
       if (e != hipSuccess) return FHE_E_DEVICE;

@@ -72,3 +72,38 @@ def test_ring_mul_fused(ctx, logN, logq, cnum):
     got = host(out, (cnum, L, N))
     for c in range(cnum):
         check(ints(got[c]), ring.ring_mul(ints(a[c]), ints(b[c]), 1 << logq), f"ring_mul {c}")
+
+
+def test_bootstrap_same_on_used_memory():
+    """The modulus raise clears the limbs above the input's in both components: repeated
+    bootstraps, whose buffers hold what earlier work left there, give the same output."""
+    import torch
+    logN, logq_in, logQ, logc, degree = 10, 40, 840, 40, 11
+    N, L = 1 << logN, synth.nlimbs(logQ)
+    say("bootstrap on used memory")
+    rng = np.random.default_rng(3)
+    c = fhe.Context(logQ, logQ)
+
+    def key(g=0):
+        return fhe.EvalKey(c, fhe.CKKS, 0, logN, logQ, logQ, synth.uniform_limbs(rng, 2 * logQ, N),
+                           synth.uniform_limbs(rng, 2 * logQ, N), g=g)
+
+    relin, conj = key(), key(2 * N - 1)
+    rot = {r: key(pow(5, r, 2 * N)) for r in [1, 2, 3] + [1 << i for i in range(2, logN - 1)]}
+    diag = [dev(synth.uniform_limbs(rng, logQ, N, count=4)).reshape(-1) for _ in range(2)]
+    taylor = [int(v) for v in rng.integers(1, 1 << 39, size=degree + 1)]
+    params = dict(logN=logN, logslots=2, logq_in=logq_in, logQ=logQ, logc=logc, logT=8, degree=degree)
+    x = fhe.Ciphertext(*(dev(synth.uniform_limbs(rng, logq_in, N)).reshape(-1) for _ in range(2)), logN, logq_in, 30,
+                       fhe.CKKS, 0, 1, 1)
+    first = None
+    try:
+        for _ in range(3):
+            out = [torch.zeros(L * N, dtype=torch.int32, device="cuda") for _ in range(2)]
+            o = c.ct_bootstrap(params, relin, rot, conj, *diag, 1 << 42, taylor, x, out)
+            got = [host(v, -1)[:synth.nlimbs(o.logq) * N].copy() for v in out]
+            first = first or got
+            assert all(np.array_equal(a, b) for a, b in zip(got, first))
+    finally:
+        for k in [relin, conj, *rot.values()]:
+            k.close()
+        c.close()
