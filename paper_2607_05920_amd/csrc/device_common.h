@@ -47,6 +47,24 @@ __device__ __forceinline__ uint32_t buffer_word(__amdgpu_buffer_rsrc_t r, uint32
   return __builtin_amdgcn_raw_buffer_load_b32(r, (int)byte_off, 0, 0);
 }
 
+// Limb rows of one coefficient per lane.  The limb-serial kernels read their rows a block of
+// kLimbBlock at a time: all of a block's loads are in flight together, where a load per limb
+// inside the carry chain waited for memory limb by limb (2^14 coefficients, 32 limbs, a sum:
+// 9.6 us a launch; with blocks 5.4).  Rows at or beyond the buffer's end read as zero.
+constexpr int kLimbBlock = 16;
+struct LimbRows {
+  __amdgpu_buffer_rsrc_t r;
+  uint32_t lane, row;  // byte offset of the lane's coefficient, bytes between rows
+  // rows l < `rows` of the polynomial at the wave-uniform `base`, N coefficients a row
+  __device__ __forceinline__ LimbRows(const uint32_t* base, int rows, int N, uint32_t coeff)
+      : r(row_buffer(wave_uniform(base), 4u * (uint32_t)rows * (uint32_t)N)), lane(4u * coeff), row(4u * (uint32_t)N) {}
+  __device__ __forceinline__ uint32_t operator[](int l) const { return buffer_word(r, lane + (uint32_t)l * row); }
+  __device__ __forceinline__ void block(uint32_t (&v)[kLimbBlock], int l0) const {
+#pragma unroll
+    for (int i = 0; i < kLimbBlock; ++i) v[i] = (*this)[l0 + i];
+  }
+};
+
 // Global store at a byte offset from a wave-uniform base (the global address space is
 // stated: the pointer's provenance is lost through the scalar move).
 __device__ __forceinline__ void store_at(uint32_t* base, uint32_t byte_off, uint32_t v) {

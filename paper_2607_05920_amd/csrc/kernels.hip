@@ -1008,21 +1008,29 @@ hipError_t launch_lift(const LiftArgs& a, int npoly, hipStream_t st, const Tunin
 // CKKS rounds half up: floor(x / 2^s) + bit_(s-1)(x).  BGV adds the centered
 // [[ (x mod 2^s) 2^-s ]]_t instead (the t-corrected division).
 
-__device__ __forceinline__ int64_t round_correction(const uint32_t* x, long long stride, int nl,
-                                                    int sbits, int scheme, uint32_t t,
+__device__ __forceinline__ int64_t round_correction(const LimbRows& x, int nl, int sbits, int scheme, uint32_t t,
                                                     uint32_t inv, const uint32_t* pw) {
-  // Correction added to floor(x / 2^sbits), x = sum_l x[l stride] 2^(32 l), nl limbs.
+  // Correction added to floor(x / 2^sbits), x = sum_l x[l] 2^(32 l), nl limbs.
   if (sbits <= 0) return 0;
   if (scheme == 0) {
     const int bi = sbits - 1;
     if ((bi >> 5) >= nl) return 0;
-    return (x[(long long)(bi >> 5) * stride] >> (bi & 31)) & 1u;
+    return (x[bi >> 5] >> (bi & 31)) & 1u;
   }
   // BGV: r = (x mod 2^sbits) mod t, then j = [[ r 2^-s ]]_t.
   const int full = sbits >> 5, part = sbits & 31;
   uint64_t acc = 0;
-  for (int l = 0; l < full && l < nl; ++l) acc += (uint64_t)x[(long long)l * stride] * pw[l];
-  if (part && full < nl) acc += (uint64_t)(x[(long long)full * stride] & ((1u << part) - 1u)) * pw[full];
+  for (int l0 = 0; l0 <= full && l0 < nl; l0 += kLimbBlock) {
+    uint32_t v[kLimbBlock];
+    x.block(v, l0);
+#pragma unroll
+    for (int i = 0; i < kLimbBlock; ++i) {
+      const int l = l0 + i;
+      if (l >= nl || l > full) break;
+      if (l < full) acc += (uint64_t)v[i] * pw[l];
+      else if (part) acc += (uint64_t)(v[i] & ((1u << part) - 1u)) * pw[full];
+    }
+  }
   const uint64_t rr = (acc % t) * inv % t;
   return (2 * rr > t) ? (int64_t)rr - (int64_t)t : (int64_t)rr;
 }
@@ -1032,26 +1040,34 @@ __device__ __forceinline__ void compose_kernel_body(const ComposeArgs& a, const 
   const int z = bk.y;  // 2 c + i
   if (jc >= a.N) return;
   const int c = z >> 1, i = z & 1;
-  const uint32_t* k = a.k + (long long)z * a.kstride + jc;
-  const uint32_t* d = a.d + (long long)(3 * c + i) * a.dstride + jc;
-  const bool dread = !(a.d1_zero && i);  // block-uniform
+  const LimbRows k(a.k + (long long)z * a.kstride, a.LK, a.N, jc);
+  // d_1 of a key switch is zero and not read (an empty buffer)
+  const LimbRows d(a.d + (long long)(3 * c + i) * a.dstride, a.d1_zero && i ? 0 : a.L, a.N, jc);
   uint32_t* o = (a.out0s ? (i ? a.out1s[c] : a.out0s[c]) : (i ? a.out1 : a.out0) + (long long)c * a.ostride) + jc;
-  const int64_t corr = round_correction(k, a.N, a.LK, a.logP, a.scheme, a.t, a.invP, a.pw);
+  const int64_t corr = round_correction(k, a.LK, a.logP, a.scheme, a.t, a.invP, a.pw);
   const int sl = a.logP >> 5, rs = a.logP & 31;
   const uint32_t ext = corr < 0 ? 0xFFFFFFFFu : 0u;
   uint64_t carry = 0;
-  uint32_t klo = sl < a.LK ? k[(long long)sl * a.N] : 0u;
+  uint32_t klo = k[sl];
   const int topbits = a.logq - 32 * (a.L - 1);
-  for (int l = 0; l < a.L; ++l) {
-    const uint32_t khi = (sl + l + 1 < a.LK) ? k[(long long)(sl + l + 1) * a.N] : 0u;
-    const uint32_t ks = rs ? ((klo >> rs) | (khi << (32 - rs))) : klo;
-    klo = khi;
-    const uint32_t cl = l == 0 ? (uint32_t)corr : ext;
-    const uint64_t sum = (uint64_t)(dread ? d[(long long)l * a.N] : 0u) + ks + cl + carry;
-    uint32_t wv = (uint32_t)sum;
-    carry = sum >> 32;
-    if (l == a.L - 1 && topbits < 32) wv &= (1u << topbits) - 1u;
-    o[(long long)l * a.N] = wv;
+  for (int l0 = 0; l0 < a.L; l0 += kLimbBlock) {
+    uint32_t kv[kLimbBlock], dv[kLimbBlock];
+    k.block(kv, sl + 1 + l0);
+    d.block(dv, l0);
+#pragma unroll
+    for (int b = 0; b < kLimbBlock; ++b) {
+      const int l = l0 + b;
+      if (l >= a.L) break;
+      const uint32_t khi = kv[b];
+      const uint32_t ks = rs ? ((klo >> rs) | (khi << (32 - rs))) : klo;
+      klo = khi;
+      const uint32_t cl = l == 0 ? (uint32_t)corr : ext;
+      const uint64_t sum = (uint64_t)dv[b] + ks + cl + carry;
+      uint32_t wv = (uint32_t)sum;
+      carry = sum >> 32;
+      if (l == a.L - 1 && topbits < 32) wv &= (1u << topbits) - 1u;
+      o[(long long)l * a.N] = wv;
+    }
   }
 }
 
@@ -1077,16 +1093,16 @@ __device__ __forceinline__ void compose_rescale_kernel_body(const ComposeArgs& a
   const int z = bk.y;  // 2 c + i
   if (jc >= a.N) return;
   const int c = z >> 1, i = z & 1;
-  const uint32_t* k = a.k + (long long)z * a.kstride + jc;
-  const uint32_t* d = a.d + (long long)(3 * c + i) * a.dstride + jc;
-  const bool dread = !(a.d1_zero && i);  // block-uniform
+  const LimbRows k(a.k + (long long)z * a.kstride, a.LK, a.N, jc);
+  // d_1 of a key switch is zero and not read (an empty buffer)
+  const LimbRows d(a.d + (long long)(3 * c + i) * a.dstride, a.d1_zero && i ? 0 : a.L, a.N, jc);
   uint32_t* o = (a.out0s ? (i ? a.out1s[c] : a.out0s[c]) : (i ? a.out1 : a.out0) + (long long)c * a.ostride) + jc;
   // compose state
-  const int64_t corrP = round_correction(k, a.N, a.LK, a.logP, a.scheme, a.t, a.invP, a.pw);
+  const int64_t corrP = round_correction(k, a.LK, a.logP, a.scheme, a.t, a.invP, a.pw);
   const int sl = a.logP >> 5, rs = a.logP & 31;
   const uint32_t extP = corrP < 0 ? 0xFFFFFFFFu : 0u;
   uint64_t carryP = 0;
-  uint32_t klo = sl < a.LK ? k[(long long)sl * a.N] : 0u;
+  uint32_t klo = k[sl];
   const int topbits = a.logq - 32 * (a.L - 1);
   // rescale state
   const int sb = a.bits >> 5, rb = a.bits & 31;
@@ -1104,37 +1120,45 @@ __device__ __forceinline__ void compose_rescale_kernel_body(const ComposeArgs& a
     if (m == Lout - 1 && otop < 32) w &= (1u << otop) - 1u;
     o[(long long)m * a.N] = w;
   };
-  for (int l = 0; l < a.L; ++l) {
-    const uint32_t khi = (sl + l + 1 < a.LK) ? k[(long long)(sl + l + 1) * a.N] : 0u;
-    const uint32_t ks = rs ? ((klo >> rs) | (khi << (32 - rs))) : klo;
-    klo = khi;
-    const uint32_t cp = l == 0 ? (uint32_t)corrP : extP;
-    const uint64_t sum = (uint64_t)(dread ? d[(long long)l * a.N] : 0u) + ks + cp + carryP;
-    uint32_t cv = (uint32_t)sum;
-    carryP = sum >> 32;
-    if (l == a.L - 1 && topbits < 32) cv &= (1u << topbits) - 1u;
-    // the rescale's correction from the low bits of c
-    if (a.scheme == 0) {
-      if (l == ((a.bits - 1) >> 5)) rbit = (cv >> ((a.bits - 1) & 31)) & 1u;
-    } else if (l < sb) {
-      acc += (uint64_t)cv * a.pw[l];
-    } else if (l == sb && rb) {
-      acc += (uint64_t)(cv & ((1u << rb) - 1u)) * a.pw[sb];
-    }
-    if (l == sb) {
+  for (int l0 = 0; l0 < a.L; l0 += kLimbBlock) {
+    uint32_t kv[kLimbBlock], dv[kLimbBlock];
+    k.block(kv, sl + 1 + l0);
+    d.block(dv, l0);
+#pragma unroll
+    for (int b = 0; b < kLimbBlock; ++b) {
+      const int l = l0 + b;
+      if (l >= a.L) break;
+      const uint32_t khi = kv[b];
+      const uint32_t ks = rs ? ((klo >> rs) | (khi << (32 - rs))) : klo;
+      klo = khi;
+      const uint32_t cp = l == 0 ? (uint32_t)corrP : extP;
+      const uint64_t sum = (uint64_t)dv[b] + ks + cp + carryP;
+      uint32_t cv = (uint32_t)sum;
+      carryP = sum >> 32;
+      if (l == a.L - 1 && topbits < 32) cv &= (1u << topbits) - 1u;
+      // the rescale's correction from the low bits of c
       if (a.scheme == 0) {
-        corrB = rbit;
-      } else {
-        const uint64_t rr = (acc % a.t) * a.invB % a.t;
-        corrB = (2 * rr > a.t) ? (int64_t)rr - (int64_t)a.t : (int64_t)rr;
+        if (l == ((a.bits - 1) >> 5)) rbit = (cv >> ((a.bits - 1) & 31)) & 1u;
+      } else if (l < sb) {
+        acc += (uint64_t)cv * a.pw[l];
+      } else if (l == sb && rb) {
+        acc += (uint64_t)(cv & ((1u << rb) - 1u)) * a.pw[sb];
       }
-      extB = corrB < 0 ? 0xFFFFFFFFu : 0u;
+      if (l == sb) {
+        if (a.scheme == 0) {
+          corrB = rbit;
+        } else {
+          const uint64_t rr = (acc % a.t) * a.invB % a.t;
+          corrB = (2 * rr > a.t) ? (int64_t)rr - (int64_t)a.t : (int64_t)rr;
+        }
+        extB = corrB < 0 ? 0xFFFFFFFFu : 0u;
+      }
+      if (l > sb) {
+        const int m = l - sb - 1;
+        if (m < Lout) emit(m, rb ? ((cprev >> rb) | (cv << (32 - rb))) : cprev);
+      }
+      if (l >= sb) cprev = cv;
     }
-    if (l > sb) {
-      const int m = l - sb - 1;
-      if (m < Lout) emit(m, rb ? ((cprev >> rb) | (cv << (32 - rb))) : cprev);
-    }
-    if (l >= sb) cprev = cv;
   }
   const int m = a.L - sb - 1;  // the last output limb takes zeros above c
   if (m >= 0 && m < Lout) emit(m, rb ? (cprev >> rb) : cprev);
@@ -1162,25 +1186,32 @@ __global__ __launch_bounds__(256) void rescale_kernel(RescaleArgs a) {
   const int Lin = (a.logq + 31) >> 5;
   const int newq = a.logq - a.bits;
   const int Lout = (newq + 31) >> 5;
-  const uint32_t* x = (i ? a.in1 : a.in0) + (long long)c * a.istride + jc;
+  const LimbRows x((i ? a.in1 : a.in0) + (long long)c * a.istride, Lin, a.N, jc);
   uint32_t* o = (a.out0s ? (i ? a.out1s[c] : a.out0s[c]) : (i ? a.out1 : a.out0) + (long long)c * a.ostride) + jc;
-  const int64_t corr = round_correction(x, a.N, Lin, a.bits, a.scheme, a.t, a.invB, a.pw);
+  const int64_t corr = round_correction(x, Lin, a.bits, a.scheme, a.t, a.invB, a.pw);
   const int sl = a.bits >> 5, rs = a.bits & 31;
   const uint32_t ext = corr < 0 ? 0xFFFFFFFFu : 0u;
   uint64_t carry = 0;
-  uint32_t xlo = sl < Lin ? x[(long long)sl * a.N] : 0u;
+  uint32_t xlo = x[sl];
   const int topbits = newq - 32 * (Lout - 1);
-  for (int l = 0; l < Lout; ++l) {
-    // reads of limbs >= sl + l precede the write of limb l (in place is safe)
-    const uint32_t xhi = (sl + l + 1 < Lin) ? x[(long long)(sl + l + 1) * a.N] : 0u;
-    const uint32_t xs = rs ? ((xlo >> rs) | (xhi << (32 - rs))) : xlo;
-    xlo = xhi;
-    const uint32_t cl = l == 0 ? (uint32_t)corr : ext;
-    const uint64_t sum = (uint64_t)xs + cl + carry;
-    uint32_t wv = (uint32_t)sum;
-    carry = sum >> 32;
-    if (l == Lout - 1 && topbits < 32) wv &= (1u << topbits) - 1u;
-    o[(long long)l * a.N] = wv;
+  for (int l0 = 0; l0 < Lout; l0 += kLimbBlock) {
+    // reads of limbs above sl + l precede the write of limb l (in place is safe)
+    uint32_t xv[kLimbBlock];
+    x.block(xv, sl + 1 + l0);
+#pragma unroll
+    for (int b = 0; b < kLimbBlock; ++b) {
+      const int l = l0 + b;
+      if (l >= Lout) break;
+      const uint32_t xhi = xv[b];
+      const uint32_t xs = rs ? ((xlo >> rs) | (xhi << (32 - rs))) : xlo;
+      xlo = xhi;
+      const uint32_t cl = l == 0 ? (uint32_t)corr : ext;
+      const uint64_t sum = (uint64_t)xs + cl + carry;
+      uint32_t wv = (uint32_t)sum;
+      carry = sum >> 32;
+      if (l == Lout - 1 && topbits < 32) wv &= (1u << topbits) - 1u;
+      o[(long long)l * a.N] = wv;
+    }
   }
 }
 
@@ -1249,14 +1280,22 @@ __global__ __launch_bounds__(256) void add_small_kernel(const uint32_t* __restri
   const long long s = e ? mult * (long long)e[j] : 0;
   const uint32_t ext = s < 0 ? 0xFFFFFFFFu : 0u;
   uint64_t carry = 0;
-  for (int l = 0; l < L; ++l) {
-    const long long o = (long long)l * N + j;
-    const uint32_t a = l == 0 ? (uint32_t)s : (l == 1 ? (uint32_t)((unsigned long long)s >> 32) : ext);
-    const uint64_t t = (uint64_t)x[o] + (y ? y[o] : 0u) + a + carry;
-    uint32_t w = (uint32_t)t;
-    carry = t >> 32;
-    if (l == L - 1) w &= topmask;
-    out[o] = w;
+  const LimbRows xr(x, L, N, j), yr(y ? y : x, y ? L : 0, N, j);
+  for (int l0 = 0; l0 < L; l0 += kLimbBlock) {
+    uint32_t xv[kLimbBlock], yv[kLimbBlock];
+    xr.block(xv, l0);
+    yr.block(yv, l0);
+#pragma unroll
+    for (int b = 0; b < kLimbBlock; ++b) {
+      const int l = l0 + b;
+      if (l >= L) break;
+      const uint32_t a = l == 0 ? (uint32_t)s : (l == 1 ? (uint32_t)((unsigned long long)s >> 32) : ext);
+      const uint64_t t = (uint64_t)xv[b] + yv[b] + a + carry;
+      uint32_t w = (uint32_t)t;
+      carry = t >> 32;
+      if (l == L - 1) w &= topmask;
+      out[(long long)l * N + j] = w;
+    }
   }
 }
 

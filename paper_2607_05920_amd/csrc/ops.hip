@@ -8,7 +8,7 @@
 // the carry chain of the multiprecision value in registers.  A thread reads limb l of
 // its own coefficient before it writes limb l, so the coefficient-wise kernels may run
 // in place; the permutations read other coefficients and may not.
-#include "fhe_internal.h"
+#include "device_common.h"
 
 namespace fhe {
 
@@ -20,19 +20,27 @@ __global__ __launch_bounds__(256) void limb_sum_kernel(LimbSumArgs a) {
   const int j = blockIdx.x * 256 + threadIdx.x;
   if (j >= a.N) return;
   const int z = blockIdx.y, c = z >> 1, i = z & 1;
-  const uint32_t* x = (i ? a.x1 : a.x0) + (long long)c * a.xstride + j;
+  const LimbRows x((i ? a.x1 : a.x0) + (long long)c * a.xstride, a.L, a.N, j);
   const uint32_t* yb = i ? a.y1 : a.y0;
-  const uint32_t* y = yb ? yb + (long long)c * a.ystride + j : nullptr;
+  const bool has_y = yb != nullptr;  // without y its rows read as zero (an empty buffer)
+  const LimbRows y(has_y ? yb + (long long)c * a.ystride : a.x0, has_y ? a.L : 0, a.N, j);
   uint32_t* o = (i ? a.out1 : a.out0) + (long long)c * a.ostride + j;
-  const uint32_t mx = a.negx ? 0xFFFFFFFFu : 0u, my = a.negy ? 0xFFFFFFFFu : 0u;
-  uint64_t carry = (uint64_t)(a.negx != 0) + (uint64_t)(y && a.negy);
-  for (int l = 0; l < a.L; ++l) {
-    const long long off = (long long)l * a.N;
-    const uint64_t s = (uint64_t)(x[off] ^ mx) + (y ? (uint64_t)(y[off] ^ my) : 0ull) + carry;
-    uint32_t w = (uint32_t)s;
-    carry = s >> 32;
-    if (l == a.L - 1) w &= a.topmask;
-    o[off] = w;
+  const uint32_t mx = a.negx ? 0xFFFFFFFFu : 0u, my = has_y && a.negy ? 0xFFFFFFFFu : 0u;
+  uint64_t carry = (uint64_t)(a.negx != 0) + (uint64_t)(my != 0);
+  for (int l0 = 0; l0 < a.L; l0 += kLimbBlock) {
+    uint32_t xv[kLimbBlock], yv[kLimbBlock];
+    x.block(xv, l0);
+    y.block(yv, l0);
+#pragma unroll
+    for (int k = 0; k < kLimbBlock; ++k) {
+      const int l = l0 + k;
+      if (l >= a.L) break;
+      const uint64_t s = (uint64_t)(xv[k] ^ mx) + (uint64_t)(yv[k] ^ my) + carry;
+      uint32_t w = (uint32_t)s;
+      carry = s >> 32;
+      if (l == a.L - 1) w &= a.topmask;
+      o[(long long)l * a.N] = w;
+    }
   }
 }
 
@@ -49,17 +57,23 @@ __global__ __launch_bounds__(256) void signed_perm_kernel(PermArgs a) {
   const uint32_t twoN_mask = (2u << a.logN) - 1u;
   const uint32_t src = ((uint32_t)k * a.mul + a.add) & twoN_mask;
   const bool neg = src >= (uint32_t)N;
-  const uint32_t* x = (i ? a.in1 : a.in0) + (long long)c * a.istride + (src & (uint32_t)(N - 1));
+  const LimbRows x((i ? a.in1 : a.in0) + (long long)c * a.istride, a.L, N, src & (uint32_t)(N - 1));
   uint32_t* o = (i ? a.out1 : a.out0) + (long long)c * a.ostride + k;
   const uint32_t m = neg ? 0xFFFFFFFFu : 0u;
   uint64_t carry = neg ? 1u : 0u;
-  for (int l = 0; l < a.L; ++l) {
-    const long long off = (long long)l * N;
-    const uint64_t s = (uint64_t)(x[off] ^ m) + carry;
-    uint32_t w = (uint32_t)s;
-    carry = s >> 32;
-    if (l == a.L - 1) w &= a.topmask;
-    o[off] = w;
+  for (int l0 = 0; l0 < a.L; l0 += kLimbBlock) {
+    uint32_t xv[kLimbBlock];
+    x.block(xv, l0);
+#pragma unroll
+    for (int b = 0; b < kLimbBlock; ++b) {
+      const int l = l0 + b;
+      if (l >= a.L) break;
+      const uint64_t s = (uint64_t)(xv[b] ^ m) + carry;
+      uint32_t w = (uint32_t)s;
+      carry = s >> 32;
+      if (l == a.L - 1) w &= a.topmask;
+      o[(long long)l * N] = w;
+    }
   }
 }
 
@@ -71,32 +85,39 @@ __global__ __launch_bounds__(256) void const_mul_kernel(ConstMulArgs a) {
   const int j = blockIdx.x * 256 + threadIdx.x;
   if (j >= a.N) return;
   const int z = blockIdx.y, c = z >> 1, i = z & 1;
-  const uint32_t* x = (i ? a.in1 : a.in0) + (long long)c * a.istride + j;
+  const LimbRows x((i ? a.in1 : a.in0) + (long long)c * a.istride, a.L, a.N, j);
   uint32_t* o = (i ? a.out1 : a.out0) + (long long)c * a.ostride + j;
   uint32_t win[kConstMaxLimbs];
 #pragma unroll
   for (int t = 0; t < kConstMaxLimbs; ++t) win[t] = 0u;
   const uint32_t nm = a.neg ? 0xFFFFFFFFu : 0u;
   uint64_t carry = 0, ncarry = a.neg ? 1u : 0u;
-  for (int l = 0; l < a.L; ++l) {
+  for (int l0 = 0; l0 < a.L; l0 += kLimbBlock) {
+    uint32_t xv[kLimbBlock];
+    x.block(xv, l0);
 #pragma unroll
-    for (int t = kConstMaxLimbs - 1; t > 0; --t) win[t] = win[t - 1];
-    win[0] = x[(long long)l * a.N];
-    uint64_t lo = carry & 0xFFFFFFFFull, hi = carry >> 32;
+    for (int b = 0; b < kLimbBlock; ++b) {
+      const int l = l0 + b;
+      if (l >= a.L) break;
 #pragma unroll
-    for (int t = 0; t < kConstMaxLimbs; ++t) {
-      if (t < a.klimbs) {
-        const uint64_t p = (uint64_t)win[t] * a.k[t];
-        lo += (uint32_t)p;
-        hi += p >> 32;
+      for (int t = kConstMaxLimbs - 1; t > 0; --t) win[t] = win[t - 1];
+      win[0] = xv[b];
+      uint64_t lo = carry & 0xFFFFFFFFull, hi = carry >> 32;
+#pragma unroll
+      for (int t = 0; t < kConstMaxLimbs; ++t) {
+        if (t < a.klimbs) {
+          const uint64_t p = (uint64_t)win[t] * a.k[t];
+          lo += (uint32_t)p;
+          hi += p >> 32;
+        }
       }
+      carry = (lo >> 32) + hi;
+      const uint64_t s = (uint64_t)((uint32_t)lo ^ nm) + ncarry;
+      uint32_t w = (uint32_t)s;
+      ncarry = s >> 32;
+      if (l == a.L - 1) w &= a.topmask;
+      o[(long long)l * a.N] = w;
     }
-    carry = (lo >> 32) + hi;
-    const uint64_t s = (uint64_t)((uint32_t)lo ^ nm) + ncarry;
-    uint32_t w = (uint32_t)s;
-    ncarry = s >> 32;
-    if (l == a.L - 1) w &= a.topmask;
-    o[(long long)l * a.N] = w;
   }
 }
 
