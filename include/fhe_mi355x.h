@@ -393,7 +393,8 @@ typedef struct {
 /* Bootstrap one CKKS ciphertext (cnum = 1) at logq = logq_in (its logp <= logq_in):
  * out receives the refreshed ciphertext; out->c0, out->c1 must each hold L_Q N words
  * (the output's level is below logQ; the call writes out's metadata).  Allocates its
- * temporaries and synchronizes `stream` before returning.  Errors: FHE_E_INVAL (null,
+ * temporaries, which the context keeps for the next call (until it is destroyed, or another
+ * size or its scratch needs the memory), and synchronizes `stream` before returning.  Errors: FHE_E_INVAL (null,
  * parameters, a missing key), FHE_E_SHAPE (the input is not a one-ciphertext CKKS tensor
  * at logq_in of ring degree 2^logN), FHE_E_RANGE (levels exhausted: logQ too small for
  * the circuit), plus the errors of the operations. */

@@ -265,6 +265,8 @@ struct fhe_ctx {
   std::map<std::pair<int, int>, LiftTab> lifts;           // per (L, K)
   std::map<uint32_t, uint32_t*> pw;  // per BGV t: 2^(32 l) mod t
   std::map<std::pair<void*, int>, Workspace> ws;  // (stream, slot)
+  std::vector<uint32_t*> boot;  // bootstrapping's kept buffers (boot_take), boot_words each
+  size_t boot_words = 0;
   std::recursive_mutex mu;
   int sticky = FHE_OK;
   Recorder* rec = nullptr;  // non-null while profiling is on
@@ -531,6 +533,11 @@ uint32_t* pow_table(fhe_ctx* c, uint32_t t, hipError_t* err) {
 }
 
 // Scratch memory of a (context, stream, slot), grown on demand.
+void boot_release(fhe_ctx* c) {
+  for (uint32_t* p : c->boot) hipFree(p);
+  c->boot.clear();
+}
+
 void* stream_scratch(fhe_ctx* c, void* stream, int slot, size_t bytes, hipError_t* err) {
   Workspace& w = c->ws[std::make_pair(stream, slot)];
   if (w.bytes < bytes) {
@@ -541,6 +548,11 @@ void* stream_scratch(fhe_ctx* c, void* stream, int slot, size_t bytes, hipError_
       w.bytes = 0;
     }
     *err = hipMalloc(&w.ptr, bytes);
+    if (*err == hipErrorOutOfMemory && !c->boot.empty()) {
+      boot_release(c);
+      (void)hipGetLastError();
+      *err = hipMalloc(&w.ptr, bytes);
+    }
     if (*err != hipSuccess) return nullptr;
     w.bytes = bytes;
   }
@@ -1487,6 +1499,27 @@ bool ct_overlap(const fhe_ct* a, int La, const fhe_ct* b, int Lb) {
 
 // ================================================================ C ABI
 
+uint32_t* fhe::boot_take(fhe_ctx* c, size_t words) {
+  std::lock_guard<std::recursive_mutex> lg(c->mu);
+  hipSetDevice(c->device);
+  if (c->boot_words != words) boot_release(c);  // kept for another size
+  if (!c->boot.empty()) {
+    uint32_t* p = c->boot.back();
+    c->boot.pop_back();
+    return p;
+  }
+  uint32_t* p = nullptr;
+  return hipMalloc((void**)&p, words * 4) == hipSuccess ? p : nullptr;
+}
+
+void fhe::boot_give(fhe_ctx* c, uint32_t* p, size_t words, bool idle) {
+  std::lock_guard<std::recursive_mutex> lg(c->mu);
+  hipSetDevice(c->device);
+  if (c->boot_words != words && c->boot.empty()) c->boot_words = words;
+  if (idle && c->boot_words == words && (int)c->boot.size() < kBootKeep) c->boot.push_back(p);
+  else hipFree(p);
+}
+
 extern "C" {
 
 const char* fhe_error_detail(void) { return g_detail; }
@@ -1664,6 +1697,7 @@ void fhe_ctx_destroy(fhe_ctx* c) {
     for (void* p : {(void*)kv.second.A, (void*)kv.second.mneg, (void*)kv.second.eneg})
       if (p) hipFree(p);
   for (auto& kv : c->pw) hipFree(kv.second);
+  boot_release(c);
   for (auto& kv : c->ws)
     if (kv.second.ptr) hipFree(kv.second.ptr);
   delete c->rec;

@@ -13,16 +13,22 @@
 #include <map>
 #include <vector>
 
+#include "fhe_internal.h"
 #include "fhe_mi355x.h"
 
 namespace {
 
-// Device buffers of ciphertexts at the top level (2 L_Q N words each), reused.
+// Device buffers of ciphertexts at the top level (room for a CipherTensor of two), reused
+// within a call and, through the context's kept list (boot_take), from call to call:
+// allocating and freeing the two dozen of them took 3.5 ms of a call of 8 (N = 2^14).
 class CtPool {
  public:
-  CtPool(size_t words) : words_(words) {}
+  CtPool(fhe_ctx* c, size_t words, hipStream_t st) : c_(c), words_(words), st_(st) {}
   ~CtPool() {
-    for (uint32_t* p : all_) hipFree(p);
+    if (all_.empty()) return;
+    // nothing queued uses a buffer that another call may be given (also after an error)
+    const bool idle = hipStreamSynchronize(st_) == hipSuccess;
+    for (uint32_t* p : all_) fhe::boot_give(c_, p, words_, idle);
   }
   uint32_t* get() {
     if (!free_.empty()) {
@@ -30,9 +36,8 @@ class CtPool {
       free_.pop_back();
       return p;
     }
-    uint32_t* p = nullptr;
-    if (hipMalloc((void**)&p, words_ * 4) != hipSuccess) return nullptr;
-    all_.push_back(p);
+    uint32_t* p = fhe::boot_take(c_, words_);
+    if (p) all_.push_back(p);
     return p;
   }
   void put(uint32_t* p) {
@@ -40,14 +45,17 @@ class CtPool {
   }
 
  private:
+  fhe_ctx* c_;
   size_t words_;
+  hipStream_t st_;
   std::vector<uint32_t*> all_, free_;
 };
 
 class Boot {
  public:
   Boot(fhe_ctx* c, const fhe_boot_params& P, const fhe_boot_keys& K, void* st)
-      : c_(c), P_(P), K_(K), st_(st), half_((size_t)((P.logQ + 31) / 32) << P.logN), pool_(4 * half_) {}
+      : c_(c), P_(P), K_(K), st_(st), half_((size_t)((P.logQ + 31) / 32) << P.logN),
+        pool_(c, 4 * half_, (hipStream_t)st) {}
 
   int rc = FHE_OK;
 
@@ -85,13 +93,19 @@ class Boot {
     if (rc == FHE_OK && r != FHE_OK) rc = r;
   }
 
-  // a copy at level logq (moddown, or a plain copy at the same level)
+  // x at level logq: x itself, not owned, where that is its level (x must then outlive the
+  // view), else a copy (moddown)
   V level(const V& x, int logq) {
+    if (x.ct.logq == logq) {
+      V v;
+      v.ct = x.ct;
+      return v;
+    }
     V y = fresh();
     if (ok()) check(fhe_ct_moddown(c_, &x.ct, x.ct.logq - logq, &y.ct, st_));
     return y;
   }
-  // the pair brought to the lower of the two levels (new values)
+  // the pair brought to the lower of the two levels (one of the two is a view)
   void match(const V& x, const V& y, V& xo, V& yo) {
     const int q = std::min(x.ct.logq, y.ct.logq);
     xo = level(x, q);
@@ -166,8 +180,9 @@ class Boot {
       dg.logq = P_.logQ;
       dg.scheme = FHE_CKKS;
       dg.gamma = 1;
-      V m = fresh();
-      if (ok()) check(fhe_ct_moddown(c_, &dg, P_.logQ - r.ct.logq, &m.ct, st_));
+      V whole;
+      whole.ct = dg;
+      V m = level(whole, r.ct.logq);
       V term = fresh();
       if (ok()) check(fhe_ct_multconstvec(c_, &r.ct, m.ct.c0, 1, P_.logc, &term.ct, st_));
       drop(m);
@@ -225,8 +240,6 @@ class Boot {
     if (!ok()) return V{};
     V a, b;
     match(re, im, a, b);
-    drop(re);
-    drop(im);
     // the constant 1 at a's scale: 2^logp at coefficient 0
     V one = fresh();
     if (ok()) {
@@ -245,6 +258,8 @@ class Boot {
     drop(a);
     V is = imult(b);
     drop(b);
+    drop(re);
+    drop(im);
     V E = add(c, is);
     drop(c);
     drop(is);
@@ -344,7 +359,7 @@ class Boot {
     out->t = 0;
     out->gamma = 1;
     drop(z);
-    // the pool's buffers are freed when this object goes: wait for the queued work
+    // the pool's buffers go back when this object goes: wait for the queued work
     return hipStreamSynchronize(s) == hipSuccess ? FHE_OK : FHE_E_DEVICE;
   }
 

@@ -6,7 +6,17 @@
 
 #include "modarith.h"
 
+struct fhe_ctx;
+
 namespace fhe {
+
+// Bootstrapping's device buffers: taken from the context's kept list (or allocated), given
+// back to it.  The list holds buffers of one size, at most kBootKeep of them; others, and
+// those whose stream could not be waited for, are freed.  The list is freed with the
+// context, or when an allocation for the context's scratch fails.
+constexpr int kBootKeep = 48;
+uint32_t* boot_take(fhe_ctx* c, size_t words);
+void boot_give(fhe_ctx* c, uint32_t* p, size_t words, bool idle);
 
 typedef int v4i_t __attribute__((ext_vector_type(4)));
 
