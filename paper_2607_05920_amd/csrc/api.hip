@@ -679,10 +679,10 @@ LiftArgs lift_args(fhe_ctx* c, const uint32_t* limbs, uint32_t* res, long long i
 
 // CRT reconstruction of npoly polynomials: residues of X (with |X| < 2^e) on K
 // primes -> X mod 2^outbits.  Poly z reads res + (z / per_group) gstride +
-// (z % per_group) pstride and writes out + z ostride.
+// (z % per_group) pstride and writes out + z ostride, from first1 on out1 + (z - first1) ostride.
 hipError_t run_crt(fhe_ctx* c, const uint32_t* res, int per_group, long long gstride, long long pstride,
                    uint32_t* out, long long ostride, int N, int K, int e, int outbits, int npoly, const uint32_t* scale,
-                   hipStream_t st) {
+                   hipStream_t st, uint32_t* out1 = nullptr, int first1 = 1 << 30) {
   hipError_t err = hipSuccess;
   const int Lout = (outbits + 31) / 32;
   const CrtTab* t = crt_table(c, K, e, Lout, &err);
@@ -693,6 +693,8 @@ hipError_t run_crt(fhe_ctx* c, const uint32_t* res, int per_group, long long gst
   a.gstride = gstride;
   a.pstride = pstride;
   a.out = out;
+  a.out1 = out1;
+  a.first1 = first1;
   a.ostride = ostride;
   a.N = N;
   a.K = K;
@@ -1447,8 +1449,7 @@ int plain_mul_locked(fhe_ctx* c, int logN, int logq, const uint32_t* x0, const u
     ra.data2_groups = mcount > 1 ? mcount : 1;
     e = launch_rows_fused(ra, ROWS_RING, st);
   }
-  if (e == hipSuccess) e = run_crt(c, R, 1, KN, 0, out0, LN, N, K, eb, logq, cnum, sc, st);
-  if (e == hipSuccess) e = run_crt(c, R + cnum * KN, 1, KN, 0, out1, LN, N, K, eb, logq, cnum, sc, st);
+  if (e == hipSuccess) e = run_crt(c, R, 1, KN, 0, out0, LN, N, K, eb, logq, 2 * cnum, sc, st, out1, cnum);
   return set_sticky(c, e);
 }
 
@@ -1848,21 +1849,28 @@ int fhe_encrypt(fhe_ctx* c, int scheme, uint32_t t, int logN, int logq, const ui
   const uint32_t top = (logq & 31) ? (1u << (logq & 31)) - 1u : 0xFFFFFFFFu;
   const long long LN = (long long)L * N;
   hipError_t e = hipSuccess;
-  // [v, v] against [pk_b, pk_a] mod Q_l as one pair of ring products
-  uint32_t* S = (uint32_t*)stream_scratch(c, stream, 3, (size_t)6 * LN * 4, &e);
+  // v against pk_b and pk_a mod Q_l: two products that share an operand
+  uint32_t* S = (uint32_t*)stream_scratch(c, stream, 3, (size_t)5 * LN * 4, &e);
   if (!S) return set_sticky(c, e);
-  uint32_t *A = S, *B = S + 2 * LN, *P = S + 4 * LN;
-  e = launch_small_to_limbs(v, A, N, L, top, st);
-  if (e == hipSuccess) e = launch_small_to_limbs(v, A + LN, N, L, top, st);
-  if (e == hipSuccess) e = launch_mask_rows(pk_b, B, N, L, top, st);
-  if (e == hipSuccess) e = launch_mask_rows(pk_a, B + LN, N, L, top, st);
+  uint32_t *V = S, *B = S + LN, *P = S + 3 * LN;
+  e = launch_operands(v, pk_b, pk_a, V, N, L, top, st);
   if (e != hipSuccess) return set_sticky(c, e);
-  int rc = ring_mul_locked(c, logN, logq, A, B, P, 2, stream);
+  int rc = plain_mul_locked(c, logN, logq, B, B + LN, V, 1, P, P + LN, 1, st);
   if (rc != FHE_OK) return rc;
-  const long long mult = scheme == FHE_BGV ? (long long)t : 1;
-  e = launch_add_small(P, m, e0, mult, c0, N, L, top, st);
-  if (e == hipSuccess) e = launch_add_small(P + LN, nullptr, e1, mult, c1, N, L, top, st);
-  return set_sticky(c, e);
+  AddSmallArgs aa;
+  aa.x0 = P;
+  aa.y0 = m;
+  aa.e0 = e0;
+  aa.out0 = c0;
+  aa.x1 = P + LN;
+  aa.e1 = e1;
+  aa.out1 = c1;
+  aa.mult = scheme == FHE_BGV ? (long long)t : 1;
+  aa.n = 2;
+  aa.N = N;
+  aa.L = L;
+  aa.topmask = top;
+  return set_sticky(c, launch_add_small(aa, st));
 }
 
 int fhe_decrypt(fhe_ctx* c, int scheme, uint32_t t, uint32_t gamma, int logN, int logq, const uint32_t* c0,
@@ -1883,12 +1891,20 @@ int fhe_decrypt(fhe_ctx* c, int scheme, uint32_t t, uint32_t gamma, int logN, in
   uint32_t* S = (uint32_t*)stream_scratch(c, stream, 3, (size_t)3 * LN * 4, &e);
   if (!S) return set_sticky(c, e);
   uint32_t *SL = S, *P = S + LN, *PH = S + 2 * LN;
-  e = launch_small_to_limbs(s, SL, N, L, top, st);
+  e = launch_operands(s, nullptr, nullptr, SL, N, L, top, st);
   if (e != hipSuccess) return set_sticky(c, e);
   int rc = ring_mul_locked(c, logN, logq, c1, SL, P, 1, stream);
   if (rc != FHE_OK) return rc;
-  if (scheme == FHE_CKKS) return set_sticky(c, launch_add_small(P, c0, nullptr, 0, out, N, L, top, st));
-  e = launch_add_small(P, c0, nullptr, 0, PH, N, L, top, st);
+  AddSmallArgs aa;
+  aa.x0 = P;
+  aa.y0 = c0;
+  aa.out0 = scheme == FHE_CKKS ? out : PH;
+  aa.n = 1;
+  aa.N = N;
+  aa.L = L;
+  aa.topmask = top;
+  e = launch_add_small(aa, st);
+  if (scheme == FHE_CKKS) return set_sticky(c, e);
   if (e == hipSuccess)
     e = launch_bgv_decode(PH, out, N, L, logq, t, (uint32_t)powmod(2, logq, t), (uint32_t)invmod(gamma, t), st);
   return set_sticky(c, e);

@@ -253,7 +253,8 @@ __device__ __forceinline__ void crt_cols_kernel_body(const CrtArgs& a, const Blk
     // a, V plane b) and diagonal sums S_p = sum_(a+b=p) C_ab.  S_4..S_6 weigh 2^0..2^16 in
     // limb l + 1: inside the lane they join the next limb's sums, from the top limb they
     // leave with the carry.
-    uint32_t* o = wave_uniform(a.out + (long long)z * a.ostride + j0);
+    uint32_t* o = wave_uniform((z < a.first1 ? a.out + (long long)z * a.ostride
+                                             : a.out1 + (long long)(z - a.first1) * a.ostride) + j0);
     uint32_t out_off = 4u * h * row + (2u * wave + (c >> 4)) * (row >> 4) + 4u * (c & 15);
     opaque(out_off);
     const int topbits = a.outbits - 32 * (a.Lout - 1);

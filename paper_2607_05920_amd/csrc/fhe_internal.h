@@ -100,7 +100,9 @@ struct CrtArgs {
   const uint32_t* res = nullptr; // poly z: res + (z / per_group) * gstride + (z % per_group) * pstride, [K][N]
   int per_group = 0;
   long long gstride = 0, pstride = 0;
-  uint32_t* out = nullptr;  // poly z: out + z * ostride, uint32[Lout][N]
+  uint32_t* out = nullptr;  // poly z: out + z * ostride, uint32[Lout][N]; from first1 on: out1 + (z - first1) * ostride
+  uint32_t* out1 = nullptr;
+  int first1 = 1 << 30;
   long long ostride = 0;
   int N = 0, K = 0, outbits = 0, Lout = 0;
   int ntiles = 0;           // tiles of 8 output limbs
@@ -146,6 +148,17 @@ struct RescaleArgs {
   int N = 0, logq = 0, bits = 0, scheme = 0;
   uint32_t t = 0, invB = 0;  // BGV: t and 2^-bits mod t
   const uint32_t* pw = nullptr;
+};
+
+// Adding small signed polynomials modulo 2^logq: out_i = x_i + y_i + mult e_i, i < n <= 2
+struct AddSmallArgs {
+  const uint32_t *x0 = nullptr, *x1 = nullptr;
+  const uint32_t *y0 = nullptr, *y1 = nullptr;  // or null
+  const int32_t *e0 = nullptr, *e1 = nullptr;   // or null
+  uint32_t *out0 = nullptr, *out1 = nullptr;
+  long long mult = 0;
+  int n = 0, N = 0, L = 0;
+  uint32_t topmask = 0;
 };
 
 // Coefficient-wise sums: polynomial z = 2 c + i (ciphertext c, component i) of
@@ -284,10 +297,10 @@ hipError_t launch_crt_cols(CrtArgs a, int npoly, hipStream_t s);
 hipError_t launch_compose(const ComposeArgs& a, int cnum, hipStream_t s);
 hipError_t launch_rescale(const RescaleArgs& a, int cnum, hipStream_t s);
 hipError_t launch_compose_rescale(const ComposeArgs& a, int cnum, hipStream_t s);
-hipError_t launch_small_to_limbs(const int8_t* v, uint32_t* out, int N, int L, uint32_t topmask, hipStream_t s);
-hipError_t launch_mask_rows(const uint32_t* in, uint32_t* out, int N, int L, uint32_t topmask, hipStream_t s);
-hipError_t launch_add_small(const uint32_t* x, const uint32_t* y, const int32_t* e, long long mult, uint32_t* out,
-                            int N, int L, uint32_t topmask, hipStream_t s);
+// out: [v] and, unless null, [b] and [a], uint32[L][N] each, modulo 2^logq
+hipError_t launch_operands(const int8_t* v, const uint32_t* b, const uint32_t* a, uint32_t* out, int N, int L,
+                           uint32_t topmask, hipStream_t s);
+hipError_t launch_add_small(const AddSmallArgs& a, hipStream_t s);
 hipError_t launch_bgv_decode(const uint32_t* ph, uint32_t* m, int N, int L, int logq, uint32_t t, uint32_t qmodt,
                              uint32_t ginv, hipStream_t s);
 hipError_t launch_bitrev(uint32_t* data, int logN, long long rows, hipStream_t s);

@@ -1246,55 +1246,64 @@ hipError_t launch_rescale(const RescaleArgs& a, int cnum, hipStream_t st) {
 // One thread per (coefficient, limb) or per coefficient; limb-major layout keeps
 // every access of a wave on consecutive words of one limb row.
 
-// [v]_(2^logq) of small signed coefficients: limb 0 holds v mod 2^32, higher limbs
-// the sign extension, the top limb masked to logq bits.
-__global__ __launch_bounds__(256) void small_to_limbs_kernel(const int8_t* __restrict__ v, uint32_t* __restrict__ out,
-                                                             int N, int L, uint32_t topmask) {
+// The operands of encryption (blockIdx.z: v, then the two key polynomials; decryption has v
+// alone), one thread per word.  [v]_(2^logq) of small signed coefficients: limb 0 holds v
+// mod 2^32, higher limbs the sign extension; of a key polynomial the low L limb rows; the
+// top limb masked to logq bits.
+__global__ __launch_bounds__(256) void operands_kernel(const int8_t* __restrict__ v, const uint32_t* __restrict__ b,
+                                                       const uint32_t* __restrict__ a, uint32_t* __restrict__ out,
+                                                       int N, int L, uint32_t topmask) {
   const int j = blockIdx.x * 256 + threadIdx.x;
   const int l = blockIdx.y;
   if (j >= N) return;
-  const int32_t x = v[j];
-  uint32_t w = l == 0 ? (uint32_t)x : (x < 0 ? 0xFFFFFFFFu : 0u);
+  const long long at = (long long)l * N + j;
+  uint32_t w;
+  if (blockIdx.z == 0) {
+    const int32_t x = v[j];
+    w = l == 0 ? (uint32_t)x : (x < 0 ? 0xFFFFFFFFu : 0u);
+  } else {
+    w = (blockIdx.z == 1 ? b : a)[at];
+  }
   if (l == L - 1) w &= topmask;
-  out[(long long)l * N + j] = w;
+  out[(long long)blockIdx.z * L * N + at] = w;
 }
 
-// The low L limb rows of a polynomial, the top one masked: [x]_(2^logq).
-__global__ __launch_bounds__(256) void mask_rows_kernel(const uint32_t* __restrict__ in, uint32_t* __restrict__ out,
-                                                        int N, int L, uint32_t topmask) {
+// Per component i < n: out_i = [x_i + y_i + mult * e_i]_(2^logq); y_i and e_i may be null.
+// The signed addend is taken in two's complement over all limbs; one carry chain per
+// coefficient.  A thread does its coefficient's components in turn, so an output may take
+// the place of a later component's y.  Bounded by latency (a few rows, 64 workgroups at
+// N = 2^14): both components of an encryption in one launch.  With the operands in one
+// launch and v lifted once for both products, encryption and decryption at N = 2^14, 438
+// bits went from 14 launches and 69.0 us to 10 and 62.6.
+__global__ __launch_bounds__(256) void add_small_kernel(const AddSmallArgs a) {
   const int j = blockIdx.x * 256 + threadIdx.x;
-  const int l = blockIdx.y;
-  if (j >= N) return;
-  uint32_t w = in[(long long)l * N + j];
-  if (l == L - 1) w &= topmask;
-  out[(long long)l * N + j] = w;
-}
-
-// out = [x + y + mult * e]_(2^logq); y and e may be null.  The signed addend is
-// taken in two's complement over all limbs; one carry chain per coefficient.
-__global__ __launch_bounds__(256) void add_small_kernel(const uint32_t* __restrict__ x, const uint32_t* __restrict__ y,
-                                                        const int32_t* __restrict__ e, long long mult,
-                                                        uint32_t* __restrict__ out, int N, int L, uint32_t topmask) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= N) return;
-  const long long s = e ? mult * (long long)e[j] : 0;
-  const uint32_t ext = s < 0 ? 0xFFFFFFFFu : 0u;
-  uint64_t carry = 0;
-  const LimbRows xr(x, L, N, j), yr(y ? y : x, y ? L : 0, N, j);
-  for (int l0 = 0; l0 < L; l0 += kLimbBlock) {
-    uint32_t xv[kLimbBlock], yv[kLimbBlock];
-    xr.block(xv, l0);
-    yr.block(yv, l0);
+  if (j >= a.N) return;
+  const int N = a.N, L = a.L;
 #pragma unroll
-    for (int b = 0; b < kLimbBlock; ++b) {
-      const int l = l0 + b;
-      if (l >= L) break;
-      const uint32_t a = l == 0 ? (uint32_t)s : (l == 1 ? (uint32_t)((unsigned long long)s >> 32) : ext);
-      const uint64_t t = (uint64_t)xv[b] + yv[b] + a + carry;
-      uint32_t w = (uint32_t)t;
-      carry = t >> 32;
-      if (l == L - 1) w &= topmask;
-      out[(long long)l * N + j] = w;
+  for (int i = 0; i < 2; ++i) {
+    if (i >= a.n) break;
+    const uint32_t *const x = i ? a.x1 : a.x0, *const y = i ? a.y1 : a.y0;
+    const int32_t* const e = i ? a.e1 : a.e0;
+    uint32_t* const out = i ? a.out1 : a.out0;
+    const long long s = e ? a.mult * (long long)e[j] : 0;
+    const uint32_t ext = s < 0 ? 0xFFFFFFFFu : 0u;
+    uint64_t carry = 0;
+    const LimbRows xr(x, L, N, j), yr(y ? y : x, y ? L : 0, N, j);
+    for (int l0 = 0; l0 < L; l0 += kLimbBlock) {
+      uint32_t xv[kLimbBlock], yv[kLimbBlock];
+      xr.block(xv, l0);
+      yr.block(yv, l0);
+#pragma unroll
+      for (int b = 0; b < kLimbBlock; ++b) {
+        const int l = l0 + b;
+        if (l >= L) break;
+        const uint32_t w0 = l == 0 ? (uint32_t)s : (l == 1 ? (uint32_t)((unsigned long long)s >> 32) : ext);
+        const uint64_t t = (uint64_t)xv[b] + yv[b] + w0 + carry;
+        uint32_t w = (uint32_t)t;
+        carry = t >> 32;
+        if (l == L - 1) w &= a.topmask;
+        out[(long long)l * N + j] = w;
+      }
     }
   }
 }
@@ -1339,19 +1348,14 @@ __global__ __launch_bounds__(256) void bitrev_kernel(uint32_t* __restrict__ data
   }
 }
 
-hipError_t launch_small_to_limbs(const int8_t* v, uint32_t* out, int N, int L, uint32_t topmask, hipStream_t st) {
-  hipLaunchKernelGGL(small_to_limbs_kernel, dim3((N + 255) / 256, L), dim3(256), 0, st, v, out, N, L, topmask);
+hipError_t launch_operands(const int8_t* v, const uint32_t* b, const uint32_t* a, uint32_t* out, int N, int L,
+                           uint32_t topmask, hipStream_t st) {
+  hipLaunchKernelGGL(operands_kernel, dim3((N + 255) / 256, L, b ? 3 : 1), dim3(256), 0, st, v, b, a, out, N, L, topmask);
   return hipGetLastError();
 }
 
-hipError_t launch_mask_rows(const uint32_t* in, uint32_t* out, int N, int L, uint32_t topmask, hipStream_t st) {
-  hipLaunchKernelGGL(mask_rows_kernel, dim3((N + 255) / 256, L), dim3(256), 0, st, in, out, N, L, topmask);
-  return hipGetLastError();
-}
-
-hipError_t launch_add_small(const uint32_t* x, const uint32_t* y, const int32_t* e, long long mult, uint32_t* out,
-                            int N, int L, uint32_t topmask, hipStream_t st) {
-  hipLaunchKernelGGL(add_small_kernel, dim3((N + 255) / 256), dim3(256), 0, st, x, y, e, mult, out, N, L, topmask);
+hipError_t launch_add_small(const AddSmallArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL(add_small_kernel, dim3((a.N + 255) / 256), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

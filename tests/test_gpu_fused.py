@@ -74,6 +74,27 @@ def test_ring_mul_fused(ctx, logN, logq, cnum):
         check(ints(got[c]), ring.ring_mul(ints(a[c]), ints(b[c]), 1 << logq), f"ring_mul {c}")
 
 
+# one limb, a block of 16 limb rows, and one row more; the second component in m's place
+@pytest.mark.parametrize("logN,logq", [(10, 20), (10, 512), (11, 513)])
+def test_encrypt_fused(ctx, logN, logq):
+    import torch
+    say(f"encrypt fused logN={logN} logq={logq}")
+    N, L = 1 << logN, synth.nlimbs(logq)
+    rng = np.random.default_rng(9 * logN + logq)
+    pk = synth.uniform_limbs(rng, 32 * L, N, count=2)  # bits above logq, which do not count
+    m = synth.uniform_limbs(rng, logq, N)
+    v = rng.integers(-1, 2, N).astype(np.int8)
+    e = rng.integers(-(1 << 31), 1 << 31, (2, N)).astype(np.int32)
+    v[:4], e[:, :2] = -1, [-(1 << 31), (1 << 31) - 1]
+    c0, dm = dev(np.zeros((L, N), dtype=np.uint32)), dev(m)
+    ctx.encrypt(fhe.CKKS, 0, logN, logq, dev(pk[0]), dev(pk[1]), dm,
+                *(torch.from_numpy(x.copy()).cuda() for x in (v, *e)), c0, dm)
+    for i, got in enumerate((host(c0, (L, N)), host(dm, (L, N)))):
+        prod = ring.ring_mul([int(x) % (1 << logq) for x in v], [x % (1 << logq) for x in ints(pk[i])], 1 << logq)
+        add = ints(m) if i == 0 else [0] * N
+        check(ints(got), [(p + a + int(x)) % (1 << logq) for p, a, x in zip(prod, add, e[i])], f"component {i}")
+
+
 def test_bootstrap_same_on_used_memory():
     """The modulus raise clears the limbs above the input's in both components: repeated
     bootstraps, whose buffers hold what earlier work left there, give the same output."""
