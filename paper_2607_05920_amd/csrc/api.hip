@@ -648,6 +648,7 @@ RowsArgs rows_args(fhe_ctx* c, int logN, int K, int cnum) {
   a.tw = c->tw;
   a.itw = c->itw;
   a.pc = c->pc;
+  a.cus = c->cus;
   return a;
 }
 

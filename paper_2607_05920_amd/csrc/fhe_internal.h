@@ -62,6 +62,7 @@ struct RowsArgs {
   const uint32_t* tw = nullptr;    // forward and inverse twiddles, [prime][kNMax]
   const uint32_t* itw = nullptr;
   const PrimeC* pc = nullptr;
+  int cus = 0;                     // compute units
 };
 
 struct LiftArgs {

@@ -279,6 +279,94 @@ __global__ __launch_bounds__(MidRow<S>::THREADS) __attribute__((amdgpu_waves_per
   rows_mid_kernel_body<S, MODE>(cells[c], bk);
 }
 
+// The tensor and ring forms for few rows: a wave for each input polynomial, so that a
+// product's forward transforms run side by side, and then its inverse ones; the values
+// pass through the LDS in between.  Rows of up to 1024 points (N = 2^13 and 2^14), 1024 / n
+// of them per workgroup, so that a wave's threads share a polynomial.
+//
+// What bounds it: at N = 2^14, 438 bits a product has 496 rows for 1024 SIMDs, and a wave's
+// own chain (four forward transforms, the products and three inverse ones, 5 000
+// instructions) sets the time; here the chain is one of each.  Tensor form, us (rows of
+// 2^10): 15.4 -> 10.8 at 496, 24.2 -> 16.0 at 992, 28.7 -> 25.5 at 1984, 46.7 -> 44.8 at
+// 3968; an HE-mult at N = 2^14, 438 bits: 66.5 -> 59.7.
+template <int S, int MODE>
+struct MidSplit {
+  static constexpr int WAVES = MODE == ROWS_TENSOR ? 4 : 2, T = MidRow<S>::T, RPW = 64 / T;
+};
+
+// Where it is taken: rows in units of 1024 points, per compute unit.  Once every SIMD has
+// its four waves of the other form, which loads a row's twiddles once for all polynomials,
+// that one is as fast: ring form 8.0 -> 7.7 us at 496 rows, 11.8 -> 9.7 at 992, 20.2 ->
+// 17.4 at 2976, 21.3 -> 21.4 at 3968; tensor form (above) up to 4096.  The relinearization
+// form, which has one forward transform, gains nothing (11.4 -> 10.9 at 720 rows, 13.1 ->
+// 15.8 at 1440).  A stage-batched plan, whose launches hold several cells' rows, keeps the
+// other form.
+constexpr int mid_split_rows(int mode) { return mode == ROWS_TENSOR ? 16 : (mode == ROWS_RING ? 12 : 0); }
+
+template <int S, int MODE>
+__global__ __launch_bounds__((64 * MidSplit<S, MODE>::WAVES)) void rows_mid_split_kernel(RowsArgs a) {
+  typedef MidRow<S> M;
+  typedef MidSplit<S, MODE> W;
+  constexpr int n = M::n, T = M::T, RPW = W::RPW, ROWS = 16;
+  __shared__ uint32_t lds[W::WAVES][RPW * M::LDS_ROW];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int s = (threadIdx.x & 63) / T, t = threadIdx.x % T;
+  const int N = 1 << a.logN;
+  // the order of the rows over the XCDs as in rows_mid_kernel
+  const int per_prime = a.cnum * (ROWS / RPW), total = a.K * per_prime, chunk = (total + 7) / 8;
+  const int li = blockIdx.x >> 3, item = (blockIdx.x & 7) * chunk + li;
+  if (li >= chunk || item >= total) return;  // whole workgroup exits
+  const int p = item / per_prime, rem = item % per_prime;
+  const int c = rem % a.cnum, row0 = (rem / a.cnum) * RPW;
+  const Mod Q(a.pc[p]);
+  const uint32_t q = Q.q, two_q = Q.two_q, qneg = Q.qneg;
+  const TwTab tw = tw_table(a.tw, p), itw = tw_table(a.itw, p);
+  const int mult = ROWS + row0 + s;
+  const long long KN = (long long)a.K * N;
+  const long long base = (long long)p * N + (long long)row0 * n;
+  const uint32_t lane = 4u * (uint32_t)(s * n + t);
+  const uint32_t bytes = 4u * RPW * n;
+  uint32_t* const lb[1] = {lds[wave] + s * M::LDS_ROW};
+  // this thread's element u of the wave r's polynomial, between the transforms
+  auto at = [&](int r, int u) -> uint32_t& { return lds[r][s * M::LDS_ROW + 17 * t + u]; };
+
+  const uint32_t* src = a.data + (long long)c * a.group_stride;
+  if (MODE == ROWS_TENSOR) src += wave * KN;
+  if (MODE == ROWS_RING && wave == 1) src = a.data2 + (long long)(c % a.data2_groups) * a.data2_stride;
+  const __amdgpu_buffer_rsrc_t ri = row_buffer(wave_uniform(src + base), bytes);
+  uint32_t x[1][16];
+#pragma unroll
+  for (int u = 0; u < 16; ++u) x[0][u] = __builtin_amdgcn_raw_buffer_load_b32(ri, (int)lane, 4 * u * T, 0);
+  mid_forward<S, 1, 1>(x, lb, t, tw, mult, Q);
+#pragma unroll
+  for (int u = 0; u < 16; ++u) at(wave, u) = x[0][u];
+  Tw16 w2;
+  load_phase_tw<S, 2>(w2, itw, mult, t);
+  __syncthreads();
+  if (MODE == ROWS_TENSOR) {
+    if (wave == 1) {
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+        x[0][u] = csub(redc_lazy(mad64(at(0, u), at(3, u), mad64(x[0][u], at(2, u), 0)), q, qneg), two_q);
+    } else if (wave != 3) {
+      const int l = wave == 0 ? 0 : 1;  // d0 = x0 x2, d2 = x1 x3
+#pragma unroll
+      for (int u = 0; u < 16; ++u) x[0][u] = redc_lazy(mad64(at(l, u), at(l + 2, u), 0), q, qneg);
+    }
+    __syncthreads();  // every wave's values have been read
+    if (wave == 3) return;
+  } else {
+    if (wave == 1) return;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) x[0][u] = redc_lazy(mad64(x[0][u], at(1, u), 0), q, qneg);
+  }
+  mid_inverse<S, 1, 1>(x, lb, t, itw, mult, Q, w2);
+  uint32_t* const dst = a.data + (long long)c * a.group_stride + (MODE == ROWS_TENSOR ? wave * KN : 0);
+  const __amdgpu_buffer_rsrc_t ro = row_buffer(wave_uniform(dst + base), bytes);
+#pragma unroll
+  for (int u = 0; u < 16; ++u) __builtin_amdgcn_raw_buffer_store_b32(x[0][u], ro, (int)lane, 4 * u * T, 0);
+}
+
 template <int S, int MODE>
 static hipError_t rows_mid(const RowsArgs& a, hipStream_t st) {
   const int total = a.K * a.cnum * (16 / MidRow<S>::RPW);
@@ -287,6 +375,14 @@ static hipError_t rows_mid(const RowsArgs& a, hipStream_t st) {
   const double rows = MODE == ROWS_TENSOR ? 7.0 * a.cnum
                                           : (MODE == ROWS_RELIN ? 3.0 * a.cnum + 2.0 : 2.0 * a.cnum + b_rows);
   Bracket br(KID_ROWS_FUSED, st, 4.0 * rows * a.K * (double)(1 << a.logN));
+  if constexpr (S <= 10 && mid_split_rows(MODE) > 0) {
+    typedef MidSplit<S, MODE> W;
+    const int items = a.K * a.cnum * (16 / W::RPW);
+    if (!launch_sink() && items <= mid_split_rows(MODE) * a.cus) {
+      hipLaunchKernelGGL((rows_mid_split_kernel<S, MODE>), dim3(8 * ((items + 7) / 8)), dim3(64 * W::WAVES), 0, st, a);
+      return hipGetLastError();
+    }
+  }
   const hipError_t e = emit((const void*)rows_mid_kernel<S, MODE>, (const void*)rows_mid_kernel_multi<S, MODE>,
                             dim3(8 * ((total + 7) / 8)), dim3(MidRow<S>::THREADS), 0, st, a);
   return e != hipSuccess ? e : hipGetLastError();

@@ -95,6 +95,45 @@ def test_encrypt_fused(ctx, logN, logq):
         check(ints(got), [(p + a + int(x)) % (1 << logq) for p, a, x in zip(prod, add, e[i])], f"component {i}")
 
 
+# the ciphertext counts on both sides of the line where a row's polynomials share a wave (16
+# rows of 1024 points per compute unit for the HE-mult, 12 for the ring product): one more
+# than the line takes the other form for all
+@pytest.mark.parametrize("logN,logq", [(13, 218), (14, 100)])
+def test_rows_split(ctx, logN, logq):
+    import torch
+    say(f"rows split logN={logN} logq={logq}")
+    N, L = 1 << logN, synth.nlimbs(logq)
+    rng = np.random.default_rng(11 * logN + logq)
+    per = ((2 * logq + logN) // 30 + 1) * (N >> 10)  # rows of 1024 points per ciphertext, about
+    most = 16 * torch.cuda.get_device_properties(0).multi_processor_count // per + 8
+    x = [synth.uniform_limbs(rng, logq, N, count=most) for _ in range(4)]
+    top = limbs_of([(1 << logq) - 1], logq)[:, 0]
+    for v in x:
+        v[0, :, :] = top[:, None]
+    key = fhe.EvalKey(ctx, fhe.CKKS, 0, logN, logq, logq, synth.uniform_limbs(rng, 2 * logq, N),
+                      synth.uniform_limbs(rng, 2 * logq, N))
+
+    def mult(n, first=0):
+        out = [dev(np.zeros((n, L, N), dtype=np.uint32)) for _ in range(2)]
+        ctx.mul_relin(key, logq, *(dev(v[first:first + n]) for v in x), *out, cnum=n)
+        return np.stack([host(o, (n, L, N)) for o in out])
+
+    def ring_mul(n, first=0):
+        out = dev(np.zeros((n, L, N), dtype=np.uint32))
+        ctx.ring_mul(logN, logq, dev(x[0][first:first + n]), dev(x[1][first:first + n]), out, cnum=n)
+        return host(out, (1, n, L, N))
+
+    try:
+        for f in (mult, ring_mul):
+            want = f(most)  # the other form
+            for i in (0, 1, most - 1):
+                assert np.array_equal(f(1, i), want[:, i:i + 1]), f"{f.__name__} {i}"
+            for n in range(3, most, 4):
+                assert np.array_equal(f(n), want[:, :n]), f"{f.__name__} of {n}"
+    finally:
+        key.close()
+
+
 def test_bootstrap_same_on_used_memory():
     """The modulus raise clears the limbs above the input's in both components: repeated
     bootstraps, whose buffers hold what earlier work left there, give the same output."""
