@@ -181,8 +181,7 @@ int fhe_ring_mul_noalloc(fhe_ctx* ctx, int logN, int logq, const uint32_t* a, co
  * b_host, a_host are host uint32[L_PQ][N], L_PQ = ceil((logP + logQ_key) / 32).
  * The library keeps a host copy of the limbs and, per ciphertext level logq used
  * with it, the NTT form of the key reduced mod P * 2^logq resident on the device
- * (built on first use or by fhe_evk_prepare; 2 K_r N words, plus a second layout
- * for odd logN).  *out is library-owned; release with fhe_evk_destroy.
+ * (built on first use or by fhe_evk_prepare; 2 K_r N words).  *out is library-owned; release with fhe_evk_destroy.
  * scheme is FHE_CKKS or FHE_BGV; t (odd, 3 <= t < 2^24, so that the t-corrected
  * divisions' sums stay within 64 bits) is read for BGV only.
  * Errors: FHE_E_INVAL, FHE_E_RANGE (logQ_key > logQ_max or logP > logP_max),

@@ -1795,7 +1795,7 @@ int fhe_ntt(fhe_ctx* c, int logN, int prime0, int nprimes, int flags, uint32_t* 
   a.tw += (long long)prime0 * kNMax;
   a.pc += prime0;
   hipError_t e = hipSuccess;
-  if (ntt_whole_wanted(logN, natural, rows))
+  if (ntt_whole_wanted(logN, natural, rows, c->cus))
     return set_sticky(c, launch_ntt_whole(a, (int)rows, inverse, natural, st));
   if (inverse && natural) e = launch_bitrev(data, logN, rows, st);
   if (e == hipSuccess) e = launch_ntt(a, (int)rows, inverse, st);

@@ -50,7 +50,7 @@ __device__ __forceinline__ uint32_t buffer_word(__amdgpu_buffer_rsrc_t r, uint32
 // Limb rows of one coefficient per lane.  The limb-serial kernels read their rows a block of
 // kLimbBlock at a time: all of a block's loads are in flight together, where a load per limb
 // inside the carry chain waited for memory limb by limb (2^14 coefficients, 32 limbs, a sum:
-// 9.6 us a launch; with blocks 5.4).  Rows at or beyond the buffer's end read as zero.
+// 9.6 us a launch; with blocks 4.9).  Rows at or beyond the buffer's end read as zero.
 constexpr int kLimbBlock = 16;
 struct LimbRows {
   __amdgpu_buffer_rsrc_t r;

@@ -278,7 +278,7 @@ hipError_t launch_ntt(const NttArgs& a, int ntransforms, bool inverse, hipStream
 // The same with one workgroup per transform (one pass over memory); natural: the
 // transformed side in natural instead of bit-reversed order.  The inverse needs a.scale.
 hipError_t launch_ntt_whole(const NttArgs& a, int ntransforms, bool inverse, bool natural, hipStream_t s);
-bool ntt_whole_wanted(int logN, bool natural, long long ntransforms);
+bool ntt_whole_wanted(int logN, bool natural, long long ntransforms, int cus);
 // Ring products split their transforms as 16 x N / 16: the four outer stages in the lift (or,
 // launch_cols16, after it) and the reconstruction, and the fused pass over rows of N / 16
 // points between them.

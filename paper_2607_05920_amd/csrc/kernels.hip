@@ -29,11 +29,13 @@ void bracket_end(int kid, hipStream_t s, double work) {
 // Negacyclic transforms (Section 2.3, Eq. negacyclic_ntt / negacyclic_intt) with
 // the psi-twist merged into the twiddles (Section 5.1): the forward transform is
 // the Cooley-Tukey network whose stage with m groups uses psi^bitrev(m + i) for
-// group i and leaves the output in bit-reversed order; the inverse is the mirrored
+// group i and leaves the output in bit-reversed order; the inverse is the reverse
 // Gentleman-Sande network with psi^-bitrev(h + i), then the factor N^-1.
 //
-// N = 2^logN is split as N = n1 * n2 (the two-pass / four-step scheme of Section
-// 5.3).  The n1-point stages run over columns {c + n2 u}; the n2-point stages run
+// These two passes serve key preparation and the standalone transforms that do not take
+// one workgroup each (ntt_whole.hip); the ring products have the outer four stages in the
+// lift and the reconstruction (lift_cols.hip, crt_cols.hip).  N = 2^logN is split as
+// N = n1 * n2 (the two-pass / four-step scheme of Section 5.3).  The n1-point stages run over columns {c + n2 u}; the n2-point stages run
 // over contiguous blocks.  Both passes use one kernel shape: a sub-transform of
 // n = 2^S points is held by T = n / 16 threads with 16 values each.  The first
 // register phase works on elements {u T + j} ("strided"), the other on
@@ -46,8 +48,7 @@ void bracket_end(int kid, hipStream_t s, double work) {
 template <int S, bool ROWS>
 constexpr int ntt_pass_threads() { return ROWS ? 256 : (S >= 8 ? 1024 : (S == 7 ? 512 : 256)); }
 
-// BLK: threads per workgroup (the autotuner may take fewer columns per workgroup than
-// ntt_pass_threads gives).  CG (row passes of 256 points over transforms one group
+// BLK: threads per workgroup.  CG (row passes of 256 points over transforms one group
 // apart): the four 16-lane slots of a wave take one block of four consecutive
 // transforms of a prime, so that its twiddles are wave-uniform (scalar loads) and
 // read once for four transforms.
@@ -413,7 +414,8 @@ __device__ __forceinline__ void inv_rows(uint32_t (&x)[NP][16], uint32_t* const 
   }
 }
 
-// Rows per workgroup of the fused pass: 8 rows of 256 points (128 threads).  The LDS
+// The fused pass over rows of up to 256 points (N <= 2^12; longer ones: rows_mid.hip).
+// Rows per workgroup: 8 rows of 256 points (128 threads).  The LDS
 // transposes of the tensor and ring forms go through kRowsBuffers buffers of 8 rows, as
 // many rows at a time: with the registers of 3 waves per SIMD (168), 6 workgroups of 2
 // buffers fit in the LDS.  The relinearization form (under 96 registers) takes one

@@ -19,8 +19,13 @@ namespace fhe {
 // The LDS holds two exchange buffers and two steps' table fragments: one barrier per step,
 // the stages a step behind the products.
 //
-// What bounds it: at 16 waves of 128 registers the limbs, accumulators and a fragment just
-// fit up to 7 k-blocks (56 limbs); larger ones take the separate lift and column pass.
+// What bounds it: instruction issue (the VALU about 75% busy between the barriers, the
+// matrix instructions beside it) and, in the first quarter of a block, its limbs' loads.  At
+// 16 waves of 128 registers the limbs, accumulators and a fragment just fit up to 7 k-blocks
+// (56 limbs); larger ones take the separate lift and column pass.  2^16 coefficients, 49
+// limbs, 106 primes, 16 polynomials: 221 us; the separate lift and column pass of eight
+// stages took 146 and 161 (the other four stages are in the middle pass now, which went from
+// 256 to 323).
 template <int NKB>
 __device__ __forceinline__ void lift_cols_kernel_body(const LiftArgs& a, const Blk bk) {
   constexpr int XS = 16 * 64 + 8;  // words per prime: the lane halves' stores fall on different banks

@@ -17,8 +17,8 @@ namespace fhe {
 // What bounds it: 2^13 and 2^14 points move 2.4-3.7 TB/s (read + write) with two or more
 // workgroups per compute unit, VALU issue and the exchanges together.  2^16 points fill one
 // compute unit (1024 threads x 64 values; the LDS takes half a transform at a time, so an
-// exchange runs in two rounds): 29 us of VALU issue, and loads and stores that nothing
-// overlaps.
+// exchange runs in two rounds): about 26 us of VALU issue of 46 a transform, and loads and
+// stores that nothing overlaps.
 template <int LG, int V>
 struct Whole {
   static constexpr int R = 1 << V, T = 1 << (LG - V);
@@ -171,21 +171,28 @@ struct Whole {
     }
   }
 
-  // Natural order: through LDS at the reversed positions.  A round holds one half of the
-  // natural order, i.e. the elements of one parity.
-  template <bool STORE>
-  static __device__ __forceinline__ void natural(uint32_t (&x)[R], uint32_t* lds, __amdgpu_buffer_rsrc_t rb, int t) {
+  // Through LDS, so that memory sees runs of lanes: natural order (NAT) at the reversed
+  // positions, where a round holds one half of the natural order, i.e. the elements of one
+  // parity; or the transform's own order, where a round holds the registers of one half.
+  // The own order takes it where a thread's runs of 32 elements would go out 16 bytes a lane
+  // (2^16, 106 x 64: 1413 -> 1216 us; 2^15 forward, 106 x 16: 151 -> 137; its inverse, which
+  // loads whole lines either way, 147 without it).
+  template <bool STORE, bool NAT>
+  static __device__ __forceinline__ void through(uint32_t (&x)[R], uint32_t* lds, __amdgpu_buffer_rsrc_t rb, int t) {
     constexpr int I = NPH - 1, half = (1 << LG) / HALVES;
     static_assert(HALVES == 1 || G(I) % 2 == 0, "an element's parity is its register's");
+    static_assert(NAT || R / G(I) == HALVES, "a thread's runs are one per round");
     uint32_t* const ln = lds + pad(t);
-    uint32_t* const lv = lds + pad((int)(__brev((unsigned)elem<I>(0, t)) >> (32 - LG)));
+    uint32_t* const lv = lds + pad(NAT ? (int)(__brev((unsigned)elem<I>(0, t)) >> (32 - LG)) : elem<I>(0, t));
+    auto in = [](int r, int h) { return HALVES == 1 || (NAT ? r % 2 : r / RH) == h; };
+    auto at = [](int r, int h) { return pad((NAT ? rev(elem<I>(r, 0)) : elem<I>(r, 0)) - h * half); };
 #pragma unroll
     for (int h = 0; h < HALVES; ++h) {
       if (STORE || h > 0) __syncthreads();  // the LDS's previous contents have been read
       if (STORE) {
 #pragma unroll
         for (int r = 0; r < R; ++r)
-          if (HALVES == 1 || r % 2 == h) lv[pad(rev(elem<I>(r, 0)) - h * half)] = x[r];
+          if (in(r, h)) lv[at(r, h)] = x[r];
         __syncthreads();
 #pragma unroll
         for (int r = 0; r < RH; ++r)
@@ -199,7 +206,7 @@ struct Whole {
         __syncthreads();
 #pragma unroll
         for (int r = 0; r < R; ++r)
-          if (HALVES == 1 || r % 2 == h) x[r] = lv[pad(rev(elem<I>(r, 0)) - h * half)];
+          if (in(r, h)) x[r] = lv[at(r, h)];
       }
     }
     if (!STORE) __syncthreads();
@@ -251,10 +258,10 @@ __global__ __launch_bounds__((Whole<LG, V>::T)) void ntt_whole_kernel(NttArgs a)
     W::template forward_from<0>(x, lds, tw, t, M);
 #pragma unroll
     for (int r = 0; r < W::R; ++r) x[r] = csub(fwd_lift(x[r], M), q);
-    if (NAT) W::template natural<true>(x, lds, rb, t);
+    if constexpr (NAT || V >= 5) W::template through<true, NAT>(x, lds, rb, t);
     else W::template runs<true>(x, rb, t);
   } else {
-    if (NAT) W::template natural<false>(x, lds, rb, t);
+    if constexpr (NAT || V == 6) W::template through<false, NAT>(x, lds, rb, t);
     else W::template runs<false>(x, rb, t);
     W::template inverse_from<W::NPH - 1>(x, lds, tw, t, M);
     // the last stage with the final factor folded in, as in the two-pass form
@@ -287,18 +294,22 @@ static hipError_t ntt_whole_dir(const NttArgs& a, bool inverse, bool natural, hi
 // Where one workgroup per transform is the faster form (us, two passes [and the permutation]
 // against one; N, primes x polynomials):
 //   up to 2^14 always: 2^10, 106 x 64: 69 -> 16, natural order 108 -> 16; 2^13, 31 x 16:
-//   20.7 -> 13.0, natural 77 -> 14; 2^14, 9 x 1: 10.6 -> 9.4, 106 x 64: 452 -> 243.
-//   2^15: a transform takes 20 us on its one compute unit, so few of them are faster in two
-//   passes over many: 5 x 1: 10 against 20, 31 x 4: 21 against 24, 31 x 8: 32 against 28.
-//   Natural order adds a permutation pass to the two: 5 x 1: 14 against 19, 31 x 4: 52
-//   against 23.
-//   2^16: 40 us on its compute unit (56 with the others' memory traffic), no faster than two
-//   passes at the copy rate (106 x 64: 1544 against 1484), but natural order is: 31 x 4: 92
-//   against 54, 106 x 64: 6798 against 1604; 5 x 1: 17 against 42.
-bool ntt_whole_wanted(int logN, bool natural, long long ntransforms) {
+//   20.7 -> 13.0, natural 77 -> 13; 2^14, 9 x 1: 10.6 -> 9.4, 106 x 64: 452 -> 243.
+//   2^15: a transform takes 18 us on its one compute unit, so few of them are faster in two
+//   passes over many: 31 x 2: 14.7 against 18.8, 31 x 4: 21.1 against 20.5 (inverse 18.6
+//   against 19.8), 31 x 6: 27.9 against 21.0.  Natural order adds a permutation pass to the
+//   two: 5 x 1: 14 against 19, 31 x 4: 52 against 20.
+//   2^16: 46 us a round of one transform per compute unit, against 50 of two passes (54
+//   beyond the last-level cache): faster where the last round is nearly full or one of
+//   many: 31 x 8: 54.1 -> 50.1, 32 x 12 (1.5 rounds): 76.8 against 88.6, 32 x 16: 96.8 ->
+//   93.4, 53 x 16 (3.3 rounds): 153 against 172, 106 x 16 (6.6): 350 -> 340, 106 x 64: 1474
+//   -> 1216.  Natural order: 31 x 4: 92 -> 41, 106 x 64: 6798 -> 1233; 5 x 1: 17 against 42.
+bool ntt_whole_wanted(int logN, bool natural, long long ntransforms, int cus) {
   if (logN <= 14) return true;
-  if (logN == 15) return ntransforms >= (natural ? 32 : 224);
-  return natural && ntransforms >= 64;
+  if (logN == 15) return ntransforms >= (natural ? 32 : 160);
+  if (natural) return ntransforms >= 64;
+  const long long slots = (ntransforms + cus - 1) / cus * cus;  // at most one in 16 idle, or 8 full rounds
+  return ntransforms > 8LL * cus || 15 * slots <= 16 * ntransforms;
 }
 
 hipError_t launch_ntt_whole(const NttArgs& a0, int ntr, bool inverse, bool natural, hipStream_t st) {
@@ -315,8 +326,7 @@ hipError_t launch_ntt_whole(const NttArgs& a0, int ntr, bool inverse, bool natur
     case 14: return ntt_whole_dir<14, 4>(a, inverse, natural, st);
     case 15: return ntt_whole_dir<15, 5>(a, inverse, natural, st);
     case 16:
-      if (!natural) return hipErrorInvalidValue;  // ntt_whole_wanted
-      return inverse ? ntt_whole<16, 6, true, true>(a, st) : ntt_whole<16, 6, false, true>(a, st);
+      return ntt_whole_dir<16, 6>(a, inverse, natural, st);
     default: return hipErrorInvalidValue;
   }
 }

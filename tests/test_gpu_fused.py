@@ -27,7 +27,8 @@ def ctx():
 # 2^15 and 2^16 points
 @pytest.mark.parametrize("logN,nprimes,count,natural", [
     (10, 1, 1, True), (10, 3, 11, False), (11, 5, 3, True), (12, 3, 5, True), (13, 9, 1, False), (13, 3, 7, True),
-    (14, 1, 1, True), (14, 5, 5, False), (15, 4, 8, True), (15, 7, 32, False), (16, 4, 16, True)])
+    (14, 1, 1, True), (14, 5, 5, False), (15, 4, 8, True), (15, 5, 32, False),
+    (15, 7, 32, False), (16, 4, 16, True), (16, 4, 60, False), (16, 3, 85, False)])
 def test_ntt_whole(ctx, logN, nprimes, count, natural):
     say(f"ntt whole logN={logN} primes={nprimes} count={count} natural={natural}")
     prime0, N = 2, 1 << logN
