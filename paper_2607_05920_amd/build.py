@@ -35,7 +35,9 @@ def build(verbose: bool = False) -> str:
 
     with tempfile.TemporaryDirectory() as tmp:
         objs = [os.path.join(tmp, s + ".o") for s in SOURCES]
-        jobs = [[hipcc(), *flags, "-c", "-o", o, os.path.join(HERE, "csrc", s)] for s, o in zip(SOURCES, objs)]
+        # -cuid: the same code objects for the same sources, whatever the temporary folder is called
+        jobs = [[hipcc(), *flags, "-cuid=" + s.split(".")[0], "-c", "-o", o, os.path.join(HERE, "csrc", s)]
+                for s, o in zip(SOURCES, objs)]
         with ThreadPoolExecutor(min(len(jobs), os.cpu_count() or 1)) as pool:
             res = list(pool.map(run, jobs))
         if all(r.returncode == 0 for r in res):
