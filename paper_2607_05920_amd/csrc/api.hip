@@ -992,7 +992,8 @@ int plan_run_cells(fhe_plan* pl, hipStream_t st) {
 // the median of three runs) and keeps the fastest.
 // Stage-batched plan: each cell's pipeline is recorded (a LaunchSink: nothing runs),
 // every cell with scratch of its own; then step s of every cell's pipeline, which is
-// the same stage of the same pipeline for all cells, becomes one launch per graph
+// the same stage of the same pipeline for all cells (an empty record where a cell's
+// kernels do that stage's work in the step before), becomes one launch per graph
 // branch and kernel variant (template instance and workgroup) over the cells that use
 // it (queue_layout.h: the grouping, the cells' order, and the segments, each cell's
 // grid rounded up to a multiple of 8 workgroups so that every workgroup keeps the XCD

@@ -246,7 +246,9 @@ struct CellSeg {
 
 // A launch as recorded instead of issued while a sink is installed: the entry point
 // that runs it as one cell of a stage-batched launch, its grid, workgroup, dynamic LDS
-// and argument struct (raw bytes; every entry point takes one struct).
+// and argument struct (raw bytes; every entry point takes one struct).  A record without an
+// entry point keeps the place of a step whose work this cell's other kernels do: the
+// launchers record the same number of steps whatever form they take.
 struct LaunchRec {
   const void* multi = nullptr;
   dim3 grid, block;

@@ -174,6 +174,7 @@ static hipError_t lift_cols(const LiftArgs& b, hipStream_t st) {
   const int units = b.npoly * (b.N >> 10);
   (void)emit((const void*)lift_cols_kernel<NKB>, (const void*)lift_cols_kernel_multi<NKB>,
              dim3(8 * ((units + 7) / 8) * b.nsplit), dim3(1024), 0, st, b);
+  if (LaunchSink* sink = launch_sink()) sink->recs.emplace_back();  // the place of the separate column pass
   return hipGetLastError();
 }
 

@@ -1,8 +1,9 @@
 // Layout of stage-batched launches (host only, no HIP types).
 //
-// A stage-batched batch plan records every cell's pipeline (one launch per step, the
-// same steps for every cell) and runs step s of all cells together: one launch per
-// (graph branch, kernel variant) over the cells of that branch using that variant.
+// A stage-batched batch plan records every cell's pipeline (the same steps for every cell,
+// each of one launch, or of none where the cell's kernels do that step's work in another)
+// and runs step s of all cells together: one launch per (graph branch, kernel variant)
+// over the cells of that branch using that variant.
 // This header decides which cells go into which launch and where each cell's
 // workgroups sit in it; the device side finds a workgroup's cell by a binary search
 // over the segment offsets (cell_of in the kernels).
@@ -14,7 +15,7 @@
 namespace fhe {
 
 // One recorded launch: its kernel variant (entry point and workgroup shape), grid, and
-// the graph branch of its cell.
+// the graph branch of its cell.  A null variant: the cell launches nothing at this step.
 struct QRec {
   const void* variant = nullptr;
   uint32_t bx = 0, by = 0, bz = 0;  // workgroup shape
@@ -39,10 +40,10 @@ struct QLaunch {
 enum { QL_OK = 0, QL_MISMATCH = 1, QL_TOO_BIG = 2 };
 
 // recs[c][s]: cell c's launch at step s.  Launches come out step by step; within a
-// step, cells are visited in order for even steps and in reverse for odd ones (a step
-// then starts on the cells whose data the step before wrote last), and each launch
-// takes, from its first cell on in that order, every cell of the same branch and
-// variant.  Rounding each segment to 8 workgroups keeps a workgroup on the XCD
+// step, cells are visited in order and in reverse for every other step that launches
+// anything (a step then starts on the cells whose data the step before wrote last), and
+// each launch takes, from its first cell on in that order, every cell of the same branch
+// and variant.  Rounding each segment to 8 workgroups keeps a workgroup on the XCD
 // (blockIdx mod 8) its own launch would give it.
 inline int queue_layout(const std::vector<std::vector<QRec>>& recs, std::vector<QLaunch>* out) {
   out->clear();
@@ -51,10 +52,13 @@ inline int queue_layout(const std::vector<std::vector<QRec>>& recs, std::vector<
   const size_t nsteps = recs[0].size();
   for (size_t c = 1; c < nc; ++c)
     if (recs[c].size() != nsteps) return QL_MISMATCH;
+  bool reverse = false;
   for (size_t s = 0; s < nsteps; ++s) {
     std::vector<size_t> ord(nc);
-    for (size_t i = 0; i < nc; ++i) ord[i] = (s & 1) ? nc - 1 - i : i;
-    std::vector<char> done(nc, 0);
+    for (size_t i = 0; i < nc; ++i) ord[i] = reverse ? nc - 1 - i : i;
+    std::vector<char> done(nc);
+    for (size_t c = 0; c < nc; ++c) done[c] = recs[c][s].variant == nullptr;
+    const size_t before = out->size();
     for (size_t i0 = 0; i0 < nc; ++i0) {
       const size_t c0 = ord[i0];
       if (done[c0]) continue;
@@ -84,6 +88,7 @@ inline int queue_layout(const std::vector<std::vector<QRec>>& recs, std::vector<
       L.blocks = (uint32_t)off;
       out->push_back(std::move(L));
     }
+    if (out->size() > before) reverse = !reverse;
   }
   return QL_OK;
 }

@@ -176,3 +176,42 @@ def test_stage_batched_both_schemes_and_levels():
             k.close()
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("flags", [fhe.PLAN_QUEUE, fhe.PLAN_QUEUE | fhe.PLAN_GRAPH,
+                                   fhe.PLAN_QUEUE | fhe.PLAN_GRAPH | fhe.PLAN_AUTOTUNE])
+def test_stage_batched_cells_of_both_lift_forms(flags):
+    """A stage-batched plan whose cells differ in how many launches their lift takes: one up to
+    56 limbs, two above (and with the VALU lift, where the tuner takes it)."""
+    import torch
+    logQ = 1793
+    rk, rm, _, _ = synth.streams(33)
+    say(f"stage-batched, both lift forms flags={flags}")
+    ctx = fhe.Context(logQ, logQ)
+    try:
+        keys = {}
+        for logN in (10, 11):
+            N = 1 << logN
+            keys[logN] = fhe.EvalKey(ctx, fhe.CKKS, 0, logN, logQ, logQ, synth.uniform_limbs(rk, 2 * logQ, N),
+                                     synth.uniform_limbs(rk, 2 * logQ, N))
+        jobs = []
+        for logN, logq in [(10, 1792), (10, 1793), (10, 60), (11, 1793), (10, 1793), (11, 1792)]:
+            N, Lo = 1 << logN, synth.nlimbs(logq - 40)
+            outs = [torch.zeros(Lo * N, dtype=torch.int32, device="cuda") for _ in range(2)]
+            jobs.append((keys[logN], logq, 40, *[dev(synth.uniform_limbs(rm, logq, N)) for _ in range(4)], *outs))
+        ref = per_op(ctx, jobs)
+        plan = fhe.BatchPlan(ctx, jobs, flags=flags)
+        assert plan.info()["cells"] == 5
+        for rep in range(3):
+            for j in jobs:
+                j[7].fill_(rep + 1)
+                j[8].fill_(-rep)
+            plan.run()
+            torch.cuda.synchronize()
+            for (j, (a, b)) in zip(jobs, ref):
+                assert torch.equal(j[7], a) and torch.equal(j[8], b)
+        plan.close()
+        for k in keys.values():
+            k.close()
+    finally:
+        ctx.close()

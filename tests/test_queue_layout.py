@@ -24,3 +24,15 @@ def test_queue_layout(tmp_path):
     assert r.returncode == 0, r.stderr
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and "ALL PASSED" in r.stdout, r.stdout + r.stderr
+
+
+def test_queue_layout_empty_steps(tmp_path):
+    """Cells that launch nothing at a step (their kernels do its work in another)."""
+    if not shutil.which("g++"):
+        pytest.skip("g++ not available")
+    exe = tmp_path / "queue_empty_test"
+    src = os.path.join(ROOT, "tests", "queue_empty_test.cpp")
+    r = subprocess.run(["g++", "-std=c++17", "-O2", "-I", INC, src, "-o", str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and "ALL PASSED" in r.stdout, r.stdout + r.stderr
