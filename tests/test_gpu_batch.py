@@ -215,3 +215,18 @@ def test_stage_batched_cells_of_both_lift_forms(flags):
             k.close()
     finally:
         ctx.close()
+
+
+def test_stage_batched_launches(setup):
+    """The cells of a stage-batched plan share launches: of the eight cells' launches at a step,
+    at most the four of the ring degrees' row lengths are left."""
+    ctx, _, _, jobs, _ = setup
+    say("stage-batched launches")
+    count = {}
+    for flags in (0, fhe.PLAN_QUEUE, fhe.PLAN_QUEUE | fhe.PLAN_GRAPH):
+        plan = fhe.BatchPlan(ctx, jobs, flags=flags)
+        count[flags] = plan.info()["kernels"]
+        plan.close()
+    assert count[0] % 8 == 0
+    assert count[0] // 8 <= count[fhe.PLAN_QUEUE] <= count[0] // 2, count
+    assert count[fhe.PLAN_QUEUE] <= count[fhe.PLAN_QUEUE | fhe.PLAN_GRAPH] < count[0], count
