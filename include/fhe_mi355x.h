@@ -392,11 +392,13 @@ typedef struct {
 /* Bootstrap one CKKS ciphertext (cnum = 1) at logq = logq_in (its logp <= logq_in):
  * out receives the refreshed ciphertext; out->c0, out->c1 must each hold L_Q N words
  * (the output's level is below logQ; the call writes out's metadata).  Allocates its
- * temporaries, which the context keeps for the next call (until it is destroyed, or another
- * size or its scratch needs the memory), and synchronizes `stream` before returning.  Errors: FHE_E_INVAL (null,
- * parameters, a missing key), FHE_E_SHAPE (the input is not a one-ciphertext CKKS tensor
- * at logq_in of ring degree 2^logN), FHE_E_RANGE (levels exhausted: logQ too small for
- * the circuit), plus the errors of the operations. */
+ * temporaries and synchronizes `stream` before returning.  The context keeps up to 48 of
+ * them (4 L_Q N words each) for its next call, where eight times as much memory is free on
+ * the device then; they go back when the context is destroyed, when it bootstraps at
+ * another size, or when any allocation of the library on that device would fail.  Errors:
+ * FHE_E_INVAL (null, parameters, a missing key), FHE_E_SHAPE (the input is not a
+ * one-ciphertext CKKS tensor at logq_in of ring degree 2^logN), FHE_E_RANGE (levels
+ * exhausted: logQ too small for the circuit), plus the errors of the operations. */
 int fhe_ct_bootstrap(fhe_ctx* ctx, const fhe_boot_params* params, const fhe_boot_keys* keys, const fhe_ct* in,
                      fhe_ct* out, void* stream);
 

@@ -20,6 +20,7 @@
 
 #include "fhe_internal.h"
 #include "fhe_mi355x.h"
+#include "kept_buffers.h"
 #include "queue_layout.h"
 #include "srv_core.h"
 
@@ -39,6 +40,29 @@ thread_local char g_detail[256] = "";
 void note(const char* what, hipError_t e) {
   snprintf(g_detail, sizeof g_detail, "%s: %s (%d)", what, hipGetErrorString(e), (int)e);
 }
+
+// Every allocation of the library goes through device_malloc, which can give bootstrapping's
+// kept buffers back to the device (kept_buffers.h).
+struct HipDevice {
+  using Status = hipError_t;
+  static Status alloc(void** p, size_t bytes) {
+    const hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory) (void)hipGetLastError();  // not the next launch's error
+    return e;
+  }
+  static Status no_memory() { return hipErrorOutOfMemory; }
+  static void free(void* p) { hipFree(p); }
+  static int device() {
+    int d = 0;
+    (void)hipGetDevice(&d);
+    return d;
+  }
+};
+KeptBuffers<HipDevice>& kept() {
+  static auto* const k = new KeptBuffers<HipDevice>;  // contexts may outlive static objects
+  return *k;
+}
+hipError_t device_malloc(void** p, size_t bytes) { return kept().alloc(p, bytes); }
 
 // Device address of `scratch` per device, set by fhe_ctx_create with the device current.
 constexpr int kMaxDevices = 64;
@@ -134,7 +158,7 @@ struct Big {
 
 template <typename T>
 hipError_t upload(T** dptr, const std::vector<T>& h) {
-  hipError_t e = hipMalloc((void**)dptr, h.size() * sizeof(T));
+  hipError_t e = device_malloc((void**)dptr, h.size() * sizeof(T));
   if (e != hipSuccess) {
     note("hipMalloc of a constant table", e);
     return e;
@@ -265,8 +289,6 @@ struct fhe_ctx {
   std::map<std::pair<int, int>, LiftTab> lifts;           // per (L, K)
   std::map<uint32_t, uint32_t*> pw;  // per BGV t: 2^(32 l) mod t
   std::map<std::pair<void*, int>, Workspace> ws;  // (stream, slot)
-  std::vector<uint32_t*> boot;  // bootstrapping's kept buffers (boot_take), boot_words each
-  size_t boot_words = 0;
   std::recursive_mutex mu;
   int sticky = FHE_OK;
   Recorder* rec = nullptr;  // non-null while profiling is on
@@ -533,11 +555,6 @@ uint32_t* pow_table(fhe_ctx* c, uint32_t t, hipError_t* err) {
 }
 
 // Scratch memory of a (context, stream, slot), grown on demand.
-void boot_release(fhe_ctx* c) {
-  for (uint32_t* p : c->boot) hipFree(p);
-  c->boot.clear();
-}
-
 void* stream_scratch(fhe_ctx* c, void* stream, int slot, size_t bytes, hipError_t* err) {
   Workspace& w = c->ws[std::make_pair(stream, slot)];
   if (w.bytes < bytes) {
@@ -547,12 +564,7 @@ void* stream_scratch(fhe_ctx* c, void* stream, int slot, size_t bytes, hipError_
       w.ptr = nullptr;
       w.bytes = 0;
     }
-    *err = hipMalloc(&w.ptr, bytes);
-    if (*err == hipErrorOutOfMemory && !c->boot.empty()) {
-      boot_release(c);
-      (void)hipGetLastError();
-      *err = hipMalloc(&w.ptr, bytes);
-    }
+    *err = device_malloc(&w.ptr, bytes);
     if (*err != hipSuccess) return nullptr;
     w.bytes = bytes;
   }
@@ -755,9 +767,9 @@ int evk_prepare_locked(fhe_evk* k, int logq, hipStream_t stream) {
   }
   uint32_t* limbs = nullptr;
   uint32_t* out = nullptr;
-  hipError_t e = hipMalloc(&limbs, h.size() * 4);
+  hipError_t e = device_malloc((void**)&limbs, h.size() * 4);
   if (e != hipSuccess) return set_sticky(c, e);
-  e = hipMalloc(&out, (size_t)2 * Kr * N * 4);
+  e = device_malloc((void**)&out, (size_t)2 * Kr * N * 4);
   if (e != hipSuccess) {
     hipFree(limbs);
     return set_sticky(c, e);
@@ -780,7 +792,7 @@ int evk_prepare_locked(fhe_evk* k, int logq, hipStream_t stream) {
   // the fused relinearization pass reads each row in its transposed register order
   const long long words = 2LL * Kr * N;
   uint32_t* perm = nullptr;
-  e = hipMalloc(&perm, (size_t)words * 4);
+  e = device_malloc((void**)&perm, (size_t)words * 4);
   if (e == hipSuccess) e = launch_row_transpose(out, perm, words, k->logN - 4, stream);
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   hipFree(out);
@@ -1006,7 +1018,7 @@ int plan_build_queue(fhe_plan* pl, hipStream_t st) {
   for (size_t ci = 0; ci < nc; ++ci) {
     PlanCell& cell = pl->cells[ci];
     const PipeSize z = pipe_size(c, cell.evk, cell.logN, cell.logq, cell.cnum);
-    hipError_t e = hipMalloc((void**)&pl->cws[ci], (size_t)std::max(z.main_words, 1LL) * 4);
+    hipError_t e = device_malloc((void**)&pl->cws[ci], (size_t)std::max(z.main_words, 1LL) * 4);
     if (e != hipSuccess) return set_sticky(c, e);
     PipeIO io;
     io.ins = cell.ptrs;
@@ -1080,7 +1092,7 @@ int plan_build_queue(fhe_plan* pl, hipStream_t st) {
   for (const auto& kv : lds_need)  // dynamic LDS beyond the default for these entry points
     if (e == hipSuccess)
       e = hipFuncSetAttribute(kv.first, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kv.second);
-  if (e == hipSuccess && !img.empty()) e = hipMalloc(&pl->qmem, img.size());
+  if (e == hipSuccess && !img.empty()) e = device_malloc(&pl->qmem, img.size());
   if (e == hipSuccess && !img.empty()) e = hipMemcpy(pl->qmem, img.data(), img.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) return set_sticky(c, e);
   for (Pending& pd : pend) {
@@ -1505,22 +1517,17 @@ bool ct_overlap(const fhe_ct* a, int La, const fhe_ct* b, int Lb) {
 uint32_t* fhe::boot_take(fhe_ctx* c, size_t words) {
   std::lock_guard<std::recursive_mutex> lg(c->mu);
   hipSetDevice(c->device);
-  if (c->boot_words != words) boot_release(c);  // kept for another size
-  if (!c->boot.empty()) {
-    uint32_t* p = c->boot.back();
-    c->boot.pop_back();
-    return p;
-  }
-  uint32_t* p = nullptr;
-  return hipMalloc((void**)&p, words * 4) == hipSuccess ? p : nullptr;
+  return kept().take(c, words);
 }
 
-void fhe::boot_give(fhe_ctx* c, uint32_t* p, size_t words, bool idle) {
+void fhe::boot_give(fhe_ctx* c, const std::vector<uint32_t*>& bufs, size_t words, hipStream_t st) {
+  // nothing queued uses a buffer that another call may be given (also after an error)
+  const bool idle = hipStreamSynchronize(st) == hipSuccess;
   std::lock_guard<std::recursive_mutex> lg(c->mu);
   hipSetDevice(c->device);
-  if (c->boot_words != words && c->boot.empty()) c->boot_words = words;
-  if (idle && c->boot_words == words && (int)c->boot.size() < kBootKeep) c->boot.push_back(p);
-  else hipFree(p);
+  size_t free_bytes = 0, total = 0;
+  if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) free_bytes = 0;
+  kept().give(c, bufs, words, idle, free_bytes);
 }
 
 extern "C" {
@@ -1700,7 +1707,7 @@ void fhe_ctx_destroy(fhe_ctx* c) {
     for (void* p : {(void*)kv.second.A, (void*)kv.second.mneg, (void*)kv.second.eneg})
       if (p) hipFree(p);
   for (auto& kv : c->pw) hipFree(kv.second);
-  boot_release(c);
+  kept().forget(c);
   for (auto& kv : c->ws)
     if (kv.second.ptr) hipFree(kv.second.ptr);
   delete c->rec;
@@ -2085,12 +2092,12 @@ int fhe_batch_plan(fhe_ctx* c, const fhe_job* jobs, int njobs, int flags, void* 
       h[4 * cell.cnum + m] = j.out0;
       h[5 * cell.cnum + m] = j.out1;
     }
-    hipError_t e = hipMalloc((void**)&cell.ptrs, h.size() * sizeof(void*));
+    hipError_t e = device_malloc((void**)&cell.ptrs, h.size() * sizeof(void*));
     if (e == hipSuccess) e = hipMemcpy(cell.ptrs, h.data(), h.size() * sizeof(void*), hipMemcpyHostToDevice);
     if (e != hipSuccess) rc = set_sticky(c, e);
   }
   if (rc == FHE_OK) {
-    hipError_t e = hipMalloc((void**)&pl->ws, (size_t)std::max(mw, 1LL) * 4);
+    hipError_t e = device_malloc((void**)&pl->ws, (size_t)std::max(mw, 1LL) * 4);
     if (e != hipSuccess) rc = set_sticky(c, e);
   }
   // graph branches: cells by decreasing scratch size (a proxy for their work), each to
@@ -2119,7 +2126,7 @@ int fhe_batch_plan(fhe_ctx* c, const fhe_job* jobs, int njobs, int flags, void* 
     for (int b = 1; b < kPlanBranches && e == hipSuccess; ++b) {
       if (need[b] == 0) continue;  // an empty branch
       // a stage-batched plan gives every cell scratch of its own instead
-      if (!queue) e = hipMalloc((void**)&pl->bws[b], (size_t)need[b] * 4);
+      if (!queue) e = device_malloc((void**)&pl->bws[b], (size_t)need[b] * 4);
       if (e == hipSuccess) e = hipStreamCreateWithFlags(&pl->bst[b], hipStreamNonBlocking);
       if (e == hipSuccess) e = hipEventCreateWithFlags(&pl->join[b], hipEventDisableTiming);
     }
@@ -2226,12 +2233,12 @@ int fhe_server_create(fhe_ctx* c, size_t hbm_budget, int nstreams, int max_batch
   ex.slots.resize(nstreams);
   hipError_t e = hipSuccess;
   const size_t arena = hbm_budget & ~(size_t)255;
-  if (arena) e = hipMalloc((void**)&ex.arena, arena);
+  if (arena) e = device_malloc((void**)&ex.arena, arena);
   for (SrvExec::Slot& sl : ex.slots) {
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&sl.st, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&sl.done, hipEventDisableTiming);
     if (e == hipSuccess) e = hipHostMalloc((void**)&sl.hptr, 6 * (size_t)max_batch * sizeof(void*), 0);
-    if (e == hipSuccess) e = hipMalloc((void**)&sl.dptr, 6 * (size_t)max_batch * sizeof(void*));
+    if (e == hipSuccess) e = device_malloc((void**)&sl.dptr, 6 * (size_t)max_batch * sizeof(void*));
   }
   if (e == hipSuccess) sv->core = new (std::nothrow) SrvCore<SrvExec>(ex, arena, nstreams, max_batch);
   if (e != hipSuccess || !sv->core) {

@@ -19,16 +19,13 @@
 namespace {
 
 // Device buffers of ciphertexts at the top level (room for a CipherTensor of two), reused
-// within a call and, through the context's kept list (boot_take), from call to call:
+// within a call and, from call to call, through those that the context keeps (boot_take):
 // allocating and freeing the two dozen of them took 3.5 ms of a call of 8 (N = 2^14).
 class CtPool {
  public:
   CtPool(fhe_ctx* c, size_t words, hipStream_t st) : c_(c), words_(words), st_(st) {}
   ~CtPool() {
-    if (all_.empty()) return;
-    // nothing queued uses a buffer that another call may be given (also after an error)
-    const bool idle = hipStreamSynchronize(st_) == hipSuccess;
-    for (uint32_t* p : all_) fhe::boot_give(c_, p, words_, idle);
+    if (!all_.empty()) fhe::boot_give(c_, all_, words_, st_);
   }
   uint32_t* get() {
     if (!free_.empty()) {

@@ -4,19 +4,18 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 #include "modarith.h"
 
 struct fhe_ctx;
 
 namespace fhe {
 
-// Bootstrapping's device buffers: taken from the context's kept list (or allocated), given
-// back to it.  The list holds buffers of one size, at most kBootKeep of them; others, and
-// those whose stream could not be waited for, are freed.  The list is freed with the
-// context, or when an allocation for the context's scratch fails.
-constexpr int kBootKeep = 48;
+// Bootstrapping's device buffers: taken from those the context keeps (kept_buffers.h) or
+// allocated; given back once `st` has been waited for (freed where it could not be).
 uint32_t* boot_take(fhe_ctx* c, size_t words);
-void boot_give(fhe_ctx* c, uint32_t* p, size_t words, bool idle);
+void boot_give(fhe_ctx* c, const std::vector<uint32_t*>& bufs, size_t words, hipStream_t st);
 
 typedef int v4i_t __attribute__((ext_vector_type(4)));
 
