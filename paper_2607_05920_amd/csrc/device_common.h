@@ -47,11 +47,7 @@ __device__ __forceinline__ uint32_t buffer_word(__amdgpu_buffer_rsrc_t r, uint32
   return __builtin_amdgcn_raw_buffer_load_b32(r, (int)byte_off, 0, 0);
 }
 
-// Limb rows of one coefficient per lane.  The limb-serial kernels read their rows a block of
-// kLimbBlock at a time: all of a block's loads are in flight together, where a load per limb
-// inside the carry chain waited for memory limb by limb (2^14 coefficients, 32 limbs, a sum:
-// 9.6 us a launch; with blocks 4.9).  Rows at or beyond the buffer's end read as zero.
-constexpr int kLimbBlock = 16;
+// Limb rows of one coefficient per lane.  Rows at or beyond the buffer's end read as zero.
 struct LimbRows {
   __amdgpu_buffer_rsrc_t r;
   uint32_t lane, row;  // byte offset of the lane's coefficient, bytes between rows
@@ -59,11 +55,56 @@ struct LimbRows {
   __device__ __forceinline__ LimbRows(const uint32_t* base, int rows, int N, uint32_t coeff)
       : r(row_buffer(wave_uniform(base), 4u * (uint32_t)rows * (uint32_t)N)), lane(4u * coeff), row(4u * (uint32_t)N) {}
   __device__ __forceinline__ uint32_t operator[](int l) const { return buffer_word(r, lane + (uint32_t)l * row); }
-  __device__ __forceinline__ void block(uint32_t (&v)[kLimbBlock], int l0) const {
+  template <int B>
+  __device__ __forceinline__ void block(uint32_t (&v)[B], int l0) const {
 #pragma unroll
-    for (int i = 0; i < kLimbBlock; ++i) v[i] = (*this)[l0 + i];
+    for (int i = 0; i < B; ++i) v[i] = (*this)[l0 + i];
   }
 };
+
+// A limb-serial kernel's rows first.. of x (and of y), `n` of them, B at a time: f(block of x,
+// block of y, first row's number) in turn, with the next block already in flight.
+//
+// What bounds these kernels: with few waves the rows' latency, with many the memory's rate,
+// which is highest while reads and stores go on side by side.  A load per limb inside the
+// carry chain waits for memory limb by limb; large blocks read, then store, the whole chip
+// in step; and a load after a block's stores waits for them too, as both are counted in
+// order.  Small blocks, the next one asked for before this one is stored, do well at both
+// ends.  us with a row at a time, with blocks of 16, with these (N = 2^16): automorphism of
+// 49 limbs 14.1, 10.7, 7.4, of 4 x 49 21.7, 25.5, 21.3; rescaling 49 limbs 18.3, 12.2, 9.9,
+// 8 x 49 89, 76, 76; BGV rescaling 8 x 14 19.4, 22.3, 18.4; sum of 8 x 14 26.3, 27.5, 25.9;
+// composition at 1555 bits 33.0, 19.2, 17.7, of 4 53.7, 48.3, 46.9.
+template <int B, typename F>
+__device__ __forceinline__ void limb_blocks(const LimbRows& x, int xfirst, const LimbRows& y, int yfirst, int n, F f) {
+  uint32_t x0[B], y0[B], x1[B], y1[B];
+  x.block(x0, xfirst);
+  y.block(y0, yfirst);
+  for (int l = 0; l < n; l += 2 * B) {
+    x.block(x1, xfirst + l + B);
+    y.block(y1, yfirst + l + B);
+    __builtin_amdgcn_sched_barrier(0);
+    f(x0, y0, l);
+    if (l + B >= n) break;
+    x.block(x0, xfirst + l + 2 * B);
+    y.block(y0, yfirst + l + 2 * B);
+    __builtin_amdgcn_sched_barrier(0);
+    f(x1, y1, l + B);
+  }
+}
+template <int B, typename F>
+__device__ __forceinline__ void limb_blocks(const LimbRows& x, int xfirst, int n, F f) {
+  uint32_t x0[B], x1[B];
+  x.block(x0, xfirst);
+  for (int l = 0; l < n; l += 2 * B) {
+    x.block(x1, xfirst + l + B);
+    __builtin_amdgcn_sched_barrier(0);
+    f(x0, l);
+    if (l + B >= n) break;
+    x.block(x0, xfirst + l + 2 * B);
+    __builtin_amdgcn_sched_barrier(0);
+    f(x1, l + B);
+  }
+}
 
 // Global store at a byte offset from a wave-uniform base (the global address space is
 // stated: the pointer's provenance is lost through the scalar move).

@@ -1022,11 +1022,12 @@ __device__ __forceinline__ int64_t round_correction(const LimbRows& x, int nl, i
   // BGV: r = (x mod 2^sbits) mod t, then j = [[ r 2^-s ]]_t.
   const int full = sbits >> 5, part = sbits & 31;
   uint64_t acc = 0;
-  for (int l0 = 0; l0 <= full && l0 < nl; l0 += kLimbBlock) {
-    uint32_t v[kLimbBlock];
+  constexpr int B = 8;
+  for (int l0 = 0; l0 <= full && l0 < nl; l0 += B) {
+    uint32_t v[B];
     x.block(v, l0);
 #pragma unroll
-    for (int i = 0; i < kLimbBlock; ++i) {
+    for (int i = 0; i < B; ++i) {
       const int l = l0 + i;
       if (l >= nl || l > full) break;
       if (l < full) acc += (uint64_t)v[i] * pw[l];
@@ -1052,12 +1053,10 @@ __device__ __forceinline__ void compose_kernel_body(const ComposeArgs& a, const 
   uint64_t carry = 0;
   uint32_t klo = k[sl];
   const int topbits = a.logq - 32 * (a.L - 1);
-  for (int l0 = 0; l0 < a.L; l0 += kLimbBlock) {
-    uint32_t kv[kLimbBlock], dv[kLimbBlock];
-    k.block(kv, sl + 1 + l0);
-    d.block(dv, l0);
+  constexpr int B = 4;
+  limb_blocks<B>(k, sl + 1, d, 0, a.L, [&](const uint32_t (&kv)[B], const uint32_t (&dv)[B], int l0) {
 #pragma unroll
-    for (int b = 0; b < kLimbBlock; ++b) {
+    for (int b = 0; b < B; ++b) {
       const int l = l0 + b;
       if (l >= a.L) break;
       const uint32_t khi = kv[b];
@@ -1070,7 +1069,7 @@ __device__ __forceinline__ void compose_kernel_body(const ComposeArgs& a, const 
       if (l == a.L - 1 && topbits < 32) wv &= (1u << topbits) - 1u;
       o[(long long)l * a.N] = wv;
     }
-  }
+  });
 }
 
 __global__ __launch_bounds__(256) void compose_kernel(ComposeArgs a) { compose_kernel_body(a, own_blk()); }
@@ -1122,12 +1121,27 @@ __device__ __forceinline__ void compose_rescale_kernel_body(const ComposeArgs& a
     if (m == Lout - 1 && otop < 32) w &= (1u << otop) - 1u;
     o[(long long)m * a.N] = w;
   };
-  for (int l0 = 0; l0 < a.L; l0 += kLimbBlock) {
-    uint32_t kv[kLimbBlock], dv[kLimbBlock];
-    k.block(kv, sl + 1 + l0);
-    d.block(dv, l0);
+  // Blocks of two, the next one in flight, as in limb_blocks but with one copy of this long
+  // body (two are slower from 2^15 coefficients and 28 limbs on, 25.9 -> 29.5 us at 1555
+  // bits; blocks of three or four at 4 x 2^16, 61 -> 67).  N = 2^16, us with a limb at a
+  // time, with blocks of 16 and now: 438 bits 12.2, 11.7, 10.1, a CipherTensor of 4 21.9,
+  // 25.1, 20.3; 1555 bits 40.2, 32.4, 25.9, of 4 62.6, 73.2, 61.3 (BGV 94, 92, 80).
+  constexpr int B = 2;
+  uint32_t kn[B], dn[B];
+  k.block(kn, sl + 1);
+  d.block(dn, 0);
+  for (int l0 = 0; l0 < a.L; l0 += B) {
+    uint32_t kv[B], dv[B];
 #pragma unroll
-    for (int b = 0; b < kLimbBlock; ++b) {
+    for (int b = 0; b < B; ++b) {
+      kv[b] = kn[b];
+      dv[b] = dn[b];
+    }
+    k.block(kn, sl + 1 + l0 + B);
+    d.block(dn, l0 + B);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
       const int l = l0 + b;
       if (l >= a.L) break;
       const uint32_t khi = kv[b];
@@ -1196,12 +1210,11 @@ __global__ __launch_bounds__(256) void rescale_kernel(RescaleArgs a) {
   uint64_t carry = 0;
   uint32_t xlo = x[sl];
   const int topbits = newq - 32 * (Lout - 1);
-  for (int l0 = 0; l0 < Lout; l0 += kLimbBlock) {
-    // reads of limbs above sl + l precede the write of limb l (in place is safe)
-    uint32_t xv[kLimbBlock];
-    x.block(xv, sl + 1 + l0);
+  constexpr int B = 4;
+  // reads of limbs above sl + l precede the write of limb l (in place is safe)
+  limb_blocks<B>(x, sl + 1, Lout, [&](const uint32_t (&xv)[B], int l0) {
 #pragma unroll
-    for (int b = 0; b < kLimbBlock; ++b) {
+    for (int b = 0; b < B; ++b) {
       const int l = l0 + b;
       if (l >= Lout) break;
       const uint32_t xhi = xv[b];
@@ -1214,7 +1227,7 @@ __global__ __launch_bounds__(256) void rescale_kernel(RescaleArgs a) {
       if (l == Lout - 1 && topbits < 32) wv &= (1u << topbits) - 1u;
       o[(long long)l * a.N] = wv;
     }
-  }
+  });
 }
 
 hipError_t launch_compose(const ComposeArgs& a, int cnum, hipStream_t st) {
@@ -1291,12 +1304,13 @@ __global__ __launch_bounds__(256) void add_small_kernel(const AddSmallArgs a) {
     const uint32_t ext = s < 0 ? 0xFFFFFFFFu : 0u;
     uint64_t carry = 0;
     const LimbRows xr(x, L, N, j), yr(y ? y : x, y ? L : 0, N, j);
-    for (int l0 = 0; l0 < L; l0 += kLimbBlock) {
-      uint32_t xv[kLimbBlock], yv[kLimbBlock];
+    constexpr int B = 16;
+    for (int l0 = 0; l0 < L; l0 += B) {
+      uint32_t xv[B], yv[B];
       xr.block(xv, l0);
       yr.block(yv, l0);
 #pragma unroll
-      for (int b = 0; b < kLimbBlock; ++b) {
+      for (int b = 0; b < B; ++b) {
         const int l = l0 + b;
         if (l >= L) break;
         const uint32_t w0 = l == 0 ? (uint32_t)s : (l == 1 ? (uint32_t)((unsigned long long)s >> 32) : ext);

@@ -27,12 +27,10 @@ __global__ __launch_bounds__(256) void limb_sum_kernel(LimbSumArgs a) {
   uint32_t* o = (i ? a.out1 : a.out0) + (long long)c * a.ostride + j;
   const uint32_t mx = a.negx ? 0xFFFFFFFFu : 0u, my = has_y && a.negy ? 0xFFFFFFFFu : 0u;
   uint64_t carry = (uint64_t)(a.negx != 0) + (uint64_t)(my != 0);
-  for (int l0 = 0; l0 < a.L; l0 += kLimbBlock) {
-    uint32_t xv[kLimbBlock], yv[kLimbBlock];
-    x.block(xv, l0);
-    y.block(yv, l0);
+  constexpr int B = 4;
+  limb_blocks<B>(x, 0, y, 0, a.L, [&](const uint32_t (&xv)[B], const uint32_t (&yv)[B], int l0) {
 #pragma unroll
-    for (int k = 0; k < kLimbBlock; ++k) {
+    for (int k = 0; k < B; ++k) {
       const int l = l0 + k;
       if (l >= a.L) break;
       const uint64_t s = (uint64_t)(xv[k] ^ mx) + (uint64_t)(yv[k] ^ my) + carry;
@@ -41,7 +39,7 @@ __global__ __launch_bounds__(256) void limb_sum_kernel(LimbSumArgs a) {
       if (l == a.L - 1) w &= a.topmask;
       o[(long long)l * a.N] = w;
     }
-  }
+  });
 }
 
 // Signed permutation of coefficients: output position k < N takes the input at
@@ -61,11 +59,10 @@ __global__ __launch_bounds__(256) void signed_perm_kernel(PermArgs a) {
   uint32_t* o = (i ? a.out1 : a.out0) + (long long)c * a.ostride + k;
   const uint32_t m = neg ? 0xFFFFFFFFu : 0u;
   uint64_t carry = neg ? 1u : 0u;
-  for (int l0 = 0; l0 < a.L; l0 += kLimbBlock) {
-    uint32_t xv[kLimbBlock];
-    x.block(xv, l0);
+  constexpr int B = 4;
+  limb_blocks<B>(x, 0, a.L, [&](const uint32_t (&xv)[B], int l0) {
 #pragma unroll
-    for (int b = 0; b < kLimbBlock; ++b) {
+    for (int b = 0; b < B; ++b) {
       const int l = l0 + b;
       if (l >= a.L) break;
       const uint64_t s = (uint64_t)(xv[b] ^ m) + carry;
@@ -74,7 +71,7 @@ __global__ __launch_bounds__(256) void signed_perm_kernel(PermArgs a) {
       if (l == a.L - 1) w &= a.topmask;
       o[(long long)l * N] = w;
     }
-  }
+  });
 }
 
 // out_z = [(-1)^neg x_z k]_(2^logq) for an integer constant k of klimbs <= 8 limbs.
@@ -92,11 +89,10 @@ __global__ __launch_bounds__(256) void const_mul_kernel(ConstMulArgs a) {
   for (int t = 0; t < kConstMaxLimbs; ++t) win[t] = 0u;
   const uint32_t nm = a.neg ? 0xFFFFFFFFu : 0u;
   uint64_t carry = 0, ncarry = a.neg ? 1u : 0u;
-  for (int l0 = 0; l0 < a.L; l0 += kLimbBlock) {
-    uint32_t xv[kLimbBlock];
-    x.block(xv, l0);
+  constexpr int B = 4;
+  limb_blocks<B>(x, 0, a.L, [&](const uint32_t (&xv)[B], int l0) {
 #pragma unroll
-    for (int b = 0; b < kLimbBlock; ++b) {
+    for (int b = 0; b < B; ++b) {
       const int l = l0 + b;
       if (l >= a.L) break;
 #pragma unroll
@@ -118,7 +114,7 @@ __global__ __launch_bounds__(256) void const_mul_kernel(ConstMulArgs a) {
       if (l == a.L - 1) w &= a.topmask;
       o[(long long)l * a.N] = w;
     }
-  }
+  });
 }
 
 hipError_t launch_limb_sum(const LimbSumArgs& a, int cnum, hipStream_t st) {

@@ -6,6 +6,7 @@ import pytest
 
 import paper_2607_05920_amd as fhe
 import synth
+from oracle import galois, ops, scheme
 from oracle import ntt as ontt
 from oracle import ring
 from tests.gpu_helpers import check, dev, host, ints, limbs_of, say
@@ -168,3 +169,55 @@ def test_bootstrap_same_on_used_memory():
         for k in [relin, conj, *rot.values()]:
             k.close()
         c.close()
+
+
+# limb counts on both sides of the limb-serial kernels' blocks (of two and four rows, the next
+# block in flight): the rescale by 20 or 32 bits keeps the count or lowers it by one
+@pytest.mark.parametrize("logq", [33, 64, 90, 128, 129, 160, 256, 257, 288, 289])
+def test_limb_blocks(ctx, logq):
+    import torch
+    logN, logP = 10, 70
+    say(f"limb blocks logq={logq}")
+    N, L = 1 << logN, synth.nlimbs(logq)
+    rng = np.random.default_rng(13 * logq)
+    top = limbs_of([(1 << logq) - 1], logq)[:, 0]
+    osch = {fhe.CKKS: scheme.CKKS, fhe.BGV: scheme.BGV}
+
+    def tensor(sch, t):
+        c = synth.uniform_limbs(rng, logq, N, count=2)
+        c[:, :, :2] = top[None, :, None]  # carries through every limb
+        c[:, :, 2] = 0
+        return (fhe.Ciphertext(dev(c[0]).reshape(-1), dev(c[1]).reshape(-1), logN, logq, 60, sch, t, 1, 1),
+                scheme.Ciphertext(ints(c[0]), ints(c[1]), logN, logq, 60, osch[sch], t))
+
+    def same(got, want, what):
+        Lo = synth.nlimbs(got.logq)
+        check(ints(host(got.c0, -1)[:Lo * N].reshape(Lo, N)), want.c0, f"{what} c0")
+        check(ints(host(got.c1, -1)[:Lo * N].reshape(Lo, N)), want.c1, f"{what} c1")
+
+    out = tuple(torch.empty(L * N, dtype=torch.int32, device="cuda") for _ in range(2))
+    for sch, t in ((fhe.CKKS, 0), (fhe.BGV, 65537)):
+        (x, ox), (y, oy) = tensor(sch, t), tensor(sch, t)
+        same(ctx.ct_add(x, y, out), ops.add(ox, oy), "add")
+        same(ctx.ct_sub(x, y, out), ops.sub(ox, oy), "sub")
+        same(ctx.ct_negate(x, out), ops.negate(ox), "negate")
+        k = (1 << 60) + 12345
+        same(ctx.ct_multconst(x, -k, out), ops.multconst(ox, -k, 0), "multconst")
+        for bits in (20, 32):
+            same(ctx.ct_rescale(x, bits, out), scheme.rescale(ox, bits), f"rescale {bits}")
+        inplace = fhe.Ciphertext(x.c0.clone(), x.c1.clone(), *[getattr(x, f) for f in
+                                 ("logN", "logq", "logp", "scheme", "t", "gamma", "cnum")])
+        same(ctx.ct_rescale(inplace, 20, (inplace.c0, inplace.c1)), scheme.rescale(ox, 20), "rescale in place")
+        eb, ea = (synth.uniform_limbs(rng, logq + logP, N) for _ in range(2))
+        key = fhe.EvalKey(ctx, sch, t, logN, logq, logP, eb, ea)
+        okey = scheme.EvalKey(ints(eb), ints(ea), logN, logq, logP, osch[sch], t)
+        try:
+            same(ctx.ct_mul_relin(key, x, y, out), scheme.mult(ox, oy, okey), "mult")
+            for bits in (20, 32):
+                same(ctx.ct_mul_relin(key, x, y, out, bits=bits), scheme.mult_rescale(ox, oy, okey, bits),
+                     f"mult, rescale {bits}")
+        finally:
+            key.close()
+        auto = torch.empty(L * N, dtype=torch.int32, device="cuda")
+        ctx.automorphism(logN, logq, 5, x.c0, auto)
+        check(ints(host(auto, (L, N))), galois.automorphism(ox.c0, 5, 1 << logq), "automorphism")
