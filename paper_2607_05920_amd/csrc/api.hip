@@ -1879,6 +1879,21 @@ int fhe_encrypt(fhe_ctx* c, int scheme, uint32_t t, int logN, int logq, const ui
   aa.N = N;
   aa.L = L;
   aa.topmask = top;
+  // One launch has both components' sums, c0's before c1's in each coefficient's thread.  Where
+  // c1 lies over what c0's sum reads and another coefficient's word is there, c0's go first.
+  auto crosses = [&](const void* p, long long words) {
+    const long long d = ((long long)(uintptr_t)p - (long long)(uintptr_t)c1) / 4;
+    return d < LN && -d < words && d % N != 0;
+  };
+  if (crosses(m, LN) || crosses(e0, N)) {
+    aa.n = 1;
+    e = launch_add_small(aa, st);
+    if (e != hipSuccess) return set_sticky(c, e);
+    aa.x0 = aa.x1;
+    aa.y0 = nullptr;
+    aa.e0 = e1;
+    aa.out0 = c1;
+  }
   return set_sticky(c, launch_add_small(aa, st));
 }
 

@@ -97,6 +97,38 @@ def test_encrypt_fused(ctx, logN, logq):
         check(ints(got), [(p + a + int(x)) % (1 << logq) for p, a, x in zip(prod, add, e[i])], f"component {i}")
 
 
+# c1 over m or e0 (read by c0's sum), with words of other coefficients on each other, a whole
+# number of rows apart, and apart; the result is that of buffers of their own
+@pytest.mark.parametrize("over,shift", [("m", 64), ("m", -3), ("m", 2048), ("m", -1025), ("e0", 5), ("e0", -700),
+                                        ("e0", -1024), ("m", 1 << 20)])
+def test_encrypt_c1_over_inputs(ctx, over, shift):
+    import torch
+    logN, logq = 10, 150
+    say(f"encrypt, c1 {shift} words from {over}")
+    N, L = 1 << logN, synth.nlimbs(logq)
+    rng = np.random.default_rng(17)
+    pk = [dev(synth.uniform_limbs(rng, logq, N)) for _ in range(2)]
+    m = dev(synth.uniform_limbs(rng, logq, N)).reshape(-1)
+    v = torch.from_numpy(rng.integers(-1, 2, N).astype(np.int8)).cuda()
+    e = [torch.from_numpy(rng.integers(-9, 10, N).astype(np.int32)).cuda() for _ in range(2)]
+
+    def run(m, e0, c1):
+        c0 = torch.empty(L * N, dtype=torch.int32, device="cuda")
+        ctx.encrypt(fhe.CKKS, 0, logN, logq, *pk, m, v, e0, e[1], c0, c1)
+        return host(c0, -1).copy(), host(c1, -1).copy()
+
+    want = run(m, e[0], torch.empty(L * N, dtype=torch.int32, device="cuda"))
+    src = m if over == "m" else e[0]
+    at = max(0, -shift)
+    room = torch.empty(at + max(shift, 0) + L * N, dtype=torch.int32, device="cuda")
+    put = room[at:at + src.numel()]
+    put.copy_(src)
+    c1 = room[at + shift:at + shift + L * N]
+    got = run(put if over == "m" else m, put if over == "e0" else e[0], c1)
+    for i in (0, 1):
+        assert np.array_equal(got[i], want[i]), f"component {i}"
+
+
 # the ciphertext counts on both sides of the line where a row's polynomials share a wave (16
 # rows of 1024 points per compute unit for the HE-mult, 12 for the ring product): one more
 # than the line takes the other form for all
