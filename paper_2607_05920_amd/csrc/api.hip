@@ -435,6 +435,19 @@ void mul_small_trunc(std::vector<uint32_t>& r, uint32_t m) {
   }
 }
 
+// r / d mod 2^(32 n) for odd d in place, from the lowest word up (Hensel's division): each
+// quotient word is the remaining low word times d^-1 mod 2^32.
+void divide_odd_trunc(std::vector<uint32_t>& r, uint32_t d) {
+  uint32_t inv = d;  // right in three bits; each Newton step doubles them
+  for (int i = 0; i < 4; ++i) inv *= 2 - d * inv;
+  uint32_t borrow = 0;
+  for (auto& w : r) {
+    const uint32_t q = (w - borrow) * inv;
+    borrow = (uint32_t)(((uint64_t)q * d) >> 32) + (w < borrow);
+    w = q;
+  }
+}
+
 // -x mod 2^(32 n) in place.
 void negate_trunc(std::vector<uint32_t>& r) {
   uint64_t carry = 1;
@@ -472,12 +485,14 @@ const CrtTab* crt_table(fhe_ctx* c, int K, int e, int Lout, hipError_t* err) {
   // V_k = (M / q_k) mod 2^(32 Lout) in balanced limbs D_kl in [-0x80808080, 0x7F7F7F7F];
   // vsum = sum_k V_k and dsum = sum_k d_k V_k mod 2^(32 Lout)
   std::vector<int64_t> D((size_t)K * Lp, 0);
-  std::vector<uint32_t> vsum(Lout, 0), dsum(Lout, 0);
+  std::vector<uint32_t> vsum(Lout, 0), dsum(Lout, 0), M(Lout, 0);
+  M[0] = 1;
+  for (int j = 0; j < K; ++j) mul_small_trunc(M, c->q[j]);
+  // The table is built while a first call's transforms run, and the reconstruction waits for
+  // it: products of the other primes for each k (K^2 Lout steps) took most of such a call.
   for (int k = 0; k < K; ++k) {
-    std::vector<uint32_t> v(Lout, 0);
-    v[0] = 1;
-    for (int j = 0; j < K; ++j)
-      if (j != k) mul_small_trunc(v, c->q[j]);
+    std::vector<uint32_t> v = M;
+    divide_odd_trunc(v, c->q[k]);
     add_trunc(vsum, v);
     int64_t carry = 0;
     for (int l = 0; l < Lout; ++l) {
@@ -511,9 +526,7 @@ const CrtTab* crt_table(fhe_ctx* c, int K, int e, int Lout, hipError_t* err) {
         f[3] = (int)w[3];
         A[((size_t)tt * nkb + kb) * 64 + lane] = f;
       }
-  std::vector<uint32_t> mneg(Lout, 0);
-  mneg[0] = 1;
-  for (int j = 0; j < K; ++j) mul_small_trunc(mneg, c->q[j]);
+  std::vector<uint32_t> mneg = M;
   negate_trunc(mneg);
   // the digits of x_k ^ 0x80808080 stand for x_k - 0x80808080
   std::vector<uint32_t> eneg(Lout, 0);
