@@ -38,10 +38,9 @@ struct NttArgs {
   long long group_stride = 0;
   const uint32_t* tw = nullptr; // [prime][kNMax] bit-reversed powers w 2^32 mod q
   const PrimeC* pc = nullptr;
-  const uint32_t* scale = nullptr; // inverse only: per-prime final factor times 2^32; null: the
-                                   // inputs already carry it (only the canonical reduction)
-  const uint32_t* scale_w = nullptr; // with scale: the factor times the last stage's twiddle
-                                  // (table entry 1), folded into that stage
+  const uint32_t* scale = nullptr;   // inverse only: per-prime final factor times 2^32
+  const uint32_t* scale_w = nullptr; // the factor times the last stage's twiddle (table
+                                     // entry 1), folded into that stage
   int ntr = 0;         // number of transforms (set by launch_ntt; a multiple of K)
 };
 
@@ -275,6 +274,7 @@ struct Tuning {
   int lift_primes = 0;  // 0: matrix-core lift; 8, 16 or 32: VALU lift with that many primes per thread
 };
 
+// In two passes, bit-reversed order; the inverse for 2^15 and 2^16 points, with its factors.
 hipError_t launch_ntt(const NttArgs& a, int ntransforms, bool inverse, hipStream_t s);
 // The same with one workgroup per transform (one pass over memory); natural: the
 // transformed side in natural instead of bit-reversed order.  The inverse needs a.scale.

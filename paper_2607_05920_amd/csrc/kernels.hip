@@ -211,12 +211,10 @@ __device__ __forceinline__ void ntt_pass_kernel_body(const NttArgs& a, const Blk
       x[u] = lrow[e + (e >> 4)];
     }
     // strided stages: register distance hd = 1, 2, 4, 8; h = 8 / hd groups.  The last
-    // inverse pass with a final factor takes its last stage below.
-    const bool fold = !ROWS && a.scale != nullptr;
+    // inverse pass takes its last stage below.
 #pragma unroll
-    for (int st = 0; st < 4; ++st) {
+    for (int st = 0; st < (ROWS ? 4 : 3); ++st) {
       const int hd = 1 << st, h = 8 >> st;
-      if (st == 3 && fold) break;
 #pragma unroll
       for (int g = 0; g < h; ++g) {
         const uint32_t w = tw[tw_mul * h + g];
@@ -224,20 +222,15 @@ __device__ __forceinline__ void ntt_pass_kernel_body(const NttArgs& a, const Blk
         for (int u = 2 * hd * g; u < 2 * hd * g + hd; ++u) gs_bfly(x[u], x[u + hd], w, M);
       }
     }
-    if (!ROWS) {  // last inverse pass: final factor (unless the inputs carry it), canonical output
-      if (fold) {
-        // the last stage (one group, twiddle w = entry 1) with the factor c folded in:
-        // X + Y - 2q times c and (X - Y) times w c (scale_w), then canonical
-        const uint32_t sc = a.scale[p], sw = a.scale_w[p];
+    if (!ROWS) {
+      // the last stage (one group, twiddle w = entry 1) with the final factor c folded in:
+      // X + Y - 2q times c and (X - Y) times w c (scale_w), then canonical
+      const uint32_t sc = a.scale[p], sw = a.scale_w[p];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const uint32_t xs = x[u], ys = x[u + 8];
-          x[u] = csub(mont_s(xs + ys + M.neg2q, sc, M), q);
-          x[u + 8] = csub(mont_s(xs - ys, sw, M), q);
-        }
-      } else {
-#pragma unroll
-        for (int u = 0; u < 16; ++u) x[u] = csub(x[u], q);
+      for (int u = 0; u < 8; ++u) {
+        const uint32_t xs = x[u], ys = x[u + 8];
+        x[u] = csub(mont_s(xs + ys + M.neg2q, sc, M), q);
+        x[u + 8] = csub(mont_s(xs - ys, sw, M), q);
       }
     }
 #pragma unroll
@@ -677,13 +670,15 @@ static hipError_t ntt_pass_s(int S, const NttArgs& a, int ntr, hipStream_t st) {
   if (ROWS && S == 8 && a.per_group == a.K && npp >= 4 && 8 * (4 * ncg4 - npp) <= 4 * ncg4 &&
       (3 * a.group_stride + (1LL << a.logN)) * 4 < 0x70000000LL)
     return ntt_pass<8, INV, true, 256, 4>(a, ntr, st);
-  switch (S) {
-    case 5: return ntt_pass<5, INV, ROWS>(a, ntr, st);
-    case 6: return ntt_pass<6, INV, ROWS>(a, ntr, st);
-    case 7: return ntt_pass<7, INV, ROWS>(a, ntr, st);
-    case 8: return ntt_pass<8, INV, ROWS>(a, ntr, st);
-    default: return hipErrorInvalidValue;
+  if (S == 8) return ntt_pass<8, INV, ROWS>(a, ntr, st);
+  if constexpr (!INV || ROWS) {
+    if (S == 7) return ntt_pass<7, INV, ROWS>(a, ntr, st);
   }
+  if constexpr (!INV) {
+    if (S == 6) return ntt_pass<6, INV, ROWS>(a, ntr, st);
+    if (S == 5) return ntt_pass<5, INV, ROWS>(a, ntr, st);
+  }
+  return hipErrorInvalidValue;
 }
 
 // dst[r n + u T + j] = src[r n + 16 j + u] within rows of n = 2^S words (T = n / 16):
@@ -737,6 +732,8 @@ hipError_t launch_rows_fused(const RowsArgs& a, int mode, hipStream_t st) {
 hipError_t launch_ntt(const NttArgs& a0, int ntr, bool inverse, hipStream_t st) {
   if (ntr <= 0) return hipSuccess;
   if (ntr % a0.K != 0 || a0.per_group % a0.K != 0) return hipErrorInvalidValue;
+  // inverse transforms of fewer points always take one workgroup each (ntt_whole_wanted)
+  if (inverse && (a0.logN < 15 || !a0.scale || !a0.scale_w)) return hipErrorInvalidValue;
   NttArgs a = a0;
   a.ntr = ntr;
   // the split groups the same stages differently and does not change the result
