@@ -100,12 +100,13 @@ int fhe_ctx_reset_error(fhe_ctx* ctx);
  * work is the kernel's algorithmic HBM bytes: every input element it must read and
  * every output element it must write, once (limbs and residues of the lift and the
  * reconstruction, transform rows of the NTT passes, ...).  Kernel classes:
- * 0 lift, 1 forward NTT column pass, 2 forward NTT row pass, 3 inverse NTT row
- * pass, 4 inverse NTT column pass, 5 pointwise (no longer launched: the fused row
- * pass does the products), 6 reconstruction (CRT),
- * 7 relinearization compose, 8 rescale, 9 fused row pass (last forward NTT row
- * pass + pointwise products + first inverse row pass, used by the HE-mult and the
- * ring multiply), 10 compose and rescale in one pass (HE-mult with rescale),
+ * 0 lift (in a product of up to 56 limbs with the transforms' first four stages), 1
+ * forward NTT column pass, or a whole forward transform in one pass, 2 forward NTT row
+ * pass, 3 inverse NTT row pass, 4 inverse NTT column pass, or a whole inverse transform, 5
+ * pointwise (no longer launched: the fused row pass does the products), 6 reconstruction
+ * (CRT, with the transforms' last four stages), 7 relinearization compose, 8 rescale, 9
+ * fused row pass (the other stages of the forward transforms, the products and the
+ * matching stages of the inverse ones, used by the HE-mult and the ring multiply), 10 compose and rescale in one pass (HE-mult with rescale),
  * 11 coefficient-wise operations (add, sub, negate, moddown, addconst, multconst,
  * the signed permutations of imult and the automorphisms).  Errors: FHE_E_INVAL,
  * FHE_E_STATE (not recording). */
@@ -127,7 +128,7 @@ int fhe_prime_info(const fhe_ctx* ctx, int idx, uint32_t* q, uint32_t* psi);
  * `terms` products: the smallest K with prod_(i<K) q_i >= 2^(e+17), where
  * e = bits_a + bits_b + logN + ceil(log2(terms)) bounds the signed exact result,
  * |X| < 2^e.  The 16 bits beyond 2^(e+1) keep the CRT quotient of X + 2^e exact
- * when it is evaluated in double precision.  (Host output.) */
+ * when it is evaluated in 64-bit fixed point.  (Host output.) */
 int fhe_primes_needed(const fhe_ctx* ctx, int logN, int bits_a, int bits_b, int terms, int* K);
 
 /* Limb -> RNS projection (Section 5.1 "Limb-to-RNS Conversion"): for each of
@@ -181,7 +182,8 @@ int fhe_ring_mul_noalloc(fhe_ctx* ctx, int logN, int logq, const uint32_t* a, co
  * b_host, a_host are host uint32[L_PQ][N], L_PQ = ceil((logP + logQ_key) / 32).
  * The library keeps a host copy of the limbs and, per ciphertext level logq used
  * with it, the NTT form of the key reduced mod P * 2^logq resident on the device
- * (built on first use or by fhe_evk_prepare; 2 K_r N words).  *out is library-owned; release with fhe_evk_destroy.
+ * (built on first use or by fhe_evk_prepare; 2 K_r N words).  *out is library-owned;
+ * release with fhe_evk_destroy.
  * scheme is FHE_CKKS or FHE_BGV; t (odd, 3 <= t < 2^24, so that the t-corrected
  * divisions' sums stay within 64 bits) is read for BGV only.
  * Errors: FHE_E_INVAL, FHE_E_RANGE (logQ_key > logQ_max or logP > logP_max),

@@ -102,7 +102,7 @@ class Boot {
     if (ok()) check(fhe_ct_moddown(c_, &x.ct, x.ct.logq - logq, &y.ct, st_));
     return y;
   }
-  // the pair brought to the lower of the two levels (one of the two is a view)
+  // the pair brought to the lower of the two levels (the lower one, or both, as views)
   void match(const V& x, const V& y, V& xo, V& yo) {
     const int q = std::min(x.ct.logq, y.ct.logq);
     xo = level(x, q);

@@ -17,7 +17,9 @@ namespace fhe {
 // are constants, so sum_k d_k (M/q_k) joins the constant row and sum_k d_k / q_k the
 // constant of the quotient; what is left per residue is x_k itself, in [0, 2 q_k).
 // The prime count leaves Y / M < 2^-16, so alpha is exact from the sum in fixed point
-// sum_k x_k floor(2^54 / q_k) (truncation error below 2^-15, an offset of 2^-10 covers it).
+// sum_k x_k floor(2^54 / q_k): a truncated reciprocal is short by less than 2^-54, so that
+// the x_k below 2 q_k and the d_k below q_k lose less than K 3 2^30 2^-54, 2^-14 for the up
+// to 256 primes, and an offset of 2^-10 covers it.
 //
 // The column sums sum_k x_k V_kl, V_kl = limb l of (M/q_k) mod 2^(32 Lout), are a dense
 // integer contraction [coefficients x K] x [K x Lout] and run on the i8 matrix cores:

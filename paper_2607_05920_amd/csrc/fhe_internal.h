@@ -44,8 +44,9 @@ struct NttArgs {
   int ntr = 0;         // number of transforms (set by launch_ntt; a multiple of K)
 };
 
-// Fused last forward row pass + pointwise products + first inverse row pass over
-// cnum groups of transforms whose column passes ran separately.
+// The middle of a ring product: the row stages of the forward transforms, the pointwise
+// products and the row stages of the inverse transforms, over cnum groups of transforms
+// whose outer four stages run in the lift and the reconstruction.
 enum { ROWS_TENSOR = 0, ROWS_RELIN = 1, ROWS_RING = 2 };
 struct RowsArgs {
   uint32_t* data = nullptr;        // group c at data + c group_stride: tensor [4][K][N]; relin [K][N]; ring a [K][N]

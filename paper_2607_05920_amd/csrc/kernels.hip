@@ -35,8 +35,8 @@ void bracket_end(int kid, hipStream_t s, double work) {
 // These two passes serve key preparation and the standalone transforms that do not take
 // one workgroup each (ntt_whole.hip); the ring products have the outer four stages in the
 // lift and the reconstruction (lift_cols.hip, crt_cols.hip).  N = 2^logN is split as
-// N = n1 * n2 (the two-pass / four-step scheme of Section 5.3).  The n1-point stages run over columns {c + n2 u}; the n2-point stages run
-// over contiguous blocks.  Both passes use one kernel shape: a sub-transform of
+// N = n1 * n2 (the two-pass / four-step scheme of Section 5.3).  The n1-point stages run
+// over columns {c + n2 u}; the n2-point stages run over contiguous blocks.  Both passes use one kernel shape: a sub-transform of
 // n = 2^S points is held by T = n / 16 threads with 16 values each.  The first
 // register phase works on elements {u T + j} ("strided"), the other on
 // {16 j + u} ("contiguous"); one LDS exchange connects them.  Forward passes run
@@ -76,8 +76,9 @@ __device__ __forceinline__ void ntt_pass_kernel_body(const NttArgs& a, const Blk
   // p = x (mod 8).  A row pass takes them one at a time, and every transform of that
   // prime in turn, so a prime's twiddle table is read into one L2 once.  A column
   // pass reads only the first n entries of each table; the forward one goes through
-  // the transforms in descending order instead, all its primes for each, so that it
-  // starts on the residues the lift wrote last (the last-level cache still holds them).
+  // the transforms in descending order instead, all its primes for each, so that in key
+  // preparation it starts on the residues the lift wrote last (the last-level cache still
+  // holds them).
   const int nwg = (nsub_total + RPW - 1) / RPW;  // workgroups per transform (block)
   const int npp = a.ntr / a.K;                    // transforms per prime
   const int ncg = (npp + CG - 1) / CG;            // blocks of CG transforms per prime
@@ -447,16 +448,14 @@ __device__ __forceinline__ void rows_fused_kernel_body(const RowsArgs& a, const 
   const int sl = CG > 1 ? s / CG : s;  // sub-row within the workgroup
   const int N = 1 << a.logN;
   const int nsub_total = N / n;
-  // XCD-aware: workgroup w runs on XCD w % 8, which takes primes p = w % 8 (mod 8).
-  // The primes run in descending order, the reverse of the column passes, so that
-  // this pass starts on the rows the forward column pass wrote last and the inverse
-  // column pass on the rows this pass wrote last: those still sit in the device's
-  // last-level cache.
+  // XCD-aware: workgroup w runs on XCD w % 8, which takes primes p = w % 8 (mod 8), so that
+  // a prime's twiddles and key rows are read into one L2.  (Their order does not matter: up
+  // to 2^12 points all rows stay in the last-level cache; descending measured the same.)
   const int nwg = (nsub_total + RPW - 1) / RPW;
   const int ncg = (a.cnum + CG - 1) / CG;
   const int per_prime = ncg * nwg;
   const int w = bk.x, xcd = w & 7, l = w >> 3;
-  const int p = (((a.K + 7) >> 3) - 1 - l / per_prime) * 8 + xcd;
+  const int p = (l / per_prime) * 8 + xcd;
   if (p >= a.K) return;  // whole workgroup exits
   const int rem = l % per_prime;
   const int c = (rem / nwg) * CG;  // the group's first ciphertext

@@ -297,17 +297,22 @@ static hipError_t ntt_whole_dir(const NttArgs& a, bool inverse, bool natural, hi
 //   20.7 -> 13.0, natural 77 -> 13; 2^14, 9 x 1: 10.6 -> 9.4, 106 x 64: 452 -> 243.
 //   2^15: a transform takes 18 us on its one compute unit, so few of them are faster in two
 //   passes over many: 31 x 2: 14.7 against 18.8, 31 x 4: 21.1 against 20.5 (inverse 18.6
-//   against 19.8), 31 x 6: 27.9 against 21.0.  Natural order adds a permutation pass to the
-//   two: 5 x 1: 14 against 19, 31 x 4: 52 against 20.
+//   against 19.8), 31 x 6: 27.9 against 21.0.  So from five transforms per eight compute
+//   units on; with the second round's first transforms it gains less, but no more turns it:
+//   11 x 24 (1.03 rounds) 42.0 -> 38.4, inverse 41.1 -> 37.0, 13 x 40 (2.03) 65.9 -> 58.9,
+//   63.3 -> 58.1, 33 x 32 (4.1) 119 -> 96, 113 -> 99.  Natural order adds a permutation pass
+//   to the two: 5 x 1: 14 against 19, 4 x 8: 26.4 -> 18.3, 31 x 4: 52 -> 20; from one per
+//   eight units on.
 //   2^16: 46 us a round of one transform per compute unit, against 50 of two passes (54
 //   beyond the last-level cache): faster where the last round is nearly full or one of
 //   many: 31 x 8: 54.1 -> 50.1, 32 x 12 (1.5 rounds): 76.8 against 88.6, 32 x 16: 96.8 ->
 //   93.4, 53 x 16 (3.3 rounds): 153 against 172, 106 x 16 (6.6): 350 -> 340, 106 x 64: 1474
-//   -> 1216.  Natural order: 31 x 4: 92 -> 41, 106 x 64: 6798 -> 1233; 5 x 1: 17 against 42.
+//   -> 1216.  Natural order: 31 x 4: 92 -> 41, 106 x 64: 6798 -> 1233; 5 x 1: 17 against 42;
+//   4 x 16: 66 -> 39; from one per four units on.
 bool ntt_whole_wanted(int logN, bool natural, long long ntransforms, int cus) {
   if (logN <= 14) return true;
-  if (logN == 15) return ntransforms >= (natural ? 32 : 160);
-  if (natural) return ntransforms >= 64;
+  if (logN == 15) return 8 * ntransforms >= (natural ? 1 : 5) * (long long)cus;
+  if (natural) return 4 * ntransforms >= cus;
   const long long slots = (ntransforms + cus - 1) / cus * cus;  // at most one in 16 idle, or 8 full rounds
   return ntransforms > 8LL * cus || 15 * slots <= 16 * ntransforms;
 }
